@@ -238,17 +238,65 @@ __global__ void k_bg_clear_snap(uint8_t* snap, int32_t k) {
 }
 
 // graphs still in the rounds whose graph kept every vertex (no union this
-// round) get the complete fallback pass; *cnt counts them
-__global__ void k_bg_fallback(const int32_t* voff, const int32_t* voff2, const uint8_t* done, int32_t k,
-                              uint8_t* prun, int32_t* cnt) {
+// round) and whose bound no threshold lowered get the complete fallback pass; *cnt counts them
+__global__ void k_bg_fallback(const int32_t* voff, const int32_t* voff2, const uint8_t* done, const uint8_t* lowered,
+                              int32_t k, uint8_t* prun, int32_t* cnt) {
     int32_t c = 0;
     for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < k; i += gridDim.x * blockDim.x) {
-        const bool need = !done[i] && voff2[i + 1] - voff2[i] == voff[i + 1] - voff[i];
+        const bool need = !done[i] && !lowered[i] && voff2[i + 1] - voff2[i] == voff[i + 1] - voff[i];
         prun[i] = need;
         c += need;
     }
     c = wave_sum_i32(c);
     if (lane_id() == 0 && c) atomicAdd(cnt, c);
+}
+
+// graphs whose unions so far leave more than half of their vertices
+// (voff2: prefix counts of the component roots) go on to the next test;
+// *cnt counts them
+__global__ void k_bg_unhalved(const int32_t* voff, const int32_t* voff2, int32_t k, uint8_t* prun,
+                              int32_t* cnt) {
+    int32_t c = 0;
+    for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < k; i += gridDim.x * blockDim.x) {
+        if (2 * (int64_t)(voff2[i + 1] - voff2[i]) <= voff[i + 1] - voff[i]) prun[i] = 0;
+        c += prun[i];
+    }
+    c = wave_sum_i32(c);
+    if (lane_id() == 0 && c) atomicAdd(cnt, c);
+}
+
+// threshold of the loosely connected parts of the graphs in prun; out: the
+// other graphs
+__global__ void k_bg_target(const int64_t* lam, const uint8_t* prun, int32_t k, int64_t* target, uint8_t* out) {
+    for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < k; i += gridDim.x * blockDim.x) {
+        target[i] = lam[i] >= 4 ? lam[i] / 4 : 1;
+        out[i] = !prun[i];
+    }
+}
+
+// the smallest part (while there are two) bounds its graph: hit and lowered
+__global__ void k_bg_threshold(const int32_t* voff2, const int64_t* dmin, int32_t k, int64_t* lam, const uint8_t* prun,
+                               uint8_t* snap, uint8_t* hit, uint8_t* lowered) {
+    for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < k; i += gridDim.x * blockDim.x) {
+        hit[i] = prun[i] && voff2[i + 1] - voff2[i] >= 2 && dmin[i] < lam[i];
+        if (!hit[i]) continue;
+        lam[i] = dmin[i];
+        snap[i] = 3;
+        lowered[i] = 1;
+    }
+}
+
+__global__ void k_bg_drop(const uint8_t* lowered, int32_t k, uint8_t* prun) {
+    for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < k; i += gridDim.x * blockDim.x)
+        if (lowered[i]) prun[i] = 0;
+}
+
+__global__ void k_bg_part_side(const int32_t* vinst, const uint8_t* hit, const int32_t* part, const int32_t* darg,
+                               int32_t n, uint8_t* fside) {
+    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
+        const int32_t i = vinst[v];
+        if (hit[i]) fside[v] = part[v] == darg[i];
+    }
 }
 
 __global__ void k_bg_active(const uint8_t* done, int32_t k, uint8_t* prun) {
@@ -423,6 +471,7 @@ struct EngineWS {
     int64_t *best, *h_dmin;   // [K]
     int32_t* h_darg;          // [K]
     uint8_t* h_hit;           // [K]
+    uint8_t *lowered, *dead2; // [K] threshold bounds: graphs lowered, graphs left out (in gerr, free after the checks)
     PrivateArgs pv;
     unsigned long long* pmarks;
     unsigned long long* vpart;
@@ -488,6 +537,8 @@ void carve_engine(Arena& a, const Caps& cp, EngineWS& w) {
     w.h_dmin = a.take<int64_t>((size_t)K + 1);
     w.h_darg = a.take<int32_t>((size_t)K + 1);
     w.h_hit = a.take<uint8_t>((size_t)K + 1);
+    w.lowered = (uint8_t*)w.gerr;
+    w.dead2 = w.lowered + K;
     PrivateArgs& pv = w.pv;
     pv = PrivateArgs{};
     pv.passes = K;
@@ -858,7 +909,7 @@ struct Engine {
         EG_HIP(hipMemcpyAsync(w.dead, dead.data(), k, hipMemcpyHostToDevice, s));
         EG_OK(fill_u8(w.snap, 0, k, s));
         EG_OK(fill_i32(w.cnt, 0, 4, s));
-        EG_OK(fill_i64((int64_t*)&w.sc->marks_pr, 0, 3, s));
+        EG_OK(fill_i64((int64_t*)&w.sc->marks_pr, 0, 4, s));
         k_bg_vinst<<<grid_for(n, 256), 256, 0, s>>>(w.voff, k, n, w.vinst);
         k_bg_vinst<<<grid_for(n0_used, 256), 256, 0, s>>>(w.ioff, k, n0_used, w.inst0);
         EG_OK(mc_hip_ok(hipGetLastError(), "k_bg_vinst"));
@@ -896,6 +947,34 @@ struct Engine {
                        s, w.vinst));
         // one CAPFOREST pass per graph still in the rounds
         k_bg_active<<<grid_for(k, 256), 256, 0, s>>>(w.done, k, w.prun);
+        EG_OK(fill_u8(w.lowered, 0, k, s));
+        // in the automatic mode, as in the single solve, the edge-disjoint
+        // subgraphs' test runs on the graphs that the reduction tests do not
+        // halve, and CAPFOREST on those that neither halves (the test's
+        // arrays lie in the graph that this round's contraction will write)
+        if (c->opt.capforest_mode == MC_CF_AUTO && !c->opt.deterministic) {
+            CertArgs ca{};
+            ca.g = G;
+            ca.lam = w.lam;
+            ca.vinst = w.vinst;
+            ca.voff = w.voff;
+            ca.ngraphs = k;
+            ca.active = w.prun;
+            ca.parent = w.parent;
+            ca.marks = &w.sc->marks_cert;
+            char* const base = (char*)Nx.col;
+            const bool room = cert_carve(ca, base, (size_t)((char*)(Nx.w + Nx.cap) - base));
+            int32_t running = 0;
+            EG_OK(unhalved(k, &running));
+            if (room && running > 0) {
+                EG_OK(certify(ca, s));
+                EG_OK(unhalved(k, &running));
+                if (running > 0) {
+                    const mc_status r = threshold_bounds(G, ca, k);
+                    if (r != MC_OK) return r;
+                }
+            }
+        }
         PrivateArgs pa = w.pv;
         pa.g = G;
         pa.lam = w.lam;
@@ -915,9 +994,9 @@ struct Engine {
         pa.threads = c->opt.batch_pass_threads;
         EG_OK(capforest_private(pa, s, cap.nmax));
         k_bg_alpha<<<grid_for(k, 256), 256, 0, s>>>(pa.alpha, w.done, k, w.lam, w.snap);
-        EG_OK(labels(k));
+        EG_OK(labels(w.parent, w.dead));
         k_bg_offsets<<<grid_for(k + 1, 256), 256, 0, s>>>(w.flag, w.voff, k, w.voff2);
-        k_bg_fallback<<<grid_for(k, 256), 256, 0, s>>>(w.voff, w.voff2, w.done, k, w.prun, w.cnt);
+        k_bg_fallback<<<grid_for(k, 256), 256, 0, s>>>(w.voff, w.voff2, w.done, w.lowered, k, w.prun, w.cnt);
         EG_OK(mc_hip_ok(hipGetLastError(), "round"));
         int32_t hcnt[4];
         EG_HIP(hipMemcpyAsync(hcnt, w.cnt, sizeof(hcnt), hipMemcpyDeviceToHost, s));
@@ -932,7 +1011,7 @@ struct Engine {
             pf.round = round + 7777;
             EG_OK(capforest_private(pf, s, cap.nmax));
             k_bg_alpha<<<grid_for(k, 256), 256, 0, s>>>(pf.alpha, w.done, k, w.lam, w.snap);
-            EG_OK(labels(k));
+            EG_OK(labels(w.parent, w.dead));
             k_bg_offsets<<<grid_for(k + 1, 256), 256, 0, s>>>(w.flag, w.voff, k, w.voff2);
             EG_OK(mc_hip_ok(hipGetLastError(), "fallback"));
         }
@@ -1001,15 +1080,87 @@ struct Engine {
         return MC_OK;
     }
 
+    // drops the graphs that this round's unions have halved from prun;
+    // *running: those that stay
+    bool unhalved(int32_t k, int32_t* running) {
+        if (!uf_labels(w.parent, n, w.L, w.flag, w.cw.scan_tmp, w.sc, s) || !fill_i32(w.cnt + 1, 0, 1, s)) return false;
+        k_bg_offsets<<<grid_for(k + 1, 256), 256, 0, s>>>(w.flag, w.voff, k, w.voff2);
+        k_bg_unhalved<<<grid_for(k, 256), 256, 0, s>>>(w.voff, w.voff2, k, w.prun, w.cnt + 1);
+        MC_LAUNCHED("k_bg_unhalved");
+        MC_HIP(hipMemcpyAsync(running, w.cnt + 1, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+        MC_HIP(hipStreamSynchronize(s));
+        return true;
+    }
+
+    // Lower bounds of the graphs that no test halved (prun), from their more
+    // loosely connected parts: the edge-disjoint subgraphs' test at a quarter
+    // of each bound, the parts it joins contracted (the other graphs left
+    // out), and again on the coarse graphs, with tests 1 and 2, while they
+    // shrink. Every collapsed degree is a cut of its graph. A graph whose
+    // bound drops takes that part as its side and skips this round's
+    // CAPFOREST: the next round's tests see the lower bound. ca: the test's
+    // arguments at the graphs' bounds. The coarse graphs take the two
+    // union-graph buffers that are not current, the vertex maps the lists of
+    // CAPFOREST's passes, and the targets and flags admission's arrays.
+    mc_status threshold_bounds(const DGraph& G, CertArgs ca, int32_t k) {
+        int64_t* const target = w.h_dmin;
+        uint8_t* const left_out = w.dead2;
+        int32_t *const par = w.pv.order, *const inst = w.pv.fifo, *const map = w.pv.touched;
+        k_bg_target<<<grid_for(k, 256), 256, 0, s>>>(w.lam, w.prun, k, target, left_out);
+        EG_OK(mc_hip_ok(hipGetLastError(), "k_bg_target"));
+        EG_OK(iota_i32(map, n, s));
+        ca.lam = target;
+        ca.parent = par;
+        DGraph Gc = G;
+        int bi = (cur + 1) % 3;
+        const int32_t *vinst = w.vinst, *voff = w.voff;
+        for (int level = 0; level < 4; level++) {
+            const int32_t nc = Gc.n;
+            DGraph& Gn = w.g[bi];
+            ca.g = Gc;
+            ca.vinst = vinst;
+            ca.voff = voff;
+            char* const base = (char*)Gn.col;
+            EG_OK(uf_init(par, nc, s));
+            if (level > 0)
+                EG_OK(pr12(Gc, target, par, &w.sc->marks_cert, nullptr, nullptr, w.prw, s, vinst));
+            if (cert_carve(ca, base, (size_t)((char*)(Gn.w + Gn.cap) - base))) EG_OK(certify(ca, s));
+            EG_OK(labels(par, left_out, nc, vinst));
+            int32_t* const off2 = voff == w.voff2 ? w.h_off2 : w.voff2;
+            k_bg_offsets<<<grid_for(k + 1, 256), 256, 0, s>>>(w.flag, voff, k, off2);
+            EG_OK(mc_hip_ok(hipGetLastError(), "threshold parts"));
+            if (!readback()) return mc_fail(MC_E_DEVICE, "readback failed");
+            const int32_t n2 = c->hsc->n2;
+            if (level > 0 && (int64_t)n2 * 20 > (int64_t)nc * 19) break;
+            EG_OK(contract(Gc, w.L, n2, Gn, w.cw, w.sc, s));
+            EG_OK(map_update(map, w.L, n, s));
+            k_bg_segmin<<<std::min(k, 8192), 256, 0, s>>>(Gn.deg, off2, k, w.dmin, w.darg);
+            k_bg_threshold<<<grid_for(k, 256), 256, 0, s>>>(off2, w.dmin, k, w.lam, w.prun, w.snap, w.h_hit, w.lowered);
+            k_bg_part_side<<<grid_for(n, 256), 256, 0, s>>>(w.vinst, w.h_hit, map, w.darg, n, w.fside);
+            k_bg_vinst<<<grid_for(n2, 256), 256, 0, s>>>(off2, k, n2, inst);
+            EG_OK(mc_hip_ok(hipGetLastError(), "threshold bounds"));
+            Gc = Gn;
+            Gc.n = n2;
+            vinst = inst;
+            voff = off2;
+            bi = bi == (cur + 1) % 3 ? (cur + 2) % 3 : (cur + 1) % 3;
+        }
+        k_bg_side<<<grid_for(n0_used, 256), 256, 0, s>>>(w.side, w.map0, w.inst0, n0_used, w.snap, w.darg, w.inpref,
+                                                          w.fside);
+        k_bg_clear_snap<<<grid_for(k, 256), 256, 0, s>>>(w.snap, k);
+        k_bg_drop<<<grid_for(k, 256), 256, 0, s>>>(w.lowered, k, w.prun);
+        EG_OK(mc_hip_ok(hipGetLastError(), "threshold sides"));
+        return MC_OK;
+    }
+
     // labels of the round: canonical components, -1 for dead graphs
-    bool labels(int32_t k) {
-        const int32_t nn = n;
-        (void)k;
-        if (!uf_labels(w.parent, nn, w.L, w.flag, w.cw.scan_tmp, w.sc, s)) return false;   // compresses
-        k_root_flag_live<<<grid_for(nn, 256), 256, 0, s>>>(w.parent, w.vinst, w.dead, nn, w.flag);
+    bool labels(int32_t* parent, const uint8_t* dead) { return labels(parent, dead, n, w.vinst); }
+    bool labels(int32_t* parent, const uint8_t* dead, int32_t nn, const int32_t* vinst) {
+        if (!uf_labels(parent, nn, w.L, w.flag, w.cw.scan_tmp, w.sc, s)) return false;   // compresses
+        k_root_flag_live<<<grid_for(nn, 256), 256, 0, s>>>(parent, vinst, dead, nn, w.flag);
         if (!mc_hip_ok(hipGetLastError(), "k_root_flag_live")) return false;
         if (!scan_i32(w.flag, w.flag, nn, w.cw.scan_tmp, s)) return false;
-        k_label_live<<<grid_for(nn, 256), 256, 0, s>>>(w.parent, w.flag, w.vinst, w.dead, nn, w.L, w.sc);
+        k_label_live<<<grid_for(nn, 256), 256, 0, s>>>(parent, w.flag, vinst, dead, nn, w.L, w.sc);
         return mc_hip_ok(hipGetLastError(), "k_label_live");
     }
 

@@ -1,0 +1,334 @@
+// Connectivity certificates by edge-disjoint subgraphs: a reduction test that
+// contracts the well-connected bulk of a graph in one step, where CAPFOREST
+// (Algorithm 1) would take a chain of single pops.
+//
+// The weight of every edge is split over k subgraphs: with c = ceil(lam / K)
+// and k = ceil(lam / c) an edge of weight w has floor(w / c) units of weight
+// c, and each subgraph may use one unit of it. Vertices that are connected
+// in all k subgraphs are joined by k paths whose units do not overlap, so
+// every cut between them weighs at least k c >= lam: they may be contracted,
+// as test-1 edges may (the forests of Nagamochi and Ibaraki, which CAPFOREST
+// follows, are edge-disjoint in the same sense; here the subgraphs need no
+// scan order, only components). How the units are dealt out is free:
+//  - an edge belongs to its endpoint of smaller degree (coarse logarithm,
+//    then id), so a vertex of small degree spends its own edges on itself
+//    and hangs as a leaf below heavier ones;
+//  - a vertex deals its units round-robin over the subgraphs, from a hashed
+//    first one (from subgraph 0 the last subgraphs would get fewest units:
+//    on Erdos-Renyi graphs of mean degree 32 and weights to 100 the weakest
+//    subgraph's largest component is then 23 % of the vertices at K = 16, and
+//    98 % with hashed starts). The first two rounds, 2 k units, are used.
+// The first unit of a vertex in a subgraph points to a heavier vertex, so the
+// first round is a forest written without atomics; the second round is
+// linked by union-find over its compressed trees. All k subgraphs are built
+// side by side (one row of k n parents), so the test is a dozen launches
+// whatever k is.
+//
+// The vertices connected in every subgraph to a reference (of 64 sampled
+// vertices the one with most samples in its class) are joined directly: one
+// coalesced comparison of k words a vertex. Others look for a neighbour of
+// their own class among their first CERT_NEAR entries.
+//
+// Solves on MI355X, with CAPFOREST alone and with this test before it:
+// Erdos-Renyi, 300,000 vertices, mean degree 24, weights to 1000: 174 and
+// 7.6 ms; Chung-Lu 2^20 and 2^22, 10-cores, unit weights: 6.9 and 4.7 ms, 14.0
+// and 11.1 ms.
+//
+// The kernels are bound by the k n random reads of the two compressions and
+// of the linking, not by the rows: one pass over the entries (12 B each, and
+// a one-byte gather) deals out the units.
+#include "mc_internal.h"
+
+namespace {
+
+constexpr int SUB = 16;          // lanes per row
+constexpr int ROWS = 64;         // rows dealt out by one workgroup at a time
+constexpr int32_t CERT_ROW = 4096;   // entries of a row looked at (a long row is a heavy vertex, which owns little)
+constexpr int CERT_NEAR = 16;
+
+inline int grid_for(int64_t count, int threads, int cap = 8192) {
+    int64_t b = (count + threads - 1) / threads;
+    if (b < 1) b = 1;
+    if (b > cap) b = cap;
+    return (int)b;
+}
+
+__device__ __forceinline__ bool inactive(const CertArgs& a, int64_t v) {
+    return a.active && !a.active[a.vinst[v]];
+}
+
+// unit weight c and subgraph count k of every graph; no member yet
+__global__ void k_cert_plan(CertArgs a) {
+    for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < a.ngraphs; i += gridDim.x * blockDim.x) {
+        const int64_t lam = a.lam[i];
+        const int64_t c = lam > a.kc ? (lam + a.kc - 1) / a.kc : 1;
+        a.unit[i] = c;
+        a.count[i] = lam > 0 ? (int32_t)((lam + c - 1) / c) : 0;
+        a.rep[i] = INT32_MAX;
+    }
+}
+
+// degree class: two bits below the leading one, so degrees within 25 % of
+// each other may share a class
+__global__ void k_cert_level(CertArgs a) {
+    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < a.g.n; v += (int64_t)gridDim.x * blockDim.x) {
+        const uint64_t d = (uint64_t)a.g.deg[v] | 1;
+        const int e = 63 - __clzll((long long)d);
+        a.level[v] = (uint8_t)((e << 2) | (int)((e >= 2 ? d >> (e - 2) : d << (2 - e)) & 3));
+    }
+}
+
+// Deals every row's units out: own[r * kc + i][v] = target of v's unit in
+// subgraph i, round r. Round 0 is written as a parent (v itself without a
+// unit), round 1 as a target or -1. A workgroup stages ROWS rows in LDS and
+// writes each subgraph's words of them side by side.
+__global__ __launch_bounds__(256) void k_cert_rows(CertArgs a) {
+    __shared__ int32_t tile[ROWS][2 * CERT_KMAX + 1];
+    const int kc2 = 2 * a.kc;
+    const int sl = threadIdx.x % SUB, sub = threadIdx.x / SUB;
+    const int32_t n = a.g.n;
+    for (int64_t v0 = (int64_t)blockIdx.x * ROWS; v0 < n; v0 += (int64_t)gridDim.x * ROWS) {
+        for (int i = threadIdx.x; i < ROWS * kc2; i += 256) tile[i / kc2][i % kc2] = -1;
+        __syncthreads();
+        for (int q = sub; q < ROWS; q += 256 / SUB) {
+            const int64_t v = v0 + q;
+            if (v >= n || inactive(a, v)) continue;
+            const int32_t inst = a.vinst ? a.vinst[v] : 0;
+            const int64_t c = a.unit[inst];
+            const int32_t k = a.count[inst];
+            const int32_t o = a.g.off[v], l = a.g.len[v] < CERT_ROW ? a.g.len[v] : CERT_ROW;
+            const int lv = a.level[v];
+            const int32_t first = (int32_t)(((uint64_t)hash32((uint32_t)v) * (uint64_t)k) >> 32);
+            int32_t base = 0;
+            for (int32_t j0 = 0; j0 < l && base < 2 * k; j0 += 4 * SUB) {
+                int32_t x[4], lx[4];
+                int64_t w[4];
+#pragma unroll
+                for (int u = 0; u < 4; u++) {
+                    const int32_t j = j0 + u * SUB + sl;
+                    x[u] = j < l ? a.g.col[o + j] : -1;
+                    w[u] = j < l ? a.g.w[o + j] : 0;
+                }
+#pragma unroll
+                for (int u = 0; u < 4; u++) lx[u] = w[u] >= c && x[u] >= 0 ? a.level[x[u]] : -1;
+#pragma unroll
+                for (int u = 0; u < 4; u++) {
+                    int32_t units = 0;
+                    if (lx[u] > lv || (lx[u] == lv && x[u] > v)) {
+                        int64_t left = w[u];
+#pragma unroll
+                        for (int b = 5; b >= 0; b--)
+                            if ((left >> b) >= c) { left -= c << b; units += 1 << b; }
+                        if (units > k) units = k;
+                    }
+                    int32_t incl = units;
+#pragma unroll
+                    for (int d = 1; d < SUB; d <<= 1) {
+                        const int32_t t = __shfl_up(incl, d, SUB);
+                        if (sl >= d) incl += t;
+                    }
+                    const int32_t start = base + incl - units;
+                    base += __shfl(incl, SUB - 1, SUB);
+                    for (int32_t t = start; t < start + units && t < 2 * k; t++) {
+                        const int r = t >= k;
+                        int32_t i = t - (r ? k : 0) + first;
+                        if (i >= k) i -= k;
+                        tile[q][r * a.kc + i] = x[u];
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        for (int i = threadIdx.x; i < ROWS * kc2; i += 256) {
+            const int slot = i / ROWS, q = i % ROWS;
+            const int64_t v = v0 + q;
+            if (v >= n) continue;
+            int32_t t = tile[q][slot];
+            if (t < 0 && slot < a.kc) t = (int32_t)v;
+            a.own[(int64_t)slot * n + v] = t;
+        }
+        __syncthreads();
+    }
+}
+
+// every vertex at its root, in every subgraph (blockIdx.y)
+__global__ __launch_bounds__(256) void k_cert_compress(CertArgs a) {
+    const int32_t n = a.g.n;
+    const int i = blockIdx.y;
+    int32_t* par = a.own + (int64_t)i * n;
+    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
+        if (inactive(a, v) || i >= a.count[a.vinst ? a.vinst[v] : 0]) continue;
+        int32_t x = (int32_t)v, p = ld_acq(&par[x]);
+        while (p != x) { x = p; p = ld_acq(&par[x]); }
+        st_rel(&par[v], x);
+    }
+}
+
+// The second round's units join the trees of the first: in a sweep a root
+// hangs under a heavier root next to one of its tree's vertices (the order of
+// the first round, so whichever of the racing stores stays, no cycle
+// arises), with a compression after it. Two sweeps leave few trees, and only
+// then does the linking use compare-and-swap (LINK): with it alone every
+// thread of a tree meets at the words of a few roots (8.7 ms at 300,000
+// vertices, k = 32; sweeps, link and their compressions together 1.3 ms).
+template <bool LINK>
+__global__ __launch_bounds__(256) void k_cert_join_trees(CertArgs a) {
+    const int32_t n = a.g.n;
+    const int i = blockIdx.y;
+    int32_t* par = a.own + (int64_t)i * n;
+    const int32_t* next = a.own + (int64_t)(a.kc + i) * n;
+    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
+        if (inactive(a, v) || i >= a.count[a.vinst ? a.vinst[v] : 0]) continue;
+        const int32_t u = next[v];
+        if (u < 0) continue;
+        // a parent read during a sweep may be a root that has been hung
+        // already, or its new root: an ancestor either way
+        int32_t x = ld_acq(&par[v]), y = ld_acq(&par[u]);
+        while (x != y) {
+            if (LINK) {
+                for (int32_t p = ld_acq(&par[x]); p != x; p = ld_acq(&par[x])) x = p;
+                for (int32_t p = ld_acq(&par[y]); p != y; p = ld_acq(&par[y])) y = p;
+                if (x == y) break;
+            }
+            const int lx = a.level[x], ly = a.level[y];
+            const bool up = lx > ly || (lx == ly && x > y);   // x is the heavier
+            const int32_t from = up ? y : x, to = up ? x : y;
+            if (LINK) {
+                if (atomicCAS(&par[from], from, to) == from) break;
+            } else {
+                if (ld_acq(&par[from]) == from) st_rel(&par[from], to);
+                break;
+            }
+        }
+    }
+}
+
+// the reference vertex of every graph: of 64 samples the one that shares its
+// class (a hash of its components) with most of them, one wavefront a graph
+__global__ __launch_bounds__(64) void k_cert_ref(CertArgs a) {
+    const int lane = lane_id();
+    for (int32_t gi = blockIdx.x; gi < a.ngraphs; gi += gridDim.x) {
+        if (a.active && !a.active[gi]) continue;
+        const int32_t base = a.voff ? a.voff[gi] : 0;
+        const int32_t n = a.voff ? a.voff[gi + 1] - base : a.g.n;
+        const int32_t k = a.count[gi];
+        if (n < 1) continue;
+        const int32_t v = base + (int32_t)(((uint64_t)hash32(lane * 2654435761u + 777u) * (uint64_t)n) >> 32);
+        uint32_t h = 0;
+#pragma unroll 8
+        for (int i = 0; i < k; i++) h += hash32((uint32_t)a.own[(int64_t)i * a.g.n + v] + 0x9E3779B9u * (uint32_t)i);
+        int64_t same = 0;
+        for (int q = 0; q < MC_WAVE; q++) same += __shfl(h, q, MC_WAVE) == h;
+        int32_t id = lane, aux = v;
+        wave_argmax(same, id, aux);
+        if (lane == 0) a.ref[gi] = aux;
+    }
+}
+
+__global__ __launch_bounds__(256) void k_cert_member(CertArgs a) {
+    const int32_t n = a.g.n;
+    for (int64_t v0 = (int64_t)blockIdx.x * blockDim.x; v0 < n; v0 += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t v = v0 + threadIdx.x;
+        bool in = false;
+        int32_t inst = 0;
+        if (v < n) {
+            inst = a.vinst ? a.vinst[v] : 0;
+            if (!a.active || a.active[inst]) {
+                const int32_t ref = a.ref[inst], k = a.count[inst];
+                int i = 0;
+                while (i < k && a.own[(int64_t)i * n + v] == a.own[(int64_t)i * n + ref]) i++;
+                in = k > 0 && i == k;
+            }
+            a.member[v] = in;
+        }
+        // a graph's first member in the wavefront (a graph's lanes are
+        // consecutive) bounds the class's smallest vertex
+        const int lane = lane_id();
+        const int32_t before = __shfl_up(inst, 1, MC_WAVE);
+        const unsigned long long starts = __ballot(lane == 0 || before != inst);
+        const int start = 63 - __clzll((long long)(starts & (~0ULL >> (63 - lane))));
+        const unsigned long long m = __ballot(in);
+        const bool head = in && ((m & ((1ULL << lane) - 1)) >> start) == 0;
+        if (head && (int32_t)v < ld_acq(&a.rep[inst])) atomicMin(&a.rep[inst], (int32_t)v);
+    }
+}
+
+// Members join the class's smallest vertex, each from its own root, so the
+// unions do not meet at one word; the others look among their first entries.
+// The workgroup counts its unions and adds them once.
+__global__ __launch_bounds__(256) void k_cert_join(CertArgs a) {
+    __shared__ int32_t sum[256 / MC_WAVE];
+    const int32_t n = a.g.n;
+    int32_t joined = 0;
+    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
+        const int32_t inst = a.vinst ? a.vinst[v] : 0;
+        if (a.active && !a.active[inst]) continue;
+        if (a.member[v]) {
+            if (uf_union(a.parent, (int32_t)v, a.rep[inst])) joined++;
+            continue;
+        }
+        const int32_t o = a.g.off[v], l = a.g.len[v] < CERT_NEAR ? a.g.len[v] : CERT_NEAR, k = a.count[inst];
+        for (int32_t j = 0; j < l; j++) {
+            const int32_t u = a.g.col[o + j];
+            if (a.member[u]) continue;
+            int i = 0;
+            while (i < k && a.own[(int64_t)i * n + v] == a.own[(int64_t)i * n + u]) i++;
+            if (i < k || k == 0) continue;
+            if (uf_union(a.parent, (int32_t)v, u)) joined++;
+            break;
+        }
+    }
+    joined = wave_sum_i32(joined);
+    if (lane_id() == 0) sum[threadIdx.x / MC_WAVE] = joined;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int32_t t = 0;
+        for (int q = 0; q < 256 / MC_WAVE; q++) t += sum[q];
+        if (t) atomicAdd(a.marks, (unsigned long long)t);
+    }
+}
+
+}  // namespace
+
+// Carves the test's arrays out of [base, base + bytes): the most subgraphs
+// that fit, at most CERT_KMAX. False when fewer than CERT_KMIN fit.
+bool cert_carve(CertArgs& a, void* base, size_t bytes) {
+    const size_t n = (size_t)a.g.n, k = (size_t)a.ngraphs;
+    const size_t fixed = 2 * n + 20 * k + 8 * 256;   // the other arrays and their alignment
+    if (bytes < fixed) return false;
+    const size_t kc = (bytes - fixed) / (n * 2 * sizeof(int32_t));
+    if (kc < (size_t)CERT_KMIN) return false;
+    a.kc = (int32_t)(kc < (size_t)CERT_KMAX ? kc : (size_t)CERT_KMAX);
+    Arena m;
+    m.base = (char*)base;
+    m.size = bytes;
+    a.unit = m.take<int64_t>(k);
+    a.count = m.take<int32_t>(k);
+    a.ref = m.take<int32_t>(k);
+    a.rep = m.take<int32_t>(k);
+    a.level = m.take<uint8_t>(n);
+    a.member = m.take<uint8_t>(n);
+    a.own = m.take<int32_t>(2 * (size_t)a.kc * n);
+    return m.used <= bytes;
+}
+
+bool certify(const CertArgs& a, hipStream_t s) {
+    const int32_t n = a.g.n;
+    const dim3 grid(grid_for(n, 256, 1024), a.kc);
+    k_cert_plan<<<grid_for(a.ngraphs, 256), 256, 0, s>>>(a);
+    k_cert_level<<<grid_for(n, 256), 256, 0, s>>>(a);
+    k_cert_rows<<<grid_for(n, ROWS), 256, 0, s>>>(a);
+    MC_LAUNCHED("k_cert_rows");
+    k_cert_compress<<<grid, 256, 0, s>>>(a);
+    for (int sweep = 0; sweep < 2; sweep++) {
+        k_cert_join_trees<false><<<grid, 256, 0, s>>>(a);
+        k_cert_compress<<<grid, 256, 0, s>>>(a);
+    }
+    k_cert_join_trees<true><<<grid, 256, 0, s>>>(a);
+    k_cert_compress<<<grid, 256, 0, s>>>(a);
+    k_cert_ref<<<a.ngraphs < 4096 ? a.ngraphs : 4096, 64, 0, s>>>(a);
+    k_cert_member<<<grid_for(n, 256), 256, 0, s>>>(a);
+    k_cert_join<<<grid_for(n, 256, 1024), 256, 0, s>>>(a);
+    MC_LAUNCHED("certify");
+    return true;
+}

@@ -190,6 +190,37 @@ void pr12_ws_carve(Arena& a, int32_t n, int64_t cap, Pr12WS& w);
 bool pr12(const DGraph& g, const int64_t* lam, int32_t* parent, unsigned long long* marks,
           uint8_t* flag1, int32_t* ptr2, Pr12WS& w, hipStream_t s, const int32_t* vinst = nullptr);
 
+// Reduction test by edge-disjoint subgraphs (mc_certify.hip): the vertices
+// connected in every one of k subgraphs whose units of weight c >= lam / k
+// do not overlap are unioned in parent; *marks counts the unions. g is a
+// simple graph with deg set. Single form: ngraphs = 1, lam one value, vinst,
+// voff and active null. Batched form: graph i's vertices are [voff[i],
+// voff[i+1]), vinst their graph, and only graphs with active[i] take part.
+constexpr int CERT_KMAX = 32;
+constexpr int CERT_KMIN = 8;
+struct CertArgs {
+    DGraph g;
+    const int64_t* lam;      // [ngraphs]
+    const int32_t* vinst;
+    const int32_t* voff;
+    int32_t ngraphs;
+    const uint8_t* active;
+    int32_t* parent;
+    unsigned long long* marks;
+    // carved by cert_carve
+    int32_t kc;              // subgraphs there is room for
+    int64_t* unit;           // [ngraphs] c
+    int32_t* count;          // [ngraphs] k <= kc
+    int32_t* ref;            // [ngraphs] reference vertex
+    int32_t* rep;            // [ngraphs] smallest vertex of the reference's class
+    uint8_t* level;          // [n] degree class
+    uint8_t* member;         // [n] in the reference's class
+    int32_t* own;            // [2 kc][n] parents of the subgraphs, then the second round's targets
+};
+bool cert_carve(CertArgs& a, void* base, size_t bytes);
+bool certify(const CertArgs& a, hipStream_t s);
+
+
 // Padberg-Rinaldi tests 3 and 4 on the edges whose rows both have at most
 // D (<= 64) entries; test-4 edges and the accepted test-3 matching (mutual
 // smallest partners touching no test-2 pointer of ptr2) are unioned into

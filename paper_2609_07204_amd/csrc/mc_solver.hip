@@ -39,6 +39,7 @@ __global__ void k_reset_round(DevScalars* sc) {
     sc->marks_pr = 0;
     sc->marks_cf = 0;
     sc->marks_tri = 0;
+    sc->marks_cert = 0;
     sc->err = 0;
     sc->best_pass = -1;
     sc->best_alpha = INT64_MAX;
@@ -557,6 +558,8 @@ struct Solver {
     int64_t lam = 0;
     bool debug = false;
     bool tri_on = false;          // reduction tests 3 and 4 still pay off
+    bool cert_on = true;          // the edge-disjoint subgraphs' test still pays off
+    bool bound_tried = false;     // threshold_bound has run
     bool in_heuristic = false;    // exact rounds on the heuristic's coarse graph
     bool conn_pending = false;    // connectivity not decided yet (the heuristic's coarse graph decides it)
     bool lp1_ready = false;       // the input pass left the first LP round of the input in lab2
@@ -590,6 +593,20 @@ struct Solver {
         const unsigned long long t = c->hsc->marks_tri;
         stats.marks_tri += (int64_t)t;
         if (t * 100 < (unsigned long long)n) tri_on = false;
+    }
+
+    // The edge-disjoint subgraphs' test on g at the bound in sc->lam, in the
+    // memory of the graph the next contraction will write.
+    bool certificates(const DGraph& g, const DGraph& free_graph) {
+        CertArgs a{};
+        a.g = g;
+        a.lam = &w.sc->lam;
+        a.ngraphs = 1;
+        a.parent = w.parent;
+        a.marks = &w.sc->marks_cert;
+        char* const base = (char*)free_graph.col;
+        if (!cert_carve(a, base, (size_t)((char*)(free_graph.w + free_graph.cap) - base))) return true;
+        return certify(a, s) && readback();
     }
 
     // passes of the private form on an n-vertex round
@@ -848,6 +865,75 @@ static mc_status finish(Solver& S, DGraph* cur, int32_t round) {
     return MC_OK;
 }
 
+// Contract cur by labels L (n2 groups) into g[*nxt_idx]; the collapsed
+// degrees of the result bound lambda (Section 2.1 "Overall algorithm"; only
+// while at least two vertices remain). Returns the new current graph.
+static DGraph* contract_and_bound(Solver& S, DGraph* cur, int32_t n2, int* nxt_idx, mc_status* err) {
+    SolveWS& w = S.w;
+    hipStream_t s = S.s;
+    DGraph* nxt = &w.g[*nxt_idx];
+    *err = MC_E_DEVICE;
+    if (!contract(entries_view(*cur, S.cur_m), w.L, n2, *nxt, w.cw, w.sc, s) || !map_update(w.map0, w.L, S.n0, s) ||
+        !S.readback())
+        return nullptr;
+    const DevScalars h = *S.c->hsc;
+    S.cur_m = h.m2;
+    if (n2 >= 2 && h.dmin < S.lam) {
+        if (!side_from_vertex(w.side, w.map0, S.n0, &w.sc->dmin_arg, s) || !S.set_lam(h.dmin)) return nullptr;
+    }
+    *nxt_idx = *nxt_idx == 1 ? 2 : 1;
+    *err = MC_OK;
+    return nxt;
+}
+
+// A lower bound from the input's loosely connected parts. The tests that
+// certify connections of weight lam / 4 (test 1 and the edge-disjoint
+// subgraphs; test 2 holds at any bound) are applied until little changes, and
+// the parts they join are contracted: a cut of the coarse graph is a cut of
+// the input, so its collapsed degrees and, once it is small enough, its
+// exact minimum (the finisher) bound lambda. A cut below lam / 4 is never
+// crossed by these unions, so it survives in the coarse graph. What it is
+// for: two dense communities joined by a few light edges, where a pass of
+// CAPFOREST finds the cut only after it has scanned one of them, pop by pop
+// (planted 2 x 1000, 12-regular, weights to 10, bound 36, lambda 5: 5.2 ms a
+// solve by CAPFOREST, 1.15 ms with the parts at a threshold of 9),
+// and the angular sectors of hyperbolic graphs. Runs on the input, whose two
+// spare graph buffers it takes, once per solve.
+constexpr int64_t kBoundShare = 4;
+static mc_status threshold_bound(Solver& S, int32_t round) {
+    SolveWS& w = S.w;
+    hipStream_t s = S.s;
+    const int64_t m0 = S.cur_m;
+    const int64_t target = S.lam / kBoundShare;
+    if (target < 1) return MC_OK;
+    DGraph* cur = &w.g[0];
+    int nxt_idx = 1;
+    mc_status err = MC_OK;
+    while (cur->n > 2 && (cur == &w.g[0] || cur->n > finish_max_n(S.c))) {
+        const int32_t n = cur->n;
+        k_reset_round<<<1, 1, 0, s>>>(w.sc);
+        k_set_lam<<<1, 1, 0, s>>>(w.sc, target);
+        if (!uf_init(w.parent, n, s) ||
+            !pr12(*cur, &w.sc->lam, w.parent, &w.sc->marks_pr, nullptr, nullptr, w.prw, s) ||
+            !S.certificates(*cur, w.g[nxt_idx]) || !uf_labels(w.parent, n, w.L, w.flag, w.cw.scan_tmp, w.sc, s) ||
+            !S.set_lam(S.lam) || !S.readback())
+            return MC_E_DEVICE;
+        const int32_t n2 = S.c->hsc->n2;
+        if (S.debug)
+            fprintf(stderr, "[mc] threshold %lld: n=%d -> %d, lam=%lld\n", (long long)target, n, n2, (long long)S.lam);
+        if (n2 < 2 || (int64_t)n2 * 20 > (int64_t)n * 19) break;
+        cur = contract_and_bound(S, cur, n2, &nxt_idx, &err);
+        if (!cur) return err;
+    }
+    if (cur != &w.g[0]) {
+        if (cur->n > 2 && cur->n <= finish_max_n(S.c) && (err = finish(S, cur, round)) != MC_OK) return err;
+        if (S.debug) fprintf(stderr, "[mc] threshold bound: lam=%lld\n", (long long)S.lam);
+        if (!iota_i32(w.map0, S.n0, s)) return MC_E_DEVICE;
+    }
+    S.cur_m = m0;
+    return MC_OK;
+}
+
 // Exact rounds of Algorithm 2 on w.g[src] until at most two vertices remain.
 static mc_status exact_rounds(Solver& S, int src) {
     SolveWS& w = S.w;
@@ -873,9 +959,31 @@ static mc_status exact_rounds(Solver& S, int src) {
         // now and leave CAPFOREST to the smaller graph of the next round
         // (any set of contractible edges is a valid round)
         if (!S.readback()) return MC_E_DEVICE;
-        S.tri_account(n);
-        const bool skip_cf = 2 * (int64_t)(S.c->hsc->marks_pr + S.c->hsc->marks_tri) >= n;
+        bool skip_cf = 2 * (int64_t)(S.c->hsc->marks_pr + S.c->hsc->marks_tri) >= n;
+        // in the automatic mode the edge-disjoint subgraphs' test comes
+        // before CAPFOREST; when both kinds of tests together halve the
+        // graph, CAPFOREST is left out
+        if (!skip_cf && !det && S.c->opt.capforest_mode == MC_CF_AUTO && S.cert_on) {
+            if (!S.certificates(*cur, *nxt)) return MC_E_DEVICE;
+            // left out for the rest of the solve once it joins fewer than
+            // one vertex in 32
+            if (S.c->hsc->marks_cert * 32 < (unsigned long long)n) S.cert_on = false;
+            skip_cf = 2 * (int64_t)(S.c->hsc->marks_pr + S.c->hsc->marks_tri + S.c->hsc->marks_cert) >= n;
+            if (S.debug)
+                fprintf(stderr, "[mc] round %d edge-disjoint subgraphs: n=%d lam=%lld marks_pr=%llu marks_cert=%llu\n", round, n,
+                        (long long)S.lam, S.c->hsc->marks_pr, S.c->hsc->marks_cert);
+        }
         int used = CF_RUN_NONE;   // the CAPFOREST form whose results the round keeps last
+        if (!skip_cf && !det && S.c->opt.capforest_mode == MC_CF_AUTO && cur == &w.g[0] && !S.bound_tried) {
+            // the input resists the tests at its bound: look for a lower
+            // bound among its more loosely connected parts, then run the
+            // round again (the unions were made over)
+            S.bound_tried = true;
+            const mc_status r = threshold_bound(S, round);
+            if (r != MC_OK) return r;
+            continue;
+        }
+        S.tri_account(n);
         if (skip_cf) {
             S.stats.rounds_pr_only++;
         } else if (det) {
@@ -939,9 +1047,9 @@ static mc_status exact_rounds(Solver& S, int src) {
         if (!S.apply_alpha(used, n)) return MC_E_DEVICE;
         if (!S.readback()) return MC_E_DEVICE;
         DevScalars h = *S.c->hsc;
-        S.stats.marks_pr += (int64_t)(h.marks_pr + h.marks_tri);
+        S.stats.marks_pr += (int64_t)(h.marks_pr + h.marks_tri + h.marks_cert);
         S.stats.marks_capforest += (int64_t)h.marks_cf;
-        const unsigned long long marks0 = h.marks_pr + h.marks_tri + h.marks_cf;
+        const unsigned long long marks0 = h.marks_pr + h.marks_tri + h.marks_cert + h.marks_cf;
         // Algorithm 2: no contractible edge found, run CAPFOREST over the
         // whole graph without a length limit; with a fixed bound it marks at
         // least one edge, otherwise it lowered the bound. The same complete
@@ -1012,9 +1120,6 @@ static mc_status exact_rounds(Solver& S, int src) {
     return MC_OK;
 }
 
-// Contract cur by labels L (n2 groups) into g[*nxt_idx]; the collapsed
-// degrees of the result bound lambda (Section 2.1 "Overall algorithm"; only
-// while at least two vertices remain). Returns the new current graph.
 // lambda = 0 iff the input is disconnected. g is the input or a contraction
 // of it that merged vertices of one component only (map0 takes input
 // vertices to g's vertices): such a contraction keeps every component
@@ -1033,24 +1138,6 @@ static bool check_connected(Solver& S, const DGraph& g) {
         if (!side_from_components(w.side, w.parent, &g == &w.g[0] ? nullptr : w.map0, S.n0, s)) return false;
     }
     return true;
-}
-
-static DGraph* contract_and_bound(Solver& S, DGraph* cur, int32_t n2, int* nxt_idx, mc_status* err) {
-    SolveWS& w = S.w;
-    hipStream_t s = S.s;
-    DGraph* nxt = &w.g[*nxt_idx];
-    *err = MC_E_DEVICE;
-    if (!contract(entries_view(*cur, S.cur_m), w.L, n2, *nxt, w.cw, w.sc, s) || !map_update(w.map0, w.L, S.n0, s) ||
-        !S.readback())
-        return nullptr;
-    const DevScalars h = *S.c->hsc;
-    S.cur_m = h.m2;
-    if (n2 >= 2 && h.dmin < S.lam) {
-        if (!side_from_vertex(w.side, w.map0, S.n0, &w.sc->dmin_arg, s) || !S.set_lam(h.dmin)) return nullptr;
-    }
-    *nxt_idx = *nxt_idx == 1 ? 2 : 1;
-    *err = MC_OK;
-    return nxt;
 }
 
 // The inexact heuristic that lowers the bound before the exact rounds
