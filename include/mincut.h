@@ -67,7 +67,11 @@ typedef struct {
     uint64_t seed;            /* start vertices of CAPFOREST passes */
     int32_t heuristic_min_n;  /* run the label-propagation bound only when
                                  n >= this (Section 4, session 2 item 2;
-                                 default 10000; <= 0 disables it) */
+                                 default 10000; <= 0 disables it). In the
+                                 automatic capforest_mode the reduction tests
+                                 come first, and where they at least halve
+                                 the input, their contraction takes the
+                                 bound's place */
     int32_t lp_iters;         /* label-propagation rounds per coarsening level
                                  (default 2) */
     int32_t pr_tri_deg_cap;   /* reduction tests 3 and 4 on edges whose two
@@ -85,7 +89,11 @@ typedef struct {
                                  private visited state that scan capped
                                  vertices in batches; MC_CF_SHARED: passes
                                  that share one visited array (Algorithm 1 as
-                                 printed); MC_CF_AUTO (default): on the first
+                                 printed); MC_CF_AUTO (default): a test by
+                                 edge-disjoint subgraphs and a bound from
+                                 loosely connected parts come before
+                                 CAPFOREST, which runs where they do not
+                                 halve the graph; on the first
                                  round of each size regime (at least / below
                                  levels_min_n vertices) that runs CAPFOREST,
                                  a short probe of shared passes (four per
@@ -132,9 +140,12 @@ typedef struct {
 
 typedef struct {
     int32_t rounds;              /* exact-phase rounds */
-    int32_t heuristic_levels;    /* coarsening levels of the bound heuristic */
+    int32_t heuristic_levels;    /* coarsening levels of the bound heuristic (1
+                                    when the reduction tests' contraction of
+                                    the input takes its place) */
     int64_t lambda_min_degree;   /* bound from the minimum degree */
-    int64_t lambda_heuristic;    /* bound after the heuristic (-1: not run) */
+    int64_t lambda_heuristic;    /* bound after the heuristic, or after that
+                                    contraction (-1: neither) */
     int64_t marks_pr;            /* edges unioned by the reduction tests */
     int64_t marks_capforest;     /* edges unioned by CAPFOREST */
     int32_t fallback_passes;     /* sequential CAPFOREST runs (Algorithm 2) */

@@ -29,10 +29,10 @@
 // coalesced comparison of k words a vertex. Others look for a neighbour of
 // their own class among their first CERT_NEAR entries.
 //
-// Solves on MI355X, with CAPFOREST alone and with this test before it:
-// Erdos-Renyi, 300,000 vertices, mean degree 24, weights to 1000: 174 and
-// 7.6 ms; Chung-Lu 2^20 and 2^22, 10-cores, unit weights: 6.9 and 4.7 ms, 14.0
-// and 11.1 ms.
+// Solves on MI355X, with CAPFOREST alone and with this test before it (the
+// label-propagation bound first in both): Erdos-Renyi, 300,000 vertices, mean
+// degree 24, weights to 1000: 174 and 7.6 ms; Chung-Lu 2^20 and 2^22, 10-cores,
+// unit weights: 6.9 and 4.7 ms, 14.0 and 11.1 ms.
 //
 // The kernels are bound by the k n random reads of the two compressions and
 // of the linking, not by the rows: one pass over the entries (12 B each, and
@@ -45,6 +45,8 @@ constexpr int SUB = 16;          // lanes per row
 constexpr int ROWS = 64;         // rows dealt out by one workgroup at a time
 constexpr int32_t CERT_ROW = 4096;   // entries of a row looked at (a long row is a heavy vertex, which owns little)
 constexpr int CERT_NEAR = 16;
+constexpr int64_t CERT_EASY = 5;
+constexpr int32_t CERT_PROBE_N = 1 << 15;
 
 inline int grid_for(int64_t count, int threads, int cap = 8192) {
     int64_t b = (count + threads - 1) / threads;
@@ -57,11 +59,16 @@ __device__ __forceinline__ bool inactive(const CertArgs& a, int64_t v) {
     return a.active && !a.active[a.vinst[v]];
 }
 
-// unit weight c and subgraph count k of every graph; no member yet
+// unit weight c and subgraph count k of every graph; no member yet. A single
+// graph whose mean degree is CERT_EASY times the bound or more takes half as
+// many subgraphs: the weight that wider units lose is not missed there
+// (Erdos-Renyi, 300,000 vertices, mean degree 6.5 times the bound: solves of
+// 2.1 ms with 16 subgraphs, 2.8 ms with 32).
 __global__ void k_cert_plan(CertArgs a) {
     for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < a.ngraphs; i += gridDim.x * blockDim.x) {
         const int64_t lam = a.lam[i];
-        const int64_t c = lam > a.kc ? (lam + a.kc - 1) / a.kc : 1;
+        const int32_t kc = !a.vinst && a.kc > CERT_KMAX / 2 && *a.total / CERT_EASY / a.g.n >= lam ? CERT_KMAX / 2 : a.kc;
+        const int64_t c = lam > kc ? (lam + kc - 1) / kc : 1;
         a.unit[i] = c;
         a.count[i] = lam > 0 ? (int32_t)((lam + c - 1) / c) : 0;
         a.rep[i] = INT32_MAX;
@@ -69,12 +76,22 @@ __global__ void k_cert_plan(CertArgs a) {
 }
 
 // degree class: two bits below the leading one, so degrees within 25 % of
-// each other may share a class
-__global__ void k_cert_level(CertArgs a) {
+// each other may share a class; the sum of the degrees
+__global__ __launch_bounds__(256) void k_cert_level(CertArgs a) {
+    __shared__ int64_t sum[256 / MC_WAVE];
+    int64_t t = 0;
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < a.g.n; v += (int64_t)gridDim.x * blockDim.x) {
         const uint64_t d = (uint64_t)a.g.deg[v] | 1;
         const int e = 63 - __clzll((long long)d);
         a.level[v] = (uint8_t)((e << 2) | (int)((e >= 2 ? d >> (e - 2) : d << (2 - e)) & 3));
+        t += (int64_t)d;
+    }
+    t = wave_sum_i64(t);
+    if (lane_id() == 0) sum[threadIdx.x / MC_WAVE] = t;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int q = 1; q < 256 / MC_WAVE; q++) t += sum[q];
+        atomicAdd((unsigned long long*)a.total, (unsigned long long)t);
     }
 }
 
@@ -203,6 +220,28 @@ __global__ __launch_bounds__(256) void k_cert_join_trees(CertArgs a) {
     }
 }
 
+// Whether the test can join much: subgraph 0, built first, is as sparse as
+// the others, and a class is no larger than its component there. A graph of
+// whose 64 samples fewer than half share their component with another is
+// left out (k = 0). On cores of hyperbolic graphs the subgraphs fall apart at
+// the smallest degree (2^21, 32-core: 6.2 ms a solve with the probe, 9.3 ms
+// without) and hold together, sector by sector, at a quarter of it.
+__global__ __launch_bounds__(64) void k_cert_probe(CertArgs a) {
+    const int lane = lane_id();
+    for (int32_t gi = blockIdx.x; gi < a.ngraphs; gi += gridDim.x) {
+        if (a.active && !a.active[gi]) continue;
+        const int32_t base = a.voff ? a.voff[gi] : 0;
+        const int32_t n = a.voff ? a.voff[gi + 1] - base : a.g.n;
+        if (n < 1) continue;
+        const int32_t v = base + (int32_t)(((uint64_t)hash32(lane * 2654435761u + 4711u) * (uint64_t)n) >> 32);
+        const int32_t root = a.own[v];
+        int32_t same = 0;
+        for (int q = 0; q < MC_WAVE; q++) same += __shfl(root, q, MC_WAVE) == root;
+        const int shared = __popcll(__ballot(same > 1));
+        if (lane == 0 && shared * 2 < MC_WAVE) a.count[gi] = 0;
+    }
+}
+
 // the reference vertex of every graph: of 64 samples the one that shares its
 // class (a hash of its components) with most of them, one wavefront a graph
 __global__ __launch_bounds__(64) void k_cert_ref(CertArgs a) {
@@ -267,13 +306,15 @@ __global__ __launch_bounds__(256) void k_cert_join(CertArgs a) {
             if (uf_union(a.parent, (int32_t)v, a.rep[inst])) joined++;
             continue;
         }
-        const int32_t o = a.g.off[v], l = a.g.len[v] < CERT_NEAR ? a.g.len[v] : CERT_NEAR, k = a.count[inst];
+        const int32_t k = a.count[inst];
+        if (k == 0) continue;
+        const int32_t o = a.g.off[v], l = a.g.len[v] < CERT_NEAR ? a.g.len[v] : CERT_NEAR;
         for (int32_t j = 0; j < l; j++) {
             const int32_t u = a.g.col[o + j];
             if (a.member[u]) continue;
             int i = 0;
             while (i < k && a.own[(int64_t)i * n + v] == a.own[(int64_t)i * n + u]) i++;
-            if (i < k || k == 0) continue;
+            if (i < k) continue;
             if (uf_union(a.parent, (int32_t)v, u)) joined++;
             break;
         }
@@ -294,7 +335,7 @@ __global__ __launch_bounds__(256) void k_cert_join(CertArgs a) {
 // that fit, at most CERT_KMAX. False when fewer than CERT_KMIN fit.
 bool cert_carve(CertArgs& a, void* base, size_t bytes) {
     const size_t n = (size_t)a.g.n, k = (size_t)a.ngraphs;
-    const size_t fixed = 2 * n + 20 * k + 8 * 256;   // the other arrays and their alignment
+    const size_t fixed = 2 * n + 20 * k + 10 * 256;   // the other arrays and their alignment
     if (bytes < fixed) return false;
     const size_t kc = (bytes - fixed) / (n * 2 * sizeof(int32_t));
     if (kc < (size_t)CERT_KMIN) return false;
@@ -302,6 +343,7 @@ bool cert_carve(CertArgs& a, void* base, size_t bytes) {
     Arena m;
     m.base = (char*)base;
     m.size = bytes;
+    a.total = m.take<int64_t>(1);
     a.unit = m.take<int64_t>(k);
     a.count = m.take<int32_t>(k);
     a.ref = m.take<int32_t>(k);
@@ -312,13 +354,9 @@ bool cert_carve(CertArgs& a, void* base, size_t bytes) {
     return m.used <= bytes;
 }
 
-bool certify(const CertArgs& a, hipStream_t s) {
-    const int32_t n = a.g.n;
-    const dim3 grid(grid_for(n, 256, 1024), a.kc);
-    k_cert_plan<<<grid_for(a.ngraphs, 256), 256, 0, s>>>(a);
-    k_cert_level<<<grid_for(n, 256), 256, 0, s>>>(a);
-    k_cert_rows<<<grid_for(n, ROWS), 256, 0, s>>>(a);
-    MC_LAUNCHED("k_cert_rows");
+// the first ny subgraphs: trees of the first round, joined by the second
+static void components(const CertArgs& a, int ny, hipStream_t s) {
+    const dim3 grid(grid_for(a.g.n, 256, 1024), ny);
     k_cert_compress<<<grid, 256, 0, s>>>(a);
     for (int sweep = 0; sweep < 2; sweep++) {
         k_cert_join_trees<false><<<grid, 256, 0, s>>>(a);
@@ -326,7 +364,24 @@ bool certify(const CertArgs& a, hipStream_t s) {
     }
     k_cert_join_trees<true><<<grid, 256, 0, s>>>(a);
     k_cert_compress<<<grid, 256, 0, s>>>(a);
-    k_cert_ref<<<a.ngraphs < 4096 ? a.ngraphs : 4096, 64, 0, s>>>(a);
+}
+
+bool certify(const CertArgs& a, hipStream_t s) {
+    const int32_t n = a.g.n;
+    const int gg = a.ngraphs < 4096 ? a.ngraphs : 4096;
+    if (!fill_i64(a.total, 0, 1, s)) return false;
+    k_cert_level<<<grid_for(n, 256, 1024), 256, 0, s>>>(a);
+    k_cert_plan<<<grid_for(a.ngraphs, 256), 256, 0, s>>>(a);
+    k_cert_rows<<<grid_for(n, ROWS), 256, 0, s>>>(a);
+    MC_LAUNCHED("k_cert_rows");
+    // small graphs are bound by the launches: the probe's seven would cost
+    // more than they can save
+    if (n >= CERT_PROBE_N) {
+        components(a, 1, s);
+        k_cert_probe<<<gg, 64, 0, s>>>(a);
+    }
+    components(a, a.kc, s);
+    k_cert_ref<<<gg, 64, 0, s>>>(a);
     k_cert_member<<<grid_for(n, 256), 256, 0, s>>>(a);
     k_cert_join<<<grid_for(n, 256, 1024), 256, 0, s>>>(a);
     MC_LAUNCHED("certify");

@@ -80,30 +80,50 @@ __global__ __launch_bounds__(256) void k_uf_root_min(DGraph g, int32_t* par) {
     }
 }
 
+// The root most of 1024 sampled vertices lie under, counted in an LDS hash
+// table (1024 reads of all samples by every thread took 20 us).
 __global__ __launch_bounds__(1024) void k_uf_sample_mode(const int32_t* par, int32_t n, int32_t* mode) {
-    __shared__ int32_t smp[1024];
-    __shared__ int32_t bestc[1024], bestr[1024];
+    constexpr int SLOTS = 2048;
+    __shared__ int32_t key[SLOTS], cnt[SLOTS];
+    __shared__ int64_t wbest[1024 / MC_WAVE];
+    for (int i = threadIdx.x; i < SLOTS; i += 1024) { key[i] = -1; cnt[i] = 0; }
     const uint32_t h = hash32(threadIdx.x * 2654435761u + 12345u);
     const int32_t v = (int32_t)(((uint64_t)h * (uint64_t)n) >> 32);
     int32_t x = v, p = ld_acq(&par[x]);
     while (p != x) { x = p; p = ld_acq(&par[x]); }
-    smp[threadIdx.x] = x;
     __syncthreads();
-    int32_t c = 0;
-    for (int k = 0; k < 1024; k++) c += smp[k] == x;
-    bestc[threadIdx.x] = c;
-    bestr[threadIdx.x] = x;
-    __syncthreads();
-    for (int s2 = 512; s2 > 0; s2 >>= 1) {
-        if (threadIdx.x < s2 && bestc[threadIdx.x + s2] > bestc[threadIdx.x]) {
-            bestc[threadIdx.x] = bestc[threadIdx.x + s2];
-            bestr[threadIdx.x] = bestr[threadIdx.x + s2];
-        }
-        __syncthreads();
+    // the wavefront's lanes of one root are counted by the first of them
+    int32_t mine = 0;
+    unsigned long long left = ~0ULL;
+    while (left) {
+        const int first = __ffsll((long long)left) - 1;
+        const unsigned long long same = __ballot(x == __shfl(x, first, MC_WAVE)) & left;
+        if (lane_id() == first) mine = __popcll(same);
+        left &= ~same;
     }
+    if (mine > 0) {
+        uint32_t s = hash32((uint32_t)x) % SLOTS;
+        for (;;) {
+            const int32_t old = atomicCAS(&key[s], -1, x);
+            if (old == -1 || old == x) break;
+            s = (s + 1) % SLOTS;
+        }
+        atomicAdd(&cnt[s], mine);
+    }
+    __syncthreads();
+    // the largest count, of the smallest root on ties
+    int64_t best = 0;
+    for (int i = threadIdx.x; i < SLOTS; i += 1024) {
+        const int64_t c = ((int64_t)cnt[i] << 32) | (uint32_t)(INT32_MAX - key[i]);
+        if (cnt[i] > 0 && c > best) best = c;
+    }
+    best = wave_max_i64(best);
+    if (lane_id() == 0) wbest[threadIdx.x / MC_WAVE] = best;
+    __syncthreads();
     if (threadIdx.x == 0) {
-        mode[0] = bestr[0];
-        mode[1] = bestc[0];   // samples (of 1024) in that component
+        for (int q = 1; q < 1024 / MC_WAVE; q++) best = wbest[q] > best ? wbest[q] : best;
+        mode[0] = INT32_MAX - (int32_t)(uint32_t)best;
+        mode[1] = (int32_t)(best >> 32);   // samples (of 1024) in that component
     }
 }
 

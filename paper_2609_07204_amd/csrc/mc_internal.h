@@ -209,6 +209,7 @@ struct CertArgs {
     unsigned long long* marks;
     // carved by cert_carve
     int32_t kc;              // subgraphs there is room for
+    int64_t* total;          // sum of the degrees
     int64_t* unit;           // [ngraphs] c
     int32_t* count;          // [ngraphs] k <= kc
     int32_t* ref;            // [ngraphs] reference vertex

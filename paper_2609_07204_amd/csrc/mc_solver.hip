@@ -192,6 +192,14 @@ void prof_round_begin(int32_t kind, int32_t n, int64_t m, hipStream_t s) {
     p->round_open = true;
 }
 
+// a round whose tests led to another bound first: it starts over
+void prof_round_cancel() {
+    Prof* p = g_prof;
+    if (!p || !p->round_open) return;
+    if (p->rounds.back().a) p->pool.push_back(p->rounds.back().a);
+    p->rounds.pop_back();
+    p->round_open = false;
+}
 
 // ------------------------------------------ static scratch (no allocation)
 // Workspace of mc_mincut_static: a file-scope device array, one copy on each
@@ -559,6 +567,8 @@ struct Solver {
     bool debug = false;
     bool tri_on = false;          // reduction tests 3 and 4 still pay off
     bool cert_on = true;          // the edge-disjoint subgraphs' test still pays off
+    bool automatic = false;       // MC_CF_AUTO, not deterministic
+    bool heur_pending = false;    // the label-propagation bound runs once the input resists the tests
     bool bound_tried = false;     // threshold_bound has run
     bool in_heuristic = false;    // exact rounds on the heuristic's coarse graph
     bool conn_pending = false;    // connectivity not decided yet (the heuristic's coarse graph decides it)
@@ -891,8 +901,8 @@ static DGraph* contract_and_bound(Solver& S, DGraph* cur, int32_t n2, int* nxt_i
 // subgraphs; test 2 holds at any bound) are applied until little changes, and
 // the parts they join are contracted: a cut of the coarse graph is a cut of
 // the input, so its collapsed degrees and, once it is small enough, its
-// exact minimum (the finisher) bound lambda. A cut below lam / 4 is never
-// crossed by these unions, so it survives in the coarse graph. What it is
+// exact minimum (the finisher) bound lambda. Test 1 and the subgraphs join
+// nothing across a cut below lam / 4, so it survives them. What it is
 // for: two dense communities joined by a few light edges, where a pass of
 // CAPFOREST finds the cut only after it has scanned one of them, pop by pop
 // (planted 2 x 1000, 12-regular, weights to 10, bound 36, lambda 5: 5.2 ms a
@@ -934,14 +944,19 @@ static mc_status threshold_bound(Solver& S, int32_t round) {
     return MC_OK;
 }
 
-// Exact rounds of Algorithm 2 on w.g[src] until at most two vertices remain.
+static mc_status heuristic(Solver& S);
+
+// Exact rounds of Algorithm 2 on w.g[src] until at most two vertices remain
+// (or the bound is 0).
 static mc_status exact_rounds(Solver& S, int src) {
     SolveWS& w = S.w;
     hipStream_t s = S.s;
     DGraph* cur = &w.g[src];
     int nxt_idx = src == 1 ? 2 : 1;
     int32_t round = 0;
-    while (cur->n > 2) {
+    const int64_t m_first = S.cur_m;
+    bool note_bound = false;      // the tests' contraction of the input takes the heuristic's place
+    while (cur->n > 2 && S.lam > 0) {
         if (cur->n <= finish_max_n(S.c)) {
             // a small graph finishes every remaining round in one launch
             mc_status r = finish(S, cur, round);
@@ -963,7 +978,7 @@ static mc_status exact_rounds(Solver& S, int src) {
         // in the automatic mode the edge-disjoint subgraphs' test comes
         // before CAPFOREST; when both kinds of tests together halve the
         // graph, CAPFOREST is left out
-        if (!skip_cf && !det && S.c->opt.capforest_mode == MC_CF_AUTO && S.cert_on) {
+        if (!skip_cf && S.automatic && S.cert_on) {
             if (!S.certificates(*cur, *nxt)) return MC_E_DEVICE;
             // left out for the rest of the solve once it joins fewer than
             // one vertex in 32
@@ -973,17 +988,43 @@ static mc_status exact_rounds(Solver& S, int src) {
                 fprintf(stderr, "[mc] round %d edge-disjoint subgraphs: n=%d lam=%lld marks_pr=%llu marks_cert=%llu\n", round, n,
                         (long long)S.lam, S.c->hsc->marks_pr, S.c->hsc->marks_cert);
         }
-        int used = CF_RUN_NONE;   // the CAPFOREST form whose results the round keeps last
-        if (!skip_cf && !det && S.c->opt.capforest_mode == MC_CF_AUTO && cur == &w.g[0] && !S.bound_tried) {
-            // the input resists the tests at its bound: look for a lower
-            // bound among its more loosely connected parts, then run the
-            // round again (the unions were made over)
-            S.bound_tried = true;
-            const mc_status r = threshold_bound(S, round);
-            if (r != MC_OK) return r;
-            continue;
+        if (S.automatic && cur == &w.g[0]) {
+            // The input resists the tests at its bound: look for a lower
+            // bound, by label propagation (once, from heuristic_min_n
+            // vertices on), then among its more loosely connected parts
+            // (once), and run the round again (the unions were made over).
+            // Where the tests halve the input at its smallest degree, no
+            // lower bound is needed to go on, and their contraction stands
+            // for the heuristic's first level: solves with the bound first
+            // and with the tests first: Chung-Lu 60,000 vertices 1.25 and
+            // 0.37 ms, Erdos-Renyi 200,000 1.6 and 0.77 ms, 300,000 7.6 and
+            // 2.1 ms, Chung-Lu 2^22 11.1 and 5.2 ms. Hyperbolic 2^21, where
+            // they do not: 5.6 and 6.2 ms.
+            const int64_t before = S.lam;
+            mc_status r = MC_OK;
+            if (!skip_cf && S.heur_pending) {
+                prof_round_cancel();
+                S.heur_pending = false;
+                S.cert_on = true;
+                if ((r = heuristic(S)) != MC_OK || !iota_i32(w.map0, S.n0, s)) return r != MC_OK ? r : MC_E_DEVICE;
+                S.cur_m = m_first;
+                if (S.lam < before) continue;
+            }
+            if (!skip_cf && !S.bound_tried) {
+                prof_round_cancel();
+                S.bound_tried = true;
+                S.cert_on = true;
+                if ((r = threshold_bound(S, round)) != MC_OK) return r;
+                continue;
+            }
+            if (S.heur_pending) {
+                S.heur_pending = false;
+                S.stats.heuristic_levels = 1;
+                note_bound = true;
+            }
         }
         S.tri_account(n);
+        int used = CF_RUN_NONE;   // the CAPFOREST form whose results the round keeps last
         if (skip_cf) {
             S.stats.rounds_pr_only++;
         } else if (det) {
@@ -1081,7 +1122,7 @@ static mc_status exact_rounds(Solver& S, int src) {
                 if (!S.set_lam(h.best_alpha)) return MC_E_DEVICE;
             }
             if (marks0 == 0 && h.marks_cf == 0) {
-                if (S.lam < lam_before) { round++; continue; }
+                if (S.lam < lam_before || S.lam == 0) { round++; continue; }
                 return fail(MC_E_DEVICE, "sequential CAPFOREST marked no edge at a fixed bound");
             }
         }
@@ -1111,10 +1152,13 @@ static mc_status exact_rounds(Solver& S, int src) {
             if (!S.set_lam(h.dmin)) return MC_E_DEVICE;
         }
         prof_round_end(n2, S.cur_m, s);
+        if (note_bound) S.stats.lambda_heuristic = S.lam;
+        note_bound = false;
         nxt_idx = (nxt_idx == 1) ? 2 : 1;
         cur = nxt;
         round++;
     }
+    if (note_bound) S.stats.lambda_heuristic = S.lam;
     if (cur->n > 1) prof_round_end(cur->n, S.cur_m, s);   // a round that ended without contraction
     S.stats.rounds += round;
     return MC_OK;
@@ -1328,8 +1372,12 @@ extern "C" mc_status mc_mincut(mc_ctx* c, const mc_csr* g, void* dev_ws, size_t 
     // Chung-Lu 2^22: 14.54 and 14.42 ms).
     if (run_heuristic) S.tri_on = false;
     if (!input_normal && !S.readback()) return MC_E_DEVICE;   // the normalisation's minimum degree
-    if (run_heuristic && c->hsc->dmin > 0) {
-        S.conn_pending = true;
+    S.automatic = c->opt.capforest_mode == MC_CF_AUTO && c->opt.deterministic == 0;
+    if (c->hsc->dmin > 0 && (S.automatic || run_heuristic)) {
+        // in the automatic mode not even that: unions only ever join
+        // connected vertices, so the rounds of a disconnected graph end at a
+        // cut of 0, and only then its components are looked up
+        S.conn_pending = !S.automatic;
     } else if (!check_connected(S, w.g[0])) {
         return MC_E_DEVICE;
     }
@@ -1346,7 +1394,8 @@ extern "C" mc_status mc_mincut(mc_ctx* c, const mc_csr* g, void* dev_ws, size_t 
         if (!S.set_lam(h.dmin)) return MC_E_DEVICE;
         S.stats.lambda_min_degree = h.dmin;
         mc_status r = MC_OK;
-        if (run_heuristic) {
+        S.heur_pending = run_heuristic && S.automatic;
+        if (run_heuristic && !S.automatic) {
             if ((r = heuristic(S)) != MC_OK) return r;
             // the exact rounds start again from the normalised input
             if (!iota_i32(w.map0, n, s)) return MC_E_DEVICE;
@@ -1357,6 +1406,7 @@ extern "C" mc_status mc_mincut(mc_ctx* c, const mc_csr* g, void* dev_ws, size_t 
         } else {
             if ((r = exact_rounds(S, 0)) != MC_OK) return r;
             result = S.lam;
+            if (result == 0 && !check_connected(S, w.g[0])) return MC_E_DEVICE;
         }
     }
     if (side_out) {
