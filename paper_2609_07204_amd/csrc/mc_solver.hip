@@ -566,7 +566,7 @@ struct Solver {
     int64_t lam = 0;
     bool debug = false;
     bool tri_on = false;          // reduction tests 3 and 4 still pay off
-    bool cert_on = true;          // the edge-disjoint subgraphs' test still pays off
+    int32_t cert_max_n = INT32_MAX;   // the edge-disjoint subgraphs' test runs on graphs of at most this size
     bool automatic = false;       // MC_CF_AUTO, not deterministic
     bool heur_pending = false;    // the label-propagation bound runs once the input resists the tests
     bool bound_tried = false;     // threshold_bound has run
@@ -704,6 +704,12 @@ static void debug_round(Solver& S, const DGraph& g, int32_t round, int32_t passe
 constexpr int32_t kProbeScans = 32;
 constexpr int32_t kProbePasses = 4;
 constexpr int32_t kProbePrivate = 4096;   // scans per private pass in a probe round
+// A private run of that many scans takes 1.4 ms or more with one workgroup a
+// pass (3,600 vertices) and 20 to 25 ms in whole-GPU steps (hyperbolic cores
+// of 95,000 to 600,000 vertices, where it joined 3,500 vertices and the
+// shared probe 14,000 in 0.2 ms; solves at 95,000 vertices 33 ms with it, 10 ms
+// without).
+constexpr double kPrivateMs = 1.4, kPrivateStepsMs = 4.0;
 static bool shared_passes(Solver& S, const DGraph& g, bool probe) {
     SolveWS& w = S.w;
     CapforestArgs ca{};
@@ -978,11 +984,11 @@ static mc_status exact_rounds(Solver& S, int src) {
         // in the automatic mode the edge-disjoint subgraphs' test comes
         // before CAPFOREST; when both kinds of tests together halve the
         // graph, CAPFOREST is left out
-        if (!skip_cf && S.automatic && S.cert_on) {
+        if (!skip_cf && S.automatic && n <= S.cert_max_n) {
             if (!S.certificates(*cur, *nxt)) return MC_E_DEVICE;
-            // left out for the rest of the solve once it joins fewer than
-            // one vertex in 32
-            if (S.c->hsc->marks_cert * 32 < (unsigned long long)n) S.cert_on = false;
+            // left out until the graph is smaller by a quarter once it joins
+            // fewer than one vertex in 32
+            if (S.c->hsc->marks_cert * 32 < (unsigned long long)n) S.cert_max_n = n - n / 4;
             skip_cf = 2 * (int64_t)(S.c->hsc->marks_pr + S.c->hsc->marks_tri + S.c->hsc->marks_cert) >= n;
             if (S.debug)
                 fprintf(stderr, "[mc] round %d edge-disjoint subgraphs: n=%d lam=%lld marks_pr=%llu marks_cert=%llu\n", round, n,
@@ -1005,7 +1011,7 @@ static mc_status exact_rounds(Solver& S, int src) {
             if (!skip_cf && S.heur_pending) {
                 prof_round_cancel();
                 S.heur_pending = false;
-                S.cert_on = true;
+                S.cert_max_n = INT32_MAX;
                 if ((r = heuristic(S)) != MC_OK || !iota_i32(w.map0, S.n0, s)) return r != MC_OK ? r : MC_E_DEVICE;
                 S.cur_m = m_first;
                 if (S.lam < before) continue;
@@ -1013,7 +1019,7 @@ static mc_status exact_rounds(Solver& S, int src) {
             if (!skip_cf && !S.bound_tried) {
                 prof_round_cancel();
                 S.bound_tried = true;
-                S.cert_on = true;
+                S.cert_max_n = INT32_MAX;
                 if ((r = threshold_bound(S, round)) != MC_OK) return r;
                 continue;
             }
@@ -1056,7 +1062,12 @@ static mc_status exact_rounds(Solver& S, int src) {
                 form = CF_RUN_PRIVATE;
                 double ms_p = 0;
                 unsigned long long marks_p = 0;
-                if (marks_s * 1024 >= (unsigned long long)n) {
+                if (marks_s * 1024 >= (unsigned long long)n && (double)n * ms_s < (reg == 0 ? kPrivateStepsMs : kPrivateMs) * (double)marks_s) {
+                    // private passes would have to join every vertex in
+                    // less than the least time they take to be the faster form
+                    form = CF_RUN_SHARED;
+                    if (!shared_passes(S, *cur, false)) return MC_E_DEVICE;
+                } else if (marks_s * 1024 >= (unsigned long long)n) {
                     const int32_t cap = private_len_cap(S.c);
                     const auto t1 = clk::now();
                     if (!private_passes(S, *cur, round, npriv, cap > 0 && cap < kProbePrivate ? cap : kProbePrivate) ||
