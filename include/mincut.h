@@ -116,7 +116,8 @@ typedef struct {
                                  512 or 1024 (0 = 256) */
     int32_t batch_lp;         /* label-propagation bound at admission in the
                                  batched and served forms: 0 = when
-                                 heuristic_min_n > 0, 1 = always, 2 = never */
+                                 heuristic_min_n > 0 and capforest_mode is not
+                                 automatic, 1 = always, 2 = never */
     int32_t finish_max_n;     /* current graphs with at most this many
                                  vertices (<= 1024) finish all their remaining
                                  rounds in one launch, one workgroup per graph

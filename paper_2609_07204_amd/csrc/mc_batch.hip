@@ -81,45 +81,66 @@ __global__ void k_bg_gather(const BatchGraph* tab, int32_t k, const int32_t* vof
 }
 
 // Per-graph checks of device inputs (what check_host_csr does on the host,
-// without the symmetry check), one workgroup per graph at a time:
-// row_ptr[0] = 0, row_ptr[n] = nnz and non-decreasing, every target in
-// [0, n) and every weight >= 0 (MC_E_BAD_GRAPH), then the graph's own total
-// weight below 2^62 (MC_E_OVERFLOW). gerr[i] receives graph i's status.
+// without the symmetry check): row_ptr[0] = 0, row_ptr[n] = nnz and
+// non-decreasing, every target in [0, n) and every weight >= 0
+// (MC_E_BAD_GRAPH), then the graph's own total weight below 2^62
+// (MC_E_OVERFLOW). gerr[i] receives graph i's status. Entries are dealt out
+// BG_CHECK to a wavefront whatever graph they belong to, so a large graph
+// does not keep one workgroup busy (384 graphs of 64 to 65,536 vertices: 0.25
+// ms, with one workgroup a graph 6.9 ms). The weights are summed in two
+// halves (31 low bits, the rest), neither of which can wrap.
 constexpr unsigned long long BG_WCAP = 1ULL << 62;
-__global__ __launch_bounds__(256) void k_bg_check(const BatchGraph* tab, int32_t k, int32_t* gerr) {
-    __shared__ unsigned long long ssum[256];
-    __shared__ int32_t sbad;
-    for (int32_t i = blockIdx.x; i < k; i += gridDim.x) {
+constexpr int BG_CHECK = 2048;
+constexpr unsigned long long BG_LOW = (1ULL << 31) - 1;
+__global__ void k_bg_check_rows(const BatchGraph* tab, int32_t k, const int32_t* voff, int32_t N, int32_t* bad) {
+    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < N; v += (int64_t)gridDim.x * blockDim.x) {
+        const int32_t i = seg_of(voff, k, v);
         const BatchGraph g = tab[i];
-        if (threadIdx.x == 0) sbad = 0;
-        __syncthreads();
-        bool bad = threadIdx.x == 0 && (g.rp[0] != 0 || g.rp[g.n] != g.nnz);
-        for (int32_t v = threadIdx.x; v < g.n; v += blockDim.x)
-            if (g.rp[v + 1] < g.rp[v]) bad = true;
-        unsigned long long sum = 0;
-        for (int32_t j = threadIdx.x; j < g.nnz; j += blockDim.x) {
-            const int32_t x = g.col[j];
-            const int64_t c = g.w[j];
-            if (x < 0 || x >= g.n || c < 0) {
-                bad = true;
-            } else {
-                // sum < 2^62 and c < 2^63 before the add: no wrap
-                sum += (unsigned long long)c;
-                if (sum >= BG_WCAP) sum = BG_WCAP;
+        const int32_t lv = (int32_t)v - voff[i];
+        if (g.rp[lv + 1] < g.rp[lv] || (lv == 0 && (g.rp[0] != 0 || g.rp[g.n] != g.nnz))) bad[i] = 1;
+    }
+}
+
+__global__ __launch_bounds__(256) void k_bg_check_entries(const BatchGraph* tab, int32_t k, const int32_t* eoff,
+                                                         int32_t C, int32_t* bad, unsigned long long* lo,
+                                                         unsigned long long* hi) {
+    const int lane = lane_id();
+    const int64_t waves = (int64_t)gridDim.x * (blockDim.x / MC_WAVE);
+    for (int64_t c0 = ((int64_t)blockIdx.x * (blockDim.x / MC_WAVE) + threadIdx.x / MC_WAVE) * BG_CHECK; c0 < C;
+         c0 += waves * BG_CHECK) {
+        const int64_t c1 = c0 + BG_CHECK < C ? c0 + BG_CHECK : C;
+        // the graphs that hold the range's entries, one after the other
+        for (int64_t e0 = c0; e0 < c1;) {
+            const int32_t i = seg_of(eoff, k, e0);
+            const BatchGraph g = tab[i];
+            const int64_t first = eoff[i], e1 = first + g.nnz < c1 ? first + g.nnz : c1;
+            unsigned long long sl = 0, sh = 0;
+            bool wrong = false;
+#pragma unroll 4
+            for (int64_t e = e0 + lane; e < e1; e += MC_WAVE) {
+                const int32_t x = g.col[e - first];
+                const int64_t c = g.w[e - first];
+                wrong |= x < 0 || x >= g.n || c < 0;
+                sl += (unsigned long long)c & BG_LOW;
+                sh += (unsigned long long)c >> 31;
             }
-        }
-        if (bad) sbad = 1;
-        ssum[threadIdx.x] = sum;
-        __syncthreads();
-        for (int o = 128; o > 0; o >>= 1) {
-            if ((int)threadIdx.x < o) {
-                const unsigned long long t = ssum[threadIdx.x] + ssum[threadIdx.x + o];
-                ssum[threadIdx.x] = t >= BG_WCAP ? BG_WCAP : t;
+            sl = (unsigned long long)wave_sum_i64((int64_t)sl);
+            sh = (unsigned long long)wave_sum_i64((int64_t)sh);
+            if (__any(wrong) && lane == 0) bad[i] = 1;
+            if (lane == 0) {
+                atomicAdd(&lo[i], sl);
+                if (sh) atomicAdd(&hi[i], sh);
             }
-            __syncthreads();
+            e0 = e1;
         }
-        if (threadIdx.x == 0) gerr[i] = sbad ? MC_E_BAD_GRAPH : (ssum[0] >= BG_WCAP ? MC_E_OVERFLOW : MC_OK);
-        __syncthreads();
+    }
+}
+
+__global__ void k_bg_check_status(int32_t k, const unsigned long long* lo, const unsigned long long* hi, int32_t* gerr) {
+    for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < k; i += gridDim.x * blockDim.x) {
+        // total >= 2^62 iff its high part reaches 2^31
+        const bool over = hi[i] + (lo[i] >> 31) >= (BG_WCAP >> 31);
+        gerr[i] = gerr[i] ? MC_E_BAD_GRAPH : (over ? MC_E_OVERFLOW : MC_OK);
     }
 }
 
@@ -725,7 +746,12 @@ struct Engine {
         }
         // the label-propagation heuristic on the staged graphs (every graph
         // at once); its best bounds are applied after the minimum degrees
-        const bool lp = c->opt.batch_lp == 1 || (c->opt.batch_lp == 0 && c->opt.heuristic_min_n > 0);
+        // (left to itself it runs only where the threshold bounds of the
+        // automatic mode do not: with them it finds little and costs as much
+        // as they do; 384 graphs of 64 to 65,536 vertices, 48 ms with it, 39
+        // without)
+        const bool lp = c->opt.batch_lp == 1 ||
+                        (c->opt.batch_lp == 0 && c->opt.heuristic_min_n > 0 && c->opt.capforest_mode != MC_CF_AUTO);
         if (lp) EG_OK(heuristic_levels(S, k, NS, sv, narrow));
         DGraph& G = w.g[cur];
         k_eg_append<<<grid_for((int64_t)CS + NS, 256), 256, 0, s>>>(S, CS, G, n, used);
@@ -832,7 +858,21 @@ struct Engine {
         for (int32_t i = 0; i < k; i++) tab[i] = {gs[i].row_ptr, gs[i].col, gs[i].w, gs[i].n, gs[i].nnz};
         std::vector<int32_t> e(k);
         EG_HIP(hipMemcpyAsync(w.tab, tab.data(), sizeof(BatchGraph) * k, hipMemcpyHostToDevice, s));
-        k_bg_check<<<std::min(k, 4096), 256, 0, s>>>(w.tab, k, w.gerr);
+        // the graphs' vertex and entry ranges side by side
+        std::vector<int32_t> sv(k + 1, 0), se(k + 1, 0);
+        for (int32_t i = 0; i < k; i++) {
+            sv[i + 1] = sv[i] + gs[i].n;
+            se[i + 1] = se[i] + gs[i].nnz;
+        }
+        EG_HIP(hipMemcpyAsync(w.s_voff, sv.data(), sizeof(int32_t) * (k + 1), hipMemcpyHostToDevice, s));
+        EG_HIP(hipMemcpyAsync(w.s_eoff, se.data(), sizeof(int32_t) * (k + 1), hipMemcpyHostToDevice, s));
+        unsigned long long *const lo = (unsigned long long*)w.lam, *const hi = (unsigned long long*)w.dmin;
+        EG_OK(fill_i32(w.gerr, 0, k, s) && fill_i64(w.lam, 0, k, s) && fill_i64(w.dmin, 0, k, s));
+        k_bg_check_rows<<<grid_for(sv[k], 256), 256, 0, s>>>(w.tab, k, w.s_voff, sv[k], w.gerr);
+        if (se[k] > 0)
+            k_bg_check_entries<<<grid_for(se[k], 4 * BG_CHECK, 4096), 256, 0, s>>>(w.tab, k, w.s_eoff, se[k], w.gerr, lo,
+                                                                                hi);
+        k_bg_check_status<<<grid_for(k, 256), 256, 0, s>>>(k, lo, hi, w.gerr);
         EG_OK(mc_hip_ok(hipGetLastError(), "k_bg_check"));
         EG_HIP(hipMemcpyAsync(e.data(), w.gerr, sizeof(int32_t) * k, hipMemcpyDeviceToHost, s));
         EG_HIP(hipStreamSynchronize(s));
@@ -1174,16 +1214,21 @@ struct Engine {
         return mc_hip_ok(hipGetLastError(), "prefix sides");
     }
 
-    // side of a finished graph (host, n0 bytes, side[0] = 0); then its input
-    // vertices are no longer tracked
+    // side of a finished graph (host, n0 bytes, side[0] = 0). Its vertices
+    // leave the union graph with the next contraction, which also ends the
+    // tracking of its input vertices (their map turns -1).
     mc_status side_of(const EngineInst& x, uint8_t* out) {
-        if (out) {
-            EG_HIP(hipMemcpyAsync(out, w.side + x.ioff, x.n0, hipMemcpyDeviceToHost, s));
-            EG_HIP(hipStreamSynchronize(s));
-            const uint8_t flip = out[0];
-            if (flip)
-                for (int32_t v = 0; v < x.n0; v++) out[v] ^= 1;
-        }
+        EG_HIP(hipMemcpyAsync(out, w.side + x.ioff, x.n0, hipMemcpyDeviceToHost, s));
+        EG_HIP(hipStreamSynchronize(s));
+        turn(out, x.n0);
+        return MC_OK;
+    }
+    static void turn(uint8_t* side, int32_t n0) {
+        if (side[0])
+            for (int32_t v = 0; v < n0; v++) side[v] ^= 1;
+    }
+    // the input vertices of a graph taken out before its end
+    mc_status untrack(const EngineInst& x) {
         k_eg_untrack<<<grid_for(x.n0, 256), 256, 0, s>>>(w.map0, x.ioff, x.n0);
         EG_OK(mc_hip_ok(hipGetLastError(), "k_eg_untrack"));
         return MC_OK;
@@ -1287,28 +1332,34 @@ extern "C" mc_status mc_mincut_batch(mc_ctx* c, int32_t k, const mc_csr* gs, voi
     // results are staged and written only once every graph is done, so a
     // failing call leaves the outputs untouched
     std::vector<int64_t> lam_out((size_t)k, 0);
-    std::vector<std::vector<uint8_t>> side_out(sides ? (size_t)k : 0);
+    std::vector<EngineInst> place((size_t)k);
     size_t got = 0;
     for (int32_t rounds = 0;; rounds++) {
         for (; got < fin.size(); got++) {
-            const EngineInst& x = fin[got];
-            lam_out[x.id] = x.lam;
-            uint8_t* so = nullptr;
-            if (sides && sides[x.id]) {
-                side_out[x.id].resize((size_t)x.n0);
-                so = side_out[x.id].data();
-            }
-            if ((r = E.side_of(x, so)) != MC_OK) return r;
+            lam_out[fin[got].id] = fin[got].lam;
+            place[fin[got].id] = fin[got];
         }
         if (E.live() == 0) break;
         if (rounds > cp.N + 64) return mc_fail(MC_E_DEVICE, "mc_mincut_batch: no progress");
         if ((r = E.step(fin)) != MC_OK) return r;
     }
+    // the graphs were admitted together, so their sides keep their places and
+    // come back in one copy
+    std::vector<uint8_t> side_out;
+    if (sides && E.n0_used > 0) {
+        side_out.resize((size_t)E.n0_used);
+        if (hipMemcpyAsync(side_out.data(), E.w.side, side_out.size(), hipMemcpyDeviceToHost, E.s) != hipSuccess ||
+            hipStreamSynchronize(E.s) != hipSuccess)
+            return mc_fail(MC_E_DEVICE, "mc_mincut_batch: copy of the sides failed");
+    }
     for (int32_t i = 0; i < k; i++) {
         if (per_graph) per_graph[i] = st[i];
         if (st[i] != MC_OK) continue;
         lambdas[i] = lam_out[i];
-        if (sides && sides[i]) std::copy(side_out[i].begin(), side_out[i].end(), sides[i]);
+        if (!sides || !sides[i]) continue;
+        uint8_t* const from = side_out.data() + place[i].ioff;
+        Engine::turn(from, place[i].n0);
+        std::copy(from, from + place[i].n0, sides[i]);
     }
     return MC_OK;
 }
@@ -1589,7 +1640,7 @@ mc_status drop_inflight(mc_server* S, uint64_t id) {
         if (x.id != id || x.dead) continue;
         x.done = true;
         x.dead = true;
-        return S->E.side_of(x, nullptr);   // stops tracking its input vertices
+        return S->E.untrack(x);   // stops tracking its input vertices
     }
     return MC_OK;
 }
