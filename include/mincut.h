@@ -124,9 +124,11 @@ typedef struct {
                                  (0 = 1024; < 0 = never) */
     int32_t queue;            /* priority queue of the finisher's CAPFOREST
                                  passes (Section 2.1 "Bounded priority
-                                 queues"): 0 = buckets while the bound is
-                                 below 2048, else a binary heap; 1 = buckets;
-                                 2 = heap (the largest key, then the
+                                 queues"): 0 = all vertices whose key has
+                                 reached the bound at once, else the largest
+                                 key, by a reduction over all keys; 1 =
+                                 buckets while the bound is below 2048, else
+                                 a heap; 2 = heap (the largest key, then the
                                  smallest id, as the sequential pass) */
     int32_t contract_mode;    /* edge merge of the contractions (Section 2:
                                  parallel edges summed, loops dropped) in

@@ -5,19 +5,29 @@
 //
 // One workgroup takes one graph of at most FIN_N vertices and runs every
 // remaining round of Algorithm 2 in one launch, with no host round trip:
-//  - a complete CAPFOREST pass (Algorithm 1, one pass, private state) run by
-//    one wavefront: one vertex is popped at a time and its row is scanned by
-//    the 64 lanes together; scanning x adds c(x) - 2 r(x) to alpha, which
-//    lowers lambda-hat while the scanned set is a proper subset; an edge to
-//    an unscanned y whose r(y) crosses lambda-hat is marked (union-find in
-//    LDS);
-//  - canonical relabelling of the marked components and contraction: the
-//    groups are merged by four wavefronts, each with a dense accumulator over
-//    the new vertices in LDS, into the other of two scratch buffers;
+//  - reduction tests 1 and 2, all rows at once; where they halve the graph
+//    the round goes on to contract;
+//  - else a complete CAPFOREST pass (Algorithm 1, one pass, private state):
+//    scanning x adds c(x) - 2 r(x) to alpha, which lowers lambda-hat while
+//    the scanned set is a proper subset; an edge to an unscanned y whose r(y)
+//    crosses lambda-hat is marked (union-find in LDS). The whole workgroup
+//    runs it, a thread per vertex, taking all capped vertices at once
+//    (fin_pass_batch);
+//  - canonical relabelling of the marked components and contraction, by slabs
+//    of the new adjacency matrix in LDS, into the other of two scratch
+//    buffers;
 //  - the collapsed degrees bound lambda-hat (Section 2.1 "Overall
 //    algorithm"),
-// until at most two vertices remain. The queue holds the keys min(r, lam),
-// integers in [0, lam]:
+// until at most two vertices remain. On MI355X a launch takes 93 us on one
+// graph of 128 vertices (247 us with the one-wavefront queues below and one
+// wavefront per merged group), 0.84 ms on the 160 graphs of at most 1024
+// vertices of a batch of 384 (3.1 ms), and 0.85 ms on the small requests of a
+// server with weights to 1000, whose bounds take the heap (9.2 ms). It is
+// bound by the steps of the passes, a serial chain of about 0.6 us each.
+//
+// Where a queue is asked for by name (or the bound is too large to be packed
+// beside a vertex), one wavefront runs the pass, one vertex a pop, with the
+// paper's queues. They hold the keys min(r, lam), integers in [0, lam]:
 //  - buckets (lam < FQB): one bucket per attainable key, each a LIFO list of
 //    nodes in an LDS pool; a key increase pushes a new node and leaves the
 //    old one behind (it is skipped when popped), so pushes from many lanes
@@ -33,11 +43,13 @@
 namespace {
 
 constexpr int FT = 1024;                 // threads of a finisher workgroup
-constexpr int FMW = 4;                   // wavefronts that merge groups
+constexpr int FWAVES = FT / MC_WAVE;
+constexpr int FSUB = 16;                 // lanes per row of the tests and the merge
+constexpr int FACC = 4 * FIN_N;          // accumulators of the merge
 constexpr int FQB = 2048;                // bucket heads: buckets while lam < FQB
 constexpr int FPOOL = 2048;              // bucket nodes before a rebuild
 
-enum : uint8_t { F_NEW = 0, F_QUEUED = 1, F_SCANNED = 2 };
+enum : uint8_t { F_NEW = 0, F_QUEUED = 1, F_SCANNED = 2, F_BATCH = 3 };
 
 struct FinLds {
     int32_t off[FIN_N], len[FIN_N];      // rows of the current graph (positions in its buffer)
@@ -56,13 +68,11 @@ struct FinLds {
     int16_t perm[FIN_N];                 // current vertices grouped by label
     uint8_t st[FIN_N];
     uint8_t bestf[FIN_N];                // side over the entry vertices of the best cut found here
-    int64_t acc[FMW][FIN_N];
-    int16_t tch[FMW][FIN_N];
-    int32_t ntch[FMW];
+    int64_t acc[FACC];
     int64_t red64[FT / MC_WAVE];
     int32_t red32[FT / MC_WAVE];
-    int32_t gnext;
-    int32_t n2;
+    int64_t bsum[3];                     // batch pass: sums of a step, in turn
+    int32_t bcnt[3];
 };
 
 // ------------------------------------------------------------ union-find
@@ -320,15 +330,152 @@ __device__ PassOut fin_pass(FinLds& S, int32_t n, const int32_t* __restrict__ co
     return o;
 }
 
-template <int NT>
-__device__ int32_t block_sum_i32(int32_t v, int32_t* red) {
-    for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, MC_WAVE);
+// ------------------------------------------------------------ batch pass
+// the largest value of the wavefront, in every lane (DPP moves: a shuffle
+// through LDS costs a few hundred cycles per step pair)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint64_t dpp_max_step(uint64_t v) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, ROWS, 0xf, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), CTRL, ROWS, 0xf, false);
+    const uint64_t u = ((uint64_t)hi << 32) | lo;
+    return u > v ? u : v;
+}
+__device__ __forceinline__ uint64_t read_lane_u64(uint64_t v, int lane) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, lane);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), lane);
+    return ((uint64_t)hi << 32) | lo;
+}
+__device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) {
+    v = dpp_max_step<0x111, 0xf>(v);   // row_shr:1, 2, 4, 8: lane 15 of each row holds its row's
+    v = dpp_max_step<0x112, 0xf>(v);
+    v = dpp_max_step<0x114, 0xf>(v);
+    v = dpp_max_step<0x118, 0xf>(v);
+    v = dpp_max_step<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
+    v = dpp_max_step<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
+    return read_lane_u64(v, 63);
+}
+
+// One complete CAPFOREST pass by the whole workgroup, a thread per vertex.
+// Each step takes every queued vertex whose key has reached lam at once (they
+// tie at the largest key, so any order among them is one of the queue's;
+// alpha grows by sum(c(x) - 2 r(x)) less the entries inside the batch), or
+// else the one vertex of the largest key, found by a reduction over all keys.
+// A step is three barriers and one round trip to the rows, about 0.6 us,
+// where a pop of the one-wavefront queues took 0.9 us (buckets) and several
+// us (heap, whose entries are sifted one at a time by one lane), and the
+// capped vertices, most of a pass, leave many at a time.
+// Keys are packed above the vertex: lam < FKEY.
+constexpr int64_t FKEY = (int64_t)1 << 52;
+__device__ PassOut fin_pass_batch(FinLds& S, int32_t n, const int32_t* __restrict__ col, const int64_t* __restrict__ w,
+                                  int32_t cbase, int32_t start, int64_t lam) {
+    const int tid = threadIdx.x, lane = lane_id(), wid = tid / MC_WAVE;
+    if (tid < n) {
+        S.st[tid] = tid == start ? F_QUEUED : F_NEW;
+        S.r[tid] = 0;
+    }
+    if (tid < 3) { S.bsum[tid] = 0; S.bcnt[tid] = 0; }
     __syncthreads();
-    if (lane_id() == 0) red[threadIdx.x / MC_WAVE] = v;
-    __syncthreads();
-    int32_t t = 0;
-    for (int k = 0; k < NT / MC_WAVE; k++) t += red[k];
-    return t;
+    PassOut o;
+    o.best_alpha = -1;
+    o.best_len = 0;
+    o.nscan = 0;
+    o.marks = 0;
+    int64_t alpha = 0;
+    for (int step = 0;; step = step == 2 ? 0 : step + 1) {
+        uint64_t key = 0;
+        bool capped = false;
+        int64_t rx = 0;
+        if (tid < n && S.st[tid] == F_QUEUED) {
+            rx = S.r[tid];
+            capped = rx >= lam;
+            key = ((uint64_t)(capped ? lam : rx) << 10) + (uint64_t)(FIN_N - tid);
+        }
+        uint64_t best = wave_max_u64(key);
+        if (lane == 0) S.red64[wid] = (int64_t)best;
+        __syncthreads();
+        best = wave_max_u64(lane < FWAVES ? (uint64_t)S.red64[lane] : 0);
+        if (best == 0) break;                         // queue empty
+        const bool batch = (int64_t)((best - 1) >> 10) >= lam;
+        const int32_t x1 = FIN_N - 1 - (int32_t)((best - 1) & (FIN_N - 1));
+        // ---- the vertices of the step: states, places in the order, alpha
+        const bool mine = batch ? capped : tid == x1;
+        const unsigned long long m = __ballot(mine);
+        if (m) {
+            int64_t part = mine ? S.deg[tid] - 2 * rx : 0;
+            int32_t at = 0;
+            if (lane == 0) at = atomicAdd(&S.bcnt[step], (int32_t)__popcll(m));
+            at = __builtin_amdgcn_readfirstlane(at);
+            if (mine) {
+                S.st[tid] = F_BATCH;
+                S.order[o.nscan + at + __popcll(m & ((1ULL << lane) - 1))] = (int16_t)tid;
+            }
+            if (batch) part = wave_sum_i64(part);
+            if (batch ? lane == 0 : mine) atomicAdd((unsigned long long*)&S.bsum[step], (unsigned long long)part);
+        }
+        // the next but one step's sums (no one has read them since the last
+        // barrier, no one adds to them before the next)
+        if (tid == 0) { const int z = step == 2 ? 0 : step + 1; S.bsum[z] = 0; S.bcnt[z] = 0; }
+        __syncthreads();
+        const int32_t b = S.bcnt[step];
+        // ---- scan the rows: one row by all threads, or a row a wavefront
+        int64_t inside = 0;
+        auto entry = [&](int32_t x, int32_t j) {
+            const int32_t y = col[j] - cbase;
+            const int64_t c = w[j];
+            const uint8_t sy = S.st[y];
+            if (sy == F_BATCH) { inside += c; return; }
+            if (sy == F_SCANNED) return;
+            const int64_t old = (int64_t)atomicAdd((unsigned long long*)&S.r[y], (unsigned long long)c);
+            if (sy == F_NEW) S.st[y] = F_QUEUED;
+            if (old < lam && lam <= old + c) lf_union(S.parent, x, y);
+        };
+        if (b == 1) {
+            const int32_t x = S.order[o.nscan];
+            const int32_t ox = S.off[x], lx = S.len[x];
+            for (int32_t j = tid; j < lx; j += FT) entry(x, ox + j);
+        } else {
+            for (int32_t q = wid; q < b; q += FWAVES) {
+                const int32_t x = S.order[o.nscan + q];
+                const int32_t ox = S.off[x], lx = S.len[x];
+                for (int32_t j = lane; j < lx; j += MC_WAVE) entry(x, ox + j);
+            }
+        }
+        if (inside) atomicAdd((unsigned long long*)&S.bsum[step], (unsigned long long)-inside);
+        __syncthreads();
+        if (mine) S.st[tid] = F_SCANNED;
+        alpha += S.bsum[step];
+        o.nscan += b;
+        if (o.nscan < n) {
+            if (o.best_alpha < 0 || alpha < o.best_alpha) { o.best_alpha = alpha; o.best_len = o.nscan; }
+            if (alpha < lam) lam = alpha;
+        }
+    }
+    o.lam = lam;
+    return o;
+}
+
+// Tests 1 and 2 on the whole graph: entries of weight lam or more, and each
+// vertex's heaviest neighbour where it holds half of the degree, are unioned.
+__device__ void fin_tests(FinLds& S, int32_t n, const int32_t* __restrict__ col, const int64_t* __restrict__ w,
+                          int32_t cbase, int64_t lam) {
+    const int sl = threadIdx.x % FSUB;
+    for (int32_t v = threadIdx.x / FSUB; v < n; v += FT / FSUB) {
+        const int32_t o = S.off[v], l = S.len[v];
+        int64_t bw = -1;
+        int32_t by = -1;
+        for (int32_t j = sl; j < l; j += FSUB) {
+            const int32_t y = col[o + j] - cbase;
+            const int64_t c = w[o + j];
+            if (c >= lam && y > v) lf_union(S.parent, v, y);
+            if (c > bw || (c == bw && y < by)) { bw = c; by = y; }
+        }
+        for (int d = FSUB / 2; d > 0; d >>= 1) {
+            const int64_t w2 = __shfl_xor(bw, d, FSUB);
+            const int32_t y2 = __shfl_xor(by, d, FSUB);
+            if (y2 >= 0 && (by < 0 || w2 > bw || (w2 == bw && y2 < by))) { bw = w2; by = y2; }
+        }
+        if (sl == 0 && by >= 0 && 2 * bw >= S.deg[v]) lf_union(S.parent, v, by);
+    }
 }
 
 // exclusive scan of a[0..n) into out[0..n] (out[n] = total), whole block;
@@ -371,6 +518,21 @@ __device__ void block_scan_lds(const int32_t* a, int32_t* out, int32_t n, FinLds
     __syncthreads();
 }
 
+// canonical labels of the marked components (roots are the smallest vertex of
+// their component): gstart[v] the root, vstart[] the roots' numbers; returns
+// their count
+__device__ int32_t fin_roots(FinLds& S, int32_t n) {
+    for (int32_t v = threadIdx.x; v < n; v += FT) {
+        int32_t r0 = S.parent[v];
+        while (S.parent[r0] != r0) r0 = S.parent[r0];
+        S.vstart[v] = r0 == v ? 1 : 0;
+        S.gstart[v] = r0;
+    }
+    __syncthreads();
+    block_scan_lds(S.vstart, S.vstart, n, S);
+    return S.vstart[n];
+}
+
 }  // namespace
 
 // All remaining rounds of graph k by one workgroup (see the file comment).
@@ -406,45 +568,55 @@ static __device__ __forceinline__ void finish_one(const FinishArgs& a, int32_t k
         if (rounds >= max_rounds) { err = 2; break; }
         for (int32_t v = tid; v < n; v += FT) S.parent[v] = v;
         __syncthreads();
-        // ---- one complete CAPFOREST pass (wavefront 0)
-        const uint64_t h = splitmix64(a.seed ^ splitmix64(((uint64_t)(uint32_t)rounds << 32) ^ (uint64_t)(uint32_t)k));
-        const int32_t start = (int32_t)(((h >> 32) * (uint64_t)n) >> 32);
-        // buckets need one bucket per attainable key, so a bound of FQB or
-        // more always takes the heap
-        const bool heap_mode = a.qmode == 2 || lam >= FQB;
         const int64_t lam_prev = lam;
-        if (wid == 0) {
-            const PassOut po = fin_pass(S, n, col, w, cbase, start, lam, heap_mode, scal);
-            if (lane == 0) {
-                sc64[0] = po.lam;
-                scal[4] = po.best_len;
-            }
-        }
-        __syncthreads();
-        const int64_t lam_pass = sc64[0];
-        const int32_t best_len = scal[4];
         rounds++;
-        if (lam_pass < lam_prev) {
-            // the best proper prefix of the pass is the new side
-            for (int32_t v = tid; v < n; v += FT) S.lab[v] = 0;
+        // ---- tests 1 and 2; where they halve the graph no pass is needed
+        // (left to itself; the queues asked for by name keep to their passes)
+        int32_t n2 = n;
+        if (a.qmode == 0) {
+            fin_tests(S, n, col, w, cbase, lam);
             __syncthreads();
-            for (int32_t i = tid; i < best_len; i += FT) S.lab[S.order[i]] = 1;
+            n2 = fin_roots(S, n);
+        }
+        if (2 * n2 > n) {
+            // ---- one complete CAPFOREST pass
+            const uint64_t h = splitmix64(a.seed ^ splitmix64(((uint64_t)(uint32_t)(rounds - 1) << 32) ^ (uint64_t)(uint32_t)k));
+            const int32_t start = (int32_t)(((h >> 32) * (uint64_t)n) >> 32);
+            if (a.qmode == 0 && lam < FKEY) {
+                const PassOut po = fin_pass_batch(S, n, col, w, cbase, start, lam);
+                if (tid == 0) {
+                    sc64[0] = po.lam;
+                    scal[4] = po.best_len;
+                }
+            } else if (wid == 0) {
+                // buckets need one bucket per attainable key, so a bound of
+                // FQB or more always takes the heap
+                const PassOut po = fin_pass(S, n, col, w, cbase, start, lam, a.qmode == 2 || lam >= FQB, scal);
+                if (lane == 0) {
+                    sc64[0] = po.lam;
+                    scal[4] = po.best_len;
+                }
+            }
             __syncthreads();
-            for (int32_t u = tid; u < n0; u += FT) S.bestf[u] = (uint8_t)S.lab[S.fmap[u]];
-            lam = lam_pass;
-            dropped = true;
+            const int64_t lam_pass = sc64[0];
+            const int32_t best_len = scal[4];
+            if (lam_pass < lam_prev) {
+                // the best proper prefix of the pass is the new side
+                for (int32_t v = tid; v < n; v += FT) S.lab[v] = 0;
+                __syncthreads();
+                for (int32_t i = tid; i < best_len; i += FT) S.lab[S.order[i]] = 1;
+                __syncthreads();
+                for (int32_t u = tid; u < n0; u += FT) S.bestf[u] = (uint8_t)S.lab[S.fmap[u]];
+                lam = lam_pass;
+                dropped = true;
+            }
+            __syncthreads();
+            n2 = fin_roots(S, n);
         }
-        // ---- canonical labels of the marked components (roots are the
-        // smallest vertex of their component)
-        for (int32_t v = tid; v < n; v += FT) {
-            int32_t r0 = S.parent[v];
-            while (S.parent[r0] != r0) r0 = S.parent[r0];
-            S.vstart[v] = r0 == v ? 1 : 0;
-            S.gstart[v] = r0;
+        if (n2 == 1) {          // everything joins one vertex: no later bound needs the rest
+            n = 1;
+            break;
         }
-        __syncthreads();
-        block_scan_lds(S.vstart, S.vstart, n, S);
-        const int32_t n2 = S.vstart[n];
         for (int32_t v = tid; v < n; v += FT) S.lab[v] = (int16_t)S.vstart[S.gstart[v]];
         __syncthreads();
         if (n2 == n) {
@@ -467,64 +639,46 @@ static __device__ __forceinline__ void finish_one(const FinishArgs& a, int32_t k
         for (int32_t g = tid; g < n2; g += FT) S.parent[g] = S.vstart[g];   // fill cursors
         __syncthreads();
         for (int32_t v = tid; v < n; v += FT) S.perm[atomicAdd(&S.parent[S.lab[v]], 1)] = (int16_t)v;
-        for (int32_t i = tid; i < FMW * n2; i += FT) S.acc[i / n2][i % n2] = 0;
-        if (tid == 0) S.gnext = 0;
+        for (int32_t i = tid; i < FACC; i += FT) S.acc[i] = 0;
         __syncthreads();
-        // ---- merge: FMW wavefronts take groups in turn; each sums its
-        // group's entries by new target in its dense accumulator
+        for (int32_t g = tid; g < n2; g += FT) { S.parent[g] = 0; S.r[g] = 0; }   // new rows' lengths and degrees
+        __syncthreads();
+        // ---- merge, a slab of groups at a time: the slab's rows of the new
+        // adjacency matrix lie in the accumulators, all its members' rows are
+        // added by 16 lanes each, and the non-zero sums are written out. (With
+        // a wavefront per group, a group of 900 members took its wavefront
+        // 900 dependent round trips.)
         int32_t* ocol = a.xcol[buf];
         int64_t* ow = a.xw[buf];
-        if (wid < FMW) {
-            int64_t* acc = S.acc[wid];
-            int16_t* tch = S.tch[wid];
-            for (;;) {
-                int32_t g = 0;
-                if (lane == 0) {
-                    g = atomicAdd(&S.gnext, 1);
-                    S.ntch[wid] = 0;
+        const int32_t slab = FACC / n2 < n2 ? FACC / n2 : n2;
+        const int sl = tid % FSUB;
+        for (int32_t g0 = 0; g0 < n2; g0 += slab) {
+            const int32_t g1 = g0 + slab < n2 ? g0 + slab : n2;
+            for (int32_t m = S.vstart[g0] + tid / FSUB; m < S.vstart[g1]; m += FT / FSUB) {
+                const int32_t v = S.perm[m];
+                const int32_t g = S.lab[v], ov = S.off[v], lv = S.len[v];
+                for (int32_t j = sl; j < lv; j += FSUB) {
+                    const int32_t t = S.lab[col[ov + j] - cbase];
+                    if (t != g)      // else inside the group
+                        atomicAdd((unsigned long long*)&S.acc[(g - g0) * n2 + t], (unsigned long long)w[ov + j]);
                 }
-                g = __shfl(g, 0, MC_WAVE);
-                wave_sync();
-                if (g >= n2) break;
-                for (int32_t m = S.vstart[g]; m < S.vstart[g + 1]; m++) {
-                    const int32_t v = S.perm[m];
-                    const int32_t ov = S.off[v], lv = S.len[v];
-                    for (int32_t j = lane; j < lv; j += MC_WAVE) {
-                        const int32_t t = S.lab[col[ov + j] - cbase];
-                        if (t == g) continue;    // inside the group
-                        const int64_t c = w[ov + j];
-                        const unsigned long long old = atomicAdd((unsigned long long*)&acc[t], (unsigned long long)c);
-                        if (old == 0) tch[atomicAdd(&S.ntch[wid], 1)] = (int16_t)t;
-                    }
-                    wave_sync();
-                }
-                const int32_t nt = S.ntch[wid];
-                const int32_t gs = ebase + S.gstart[g];
-                int64_t dsum = 0;
-                for (int32_t i = lane; i < nt; i += MC_WAVE) {
-                    const int32_t t = tch[i];
-                    const int64_t c = acc[t];
-                    acc[t] = 0;
-                    ocol[gs + i] = t;
-                    ow[gs + i] = c;
-                    dsum += c;
-                }
-                dsum = wave_sum_i64(dsum);
-                wave_sync();
-                if (lane == 0) {
-                    // the new row: start, length, degree (r[] is free until
-                    // the next pass); only this wavefront touches group g
-                    S.parent[g] = gs;
-                    S.gstart[g] = nt;
-                    S.r[g] = dsum;
-                }
-                wave_sync();
             }
+            __syncthreads();
+            for (int32_t i = tid; i < (g1 - g0) * n2; i += FT) {
+                const int64_t c = S.acc[i];
+                if (c == 0) continue;
+                S.acc[i] = 0;
+                const int32_t g = g0 + i / n2, t = i % n2;
+                const int32_t at = ebase + S.gstart[g] + atomicAdd(&S.parent[g], 1);
+                ocol[at] = t;
+                ow[at] = c;
+                atomicAdd((unsigned long long*)&S.r[g], (unsigned long long)c);
+            }
+            __syncthreads();
         }
-        __syncthreads();
         for (int32_t g = tid; g < n2; g += FT) {
-            S.off[g] = S.parent[g];
-            S.len[g] = S.gstart[g];
+            S.off[g] = ebase + S.gstart[g];
+            S.len[g] = S.parent[g];
             S.deg[g] = S.r[g];
         }
         for (int32_t u = tid; u < n0; u += FT) S.fmap[u] = S.lab[S.fmap[u]];
