@@ -20,6 +20,7 @@
 // work, not the result).
 #include <algorithm>
 #include <chrono>
+#include <cstdlib>
 #include <vector>
 
 #include "mc_internal.h"
@@ -1489,7 +1490,71 @@ extern "C" mc_status mc_batch_autotune(mc_ctx* c, int32_t k, const mc_csr* gs, v
 #include <thread>
 #include <unordered_map>
 
+// Host memory of the requests' copies. A buffer given back is kept for the
+// next request of about its size (a fresh one costs a page fault per 4 KB),
+// kPoolBytes in all at most, until the server ends. One thread at a time, as
+// the server's calls.
+class HostPool {
+public:
+    static constexpr size_t kPoolBytes = (size_t)512 << 20;
+    ~HostPool() {
+        for (const Buf& b : free_) std::free(b.p);
+    }
+    void* take(size_t bytes, size_t* cap) {
+        size_t best = free_.size();
+        for (size_t i = 0; i < free_.size(); i++)
+            if (free_[i].cap >= bytes && free_[i].cap / 2 <= bytes && (best == free_.size() || free_[i].cap < free_[best].cap))
+                best = i;
+        if (best < free_.size()) {
+            const Buf b = free_[best];
+            free_[best] = free_.back();
+            free_.pop_back();
+            held_ -= b.cap;
+            *cap = b.cap;
+            return b.p;
+        }
+        *cap = bytes;
+        return std::malloc(bytes);
+    }
+    void give(void* p, size_t cap) {
+        if (held_ + cap > kPoolBytes) { std::free(p); return; }
+        free_.push_back({p, cap});
+        held_ += cap;
+    }
+
+private:
+    struct Buf { void* p; size_t cap; };
+    std::vector<Buf> free_;
+    size_t held_ = 0;
+};
+
+// one request's copy: weights, targets and row offsets in one buffer
+struct HostCopy {
+    HostPool* pool = nullptr;
+    char* p = nullptr;
+    size_t cap = 0;
+    int32_t n = 0, nnz = 0;
+    HostCopy() = default;
+    HostCopy(const HostCopy&) = delete;
+    HostCopy& operator=(const HostCopy&) = delete;
+    HostCopy(HostCopy&& o) noexcept : pool(o.pool), p(o.p), cap(o.cap), n(o.n), nnz(o.nnz) { o.p = nullptr; }
+    ~HostCopy() {
+        if (p) pool->give(p, cap);
+    }
+    bool make(HostPool* from, int32_t vertices, int32_t entries) {
+        pool = from;
+        n = vertices;
+        nnz = entries;
+        p = (char*)pool->take(12 * (size_t)nnz + 4 * ((size_t)n + 1), &cap);
+        return p != nullptr;
+    }
+    int64_t* w() const { return (int64_t*)p; }
+    int32_t* col() const { return (int32_t*)(p + 8 * (size_t)nnz); }
+    int32_t* rp() const { return (int32_t*)(p + 12 * (size_t)nnz); }
+};
+
 struct mc_server {
+    HostPool pool;                // outlives the requests
     mc_ctx* c = nullptr;
     void* mem = nullptr;
     size_t bytes = 0;             // engine part of mem
@@ -1499,8 +1564,7 @@ struct mc_server {
     double deadline_ms = 0;
     std::chrono::steady_clock::time_point t0;
     struct Req {
-        std::vector<int32_t> rp, col;
-        std::vector<int64_t> w;
+        HostCopy data;
         int32_t n = 0, nnz = 0;
         int state = 0;             // 0 queued, 1 in flight, 2 done, 3 cancelled, 4 failed, 5 timed out
         bool cancel = false;
@@ -1581,9 +1645,9 @@ mc_csr host_csr(const mc_server::Req& r) {
     mc_csr g;
     g.n = r.n;
     g.nnz = r.nnz;
-    g.row_ptr = r.rp.data();
-    g.col = r.col.data();
-    g.w = r.w.data();
+    g.row_ptr = r.data.rp();
+    g.col = r.data.col();
+    g.w = r.data.w();
     g.location = MC_HOST;
     return g;
 }
@@ -1624,7 +1688,8 @@ bool start_solo(mc_server* S, uint64_t id) {
         mc_server::Slot* p = &sl;
         const size_t wsb = S->solo_bytes;
         sl.th = std::thread([p, g, wsb]() {
-            p->st = mc_mincut(p->ctx, &g, p->ws, wsb, &p->lam, p->side.data(), nullptr);
+            // checked when it was submitted
+            p->st = mincut_checked(p->ctx, &g, p->ws, wsb, &p->lam, p->side.data(), nullptr);
             if (p->st != MC_OK) p->err = mc_last_error();
             p->busy.store(2, std::memory_order_release);
         });
@@ -1732,7 +1797,10 @@ extern "C" mc_status mc_server_submit(mc_server* S, const mc_csr* g, uint64_t* t
     if (g->location != MC_HOST) return mc_fail(MC_E_INVALID_ARG, "mc_server_submit: host graphs only");
     // the request's contents are checked here, so admission never fails on
     // data
-    mc_status v = check_host_csr(g, S->c->opt.validate != 0);
+    if (g->n < 2 || g->nnz < 0) return check_host_csr(g, false);
+    mc_server::Req r;
+    if (!r.data.make(&S->pool, g->n, g->nnz)) return mc_fail(MC_E_OOM, "mc_server_submit: out of host memory");
+    mc_status v = check_host_csr(g, S->c->opt.validate != 0, r.data.col(), r.data.w());
     if (v != MC_OK) return v;
     const Caps& cp = S->E.cap;
     if (g->n >= S->solo_min_n) {
@@ -1743,12 +1811,9 @@ extern "C" mc_status mc_server_submit(mc_server* S, const mc_csr* g, uint64_t* t
     } else if (g->n > cp.nmax || g->n > cp.Ns || g->nnz > cp.Cs || g->n > cp.N || g->nnz > cp.C) {
         return mc_fail(MC_E_OOM, "mc_server_submit: graph larger than the server admits");
     }
-    mc_server::Req r;
     r.n = g->n;
     r.nnz = g->nnz;
-    r.rp.assign(g->row_ptr, g->row_ptr + g->n + 1);
-    r.col.assign(g->col, g->col + g->nnz);
-    r.w.assign(g->w, g->w + g->nnz);
+    std::copy(g->row_ptr, g->row_ptr + g->n + 1, r.data.rp());
     r.st.t_submit_ms = S->now();
     const uint64_t id = S->next++;
     S->reqs.emplace(id, std::move(r));

@@ -22,5 +22,6 @@ mc_status mc_options_check(const mc_options* o);
 // (MC_E_BAD_GRAPH); every target in [0, n) and weight >= 0
 // (MC_E_BAD_GRAPH); total weight below 2^62 (MC_E_OVERFLOW); with
 // `symmetric`, every folded pair (u, v, s) matched by (v, u, s)
-// (MC_E_BAD_GRAPH). Reads the arrays only.
-mc_status check_host_csr(const mc_csr* g, bool symmetric);
+// (MC_E_BAD_GRAPH). Reads the arrays only, and copies the entries to ccol and
+// cw (nnz each; null: no copy) in the same pass.
+mc_status check_host_csr(const mc_csr* g, bool symmetric, int32_t* ccol = nullptr, int64_t* cw = nullptr);

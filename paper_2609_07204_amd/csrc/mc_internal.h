@@ -482,6 +482,9 @@ bool canon_check(const int32_t* row_ptr, const int32_t* col, const int64_t* w, i
                  int64_t* deg, int32_t* noncanon, DevScalars* sc, unsigned long long* part, int32_t* lp1,
                  hipStream_t s);
 
+// mc_mincut of a graph that check_host_csr has passed
+mc_status mincut_checked(mc_ctx* c, const mc_csr* g, void* dev_ws, size_t ws_bytes, int64_t* lambda, uint8_t* side,
+                         mc_stats* st);
 // Smallest workspace mc_mincut accepts for a graph (small rounds keep their
 // first pass count); mc_workspace_size adds room for one pass per compute
 // unit.

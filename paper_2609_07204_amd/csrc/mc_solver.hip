@@ -1274,8 +1274,8 @@ static mc_status heuristic(Solver& S) {
     return MC_OK;
 }
 
-extern "C" mc_status mc_mincut(mc_ctx* c, const mc_csr* g, void* dev_ws, size_t ws_bytes, int64_t* lambda,
-                               uint8_t* side_out, mc_stats* st) {
+static mc_status solve(mc_ctx* c, const mc_csr* g, void* dev_ws, size_t ws_bytes, int64_t* lambda, uint8_t* side_out,
+                       mc_stats* st, bool checked) {
     auto t0 = std::chrono::steady_clock::now();
     if (!c || !g || !lambda) return fail(MC_E_INVALID_ARG, "mc_mincut: NULL argument");
     if (g->n < 2) return fail(MC_E_INVALID_ARG, "mc_mincut: need n >= 2");
@@ -1284,7 +1284,7 @@ extern "C" mc_status mc_mincut(mc_ctx* c, const mc_csr* g, void* dev_ws, size_t 
     if (g->location != MC_HOST && g->location != MC_DEVICE) return fail(MC_E_INVALID_ARG, "mc_mincut: bad location");
     if (!dev_ws) return fail(MC_E_INVALID_ARG, "mc_mincut: workspace is NULL");
     const bool host_input = g->location == MC_HOST;
-    if (host_input) {
+    if (host_input && !checked) {
         mc_status v = check_host_csr(g, c->opt.validate != 0);
         if (v != MC_OK) return v;
     }
@@ -1435,6 +1435,16 @@ extern "C" mc_status mc_mincut(mc_ctx* c, const mc_csr* g, void* dev_ws, size_t 
         *st = S.stats;
     }
     return MC_OK;
+}
+
+extern "C" mc_status mc_mincut(mc_ctx* c, const mc_csr* g, void* dev_ws, size_t ws_bytes, int64_t* lambda,
+                               uint8_t* side_out, mc_stats* st) {
+    return solve(c, g, dev_ws, ws_bytes, lambda, side_out, st, false);
+}
+
+mc_status mincut_checked(mc_ctx* c, const mc_csr* g, void* dev_ws, size_t ws_bytes, int64_t* lambda, uint8_t* side_out,
+                         mc_stats* st) {
+    return solve(c, g, dev_ws, ws_bytes, lambda, side_out, st, true);
 }
 
 extern "C" mc_status mc_mincut_static(mc_ctx* c, const mc_csr* g, int64_t* lambda, uint8_t* side_out, mc_stats* st) {
