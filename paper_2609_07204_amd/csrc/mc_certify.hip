@@ -20,8 +20,8 @@
 //    98 % with hashed starts). The first two rounds, 2 k units, are used.
 // The first unit of a vertex in a subgraph points to a heavier vertex, so the
 // first round is a forest written without atomics; the second round is
-// linked by union-find over its compressed trees. All k subgraphs are built
-// side by side (one row of k n parents), so the test is a dozen launches
+// linked in sweeps over its compressed trees. All k subgraphs are built
+// side by side (one row of k n parents), so the test is two dozen launches
 // whatever k is.
 //
 // The vertices connected in every subgraph to a reference (of 64 sampled
@@ -43,8 +43,9 @@ namespace {
 
 constexpr int SUB = 16;          // lanes per row
 constexpr int ROWS = 64;         // rows dealt out by one workgroup at a time
-constexpr int32_t CERT_ROW = 4096;   // entries of a row looked at (a long row is a heavy vertex, which owns little)
-constexpr int CERT_NEAR = 16;
+constexpr int32_t CERT_ROW = 512;    // entries of a row looked at (a long row is a heavy vertex, which owns little)
+constexpr int CERT_NEAR = 8;
+constexpr int CERT_SWEEPS = 4;
 constexpr int64_t CERT_EASY = 5;
 constexpr int32_t CERT_PROBE_N = 1 << 15;
 
@@ -98,41 +99,67 @@ __global__ __launch_bounds__(256) void k_cert_level(CertArgs a) {
 // Deals every row's units out: own[r * kc + i][v] = target of v's unit in
 // subgraph i, round r. Round 0 is written as a parent (v itself without a
 // unit), round 1 as a target or -1. A workgroup stages ROWS rows in LDS and
-// writes each subgraph's words of them side by side.
+// writes each subgraph's words of them side by side. It is bound by the
+// latency of its loads, each behind the last (row bounds, entries, degree
+// classes of the targets), so 16 lanes take PER rows at once: their bounds
+// come in one load, and the first entries and classes of all of them are in
+// flight together; only the words of the k subgraphs are written, and a row
+// is cut at CERT_ROW entries (Chung-Lu 2^22, 10-core, 51 million entries: 0.49
+// ms; a row at a time, all words and rows of up to 4096 entries 0.69 ms).
 __global__ __launch_bounds__(256) void k_cert_rows(CertArgs a) {
+    constexpr int PER = ROWS / (256 / SUB);   // rows of 16 lanes
+    constexpr int UN = 2;                     // entries a lane has in flight per row
     __shared__ int32_t tile[ROWS][2 * CERT_KMAX + 1];
-    const int kc2 = 2 * a.kc;
+    // a single graph writes the words of its own k subgraphs only
+    const int km = a.vinst ? a.kc : a.count[0];
     const int sl = threadIdx.x % SUB, sub = threadIdx.x / SUB;
     const int32_t n = a.g.n;
     for (int64_t v0 = (int64_t)blockIdx.x * ROWS; v0 < n; v0 += (int64_t)gridDim.x * ROWS) {
-        for (int i = threadIdx.x; i < ROWS * kc2; i += 256) tile[i / kc2][i % kc2] = -1;
+        for (int i = threadIdx.x; i < ROWS * 2 * km; i += 256) tile[i % ROWS][i / ROWS] = -1;
+        // lane q < PER holds the bounds of the q-th row of the 16 lanes
+        const int64_t mv = v0 + sub * PER + sl;
+        int32_t m_o = 0, m_l = 0, m_k = 0, m_lv = 0;
+        int64_t m_c = 1;
+        if (sl < PER && mv < n && !inactive(a, mv)) {
+            const int32_t inst = a.vinst ? a.vinst[mv] : 0;
+            m_k = a.count[inst];
+            m_c = a.unit[inst];
+            m_o = a.g.off[mv];
+            m_l = a.g.len[mv] < CERT_ROW ? a.g.len[mv] : CERT_ROW;
+            m_lv = a.level[mv];
+        }
+        int32_t x[PER][UN], lx[PER][UN];
+        int64_t w[PER][UN];
+        auto load = [&](int q, int32_t o, int32_t l, int32_t j0) {
+#pragma unroll
+            for (int u = 0; u < UN; u++) {
+                const int32_t j = j0 + u * SUB + sl;
+                x[q][u] = j < l ? a.g.col[o + j] : -1;
+                w[q][u] = j < l ? a.g.w[o + j] : 0;
+            }
+        };
+        auto classes = [&](int q, int64_t c) {
+#pragma unroll
+            for (int u = 0; u < UN; u++) lx[q][u] = w[q][u] >= c && x[q][u] >= 0 ? a.level[x[q][u]] : -1;
+        };
+#pragma unroll
+        for (int q = 0; q < PER; q++) load(q, __shfl(m_o, q, SUB), __shfl(m_l, q, SUB), 0);
+#pragma unroll
+        for (int q = 0; q < PER; q++) classes(q, __shfl(m_c, q, SUB));
         __syncthreads();
-        for (int q = sub; q < ROWS; q += 256 / SUB) {
-            const int64_t v = v0 + q;
-            if (v >= n || inactive(a, v)) continue;
-            const int32_t inst = a.vinst ? a.vinst[v] : 0;
-            const int64_t c = a.unit[inst];
-            const int32_t k = a.count[inst];
-            const int32_t o = a.g.off[v], l = a.g.len[v] < CERT_ROW ? a.g.len[v] : CERT_ROW;
-            const int lv = a.level[v];
+#pragma unroll
+        for (int q = 0; q < PER; q++) {
+            const int32_t v = (int32_t)(v0 + sub * PER + q);
+            const int32_t o = __shfl(m_o, q, SUB), l = __shfl(m_l, q, SUB), k = __shfl(m_k, q, SUB), lv = __shfl(m_lv, q, SUB);
+            const int64_t c = __shfl(m_c, q, SUB);
             const int32_t first = (int32_t)(((uint64_t)hash32((uint32_t)v) * (uint64_t)k) >> 32);
             int32_t base = 0;
-            for (int32_t j0 = 0; j0 < l && base < 2 * k; j0 += 4 * SUB) {
-                int32_t x[4], lx[4];
-                int64_t w[4];
+            for (int32_t j0 = 0; j0 < l && base < 2 * k;) {
 #pragma unroll
-                for (int u = 0; u < 4; u++) {
-                    const int32_t j = j0 + u * SUB + sl;
-                    x[u] = j < l ? a.g.col[o + j] : -1;
-                    w[u] = j < l ? a.g.w[o + j] : 0;
-                }
-#pragma unroll
-                for (int u = 0; u < 4; u++) lx[u] = w[u] >= c && x[u] >= 0 ? a.level[x[u]] : -1;
-#pragma unroll
-                for (int u = 0; u < 4; u++) {
+                for (int u = 0; u < UN; u++) {
                     int32_t units = 0;
-                    if (lx[u] > lv || (lx[u] == lv && x[u] > v)) {
-                        int64_t left = w[u];
+                    if (lx[q][u] > lv || (lx[q][u] == lv && x[q][u] > v)) {
+                        int64_t left = w[q][u];
 #pragma unroll
                         for (int b = 5; b >= 0; b--)
                             if ((left >> b) >= c) { left -= c << b; units += 1 << b; }
@@ -150,74 +177,89 @@ __global__ __launch_bounds__(256) void k_cert_rows(CertArgs a) {
                         const int r = t >= k;
                         int32_t i = t - (r ? k : 0) + first;
                         if (i >= k) i -= k;
-                        tile[q][r * a.kc + i] = x[u];
+                        tile[sub * PER + q][r * km + i] = x[q][u];
                     }
+                }
+                j0 += UN * SUB;
+                if (j0 < l && base < 2 * k) {
+                    load(q, o, l, j0);
+                    classes(q, c);
                 }
             }
         }
         __syncthreads();
-        for (int i = threadIdx.x; i < ROWS * kc2; i += 256) {
+        for (int i = threadIdx.x; i < ROWS * 2 * km; i += 256) {
             const int slot = i / ROWS, q = i % ROWS;
             const int64_t v = v0 + q;
             if (v >= n) continue;
             int32_t t = tile[q][slot];
-            if (t < 0 && slot < a.kc) t = (int32_t)v;
-            a.own[(int64_t)slot * n + v] = t;
+            if (t < 0 && slot < km) t = (int32_t)v;
+            a.own[(int64_t)(slot < km ? slot : slot - km + a.kc) * n + v] = t;
         }
         __syncthreads();
     }
 }
 
-// every vertex at its root, in every subgraph (blockIdx.y)
-__global__ __launch_bounds__(256) void k_cert_compress(CertArgs a) {
+// Parents as the last launch left them, or newer: a load that the caches may
+// serve. Device-scope loads go past the L2 of the compute unit's die, which
+// made them the bound of these kernels. An old parent is an ancestor too.
+__device__ __forceinline__ int32_t ld_old(const int32_t* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void st_new(int32_t* p, int32_t v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// every vertex at its root, in every subgraph (blockIdx.y); after sweep
+// `sweep` only in those that it changed
+__global__ __launch_bounds__(256) void k_cert_compress(CertArgs a, int sweep) {
     const int32_t n = a.g.n;
     const int i = blockIdx.y;
+    if (sweep > 0 && a.more[i] != sweep) return;
     int32_t* par = a.own + (int64_t)i * n;
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
         if (inactive(a, v) || i >= a.count[a.vinst ? a.vinst[v] : 0]) continue;
-        int32_t x = (int32_t)v, p = ld_acq(&par[x]);
-        while (p != x) { x = p; p = ld_acq(&par[x]); }
-        st_rel(&par[v], x);
+        const int32_t first = ld_old(&par[v]);
+        int32_t x = first, p = ld_old(&par[x]);
+        while (p != x) { x = p; p = ld_old(&par[x]); }
+        if (x != first) st_new(&par[v], x);
     }
 }
 
 // The second round's units join the trees of the first: in a sweep a root
 // hangs under a heavier root next to one of its tree's vertices (the order of
 // the first round, so whichever of the racing stores stays, no cycle
-// arises), with a compression after it. Two sweeps leave few trees, and only
-// then does the linking use compare-and-swap (LINK): with it alone every
-// thread of a tree meets at the words of a few roots (8.7 ms at 300,000
-// vertices, k = 32; sweeps, link and their compressions together 1.3 ms).
-template <bool LINK>
-__global__ __launch_bounds__(256) void k_cert_join_trees(CertArgs a) {
+// arises), with a compression after it. The first sweep looks at a quarter of
+// the vertices, which a tree of a few dozen can spare; a sweep that finds two
+// trees side by side stamps the subgraph, and the next runs only there. What
+// CERT_SWEEPS sweeps leave apart stays apart (any subgraph will do). No
+// compare-and-swap: linking by union-find, every thread of a tree meets at the
+// words of a few roots (300,000 vertices, k = 32: 8.7 ms; sweeps and
+// compressions 0.42 ms at k = 16).
+__global__ __launch_bounds__(256) void k_cert_sweep(CertArgs a, int sweep) {
     const int32_t n = a.g.n;
     const int i = blockIdx.y;
+    if (sweep > 1 && a.more[i] != sweep - 1) return;
     int32_t* par = a.own + (int64_t)i * n;
     const int32_t* next = a.own + (int64_t)(a.kc + i) * n;
-    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
+    bool apart = false;
+    // of the quarter, wavefronts of 64 consecutive vertices, others in each subgraph
+    const int64_t step = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;; t += step) {
+        const int64_t v = sweep == 1 ? ((t / MC_WAVE) * 4 + (i & 3)) * MC_WAVE + t % MC_WAVE : t;
+        if (v >= n) break;
         if (inactive(a, v) || i >= a.count[a.vinst ? a.vinst[v] : 0]) continue;
         const int32_t u = next[v];
         if (u < 0) continue;
-        // a parent read during a sweep may be a root that has been hung
-        // already, or its new root: an ancestor either way
-        int32_t x = ld_acq(&par[v]), y = ld_acq(&par[u]);
-        while (x != y) {
-            if (LINK) {
-                for (int32_t p = ld_acq(&par[x]); p != x; p = ld_acq(&par[x])) x = p;
-                for (int32_t p = ld_acq(&par[y]); p != y; p = ld_acq(&par[y])) y = p;
-                if (x == y) break;
-            }
-            const int lx = a.level[x], ly = a.level[y];
-            const bool up = lx > ly || (lx == ly && x > y);   // x is the heavier
-            const int32_t from = up ? y : x, to = up ? x : y;
-            if (LINK) {
-                if (atomicCAS(&par[from], from, to) == from) break;
-            } else {
-                if (ld_acq(&par[from]) == from) st_rel(&par[from], to);
-                break;
-            }
-        }
+        const int32_t x = ld_old(&par[v]), y = ld_old(&par[u]);
+        if (x == y) continue;
+        apart = true;
+        const int hx = a.level[x], hy = a.level[y];
+        const bool up = hx > hy || (hx == hy && x > y);   // x is the heavier
+        const int32_t from = up ? y : x, to = up ? x : y;
+        if (ld_old(&par[from]) == from) st_new(&par[from], to);
     }
+    if (apart && a.more[i] != sweep) a.more[i] = sweep;
 }
 
 // Whether the test can join much: subgraph 0, built first, is as sparse as
@@ -243,7 +285,9 @@ __global__ __launch_bounds__(64) void k_cert_probe(CertArgs a) {
 }
 
 // the reference vertex of every graph: of 64 samples the one that shares its
-// class (a hash of its components) with most of them, one wavefront a graph
+// class (a hash of its components) with most of them, one wavefront a graph.
+// Where three quarters of them share it, the others are single weak vertices
+// rather than classes of their own, and are not looked at again (near = 0).
 __global__ __launch_bounds__(64) void k_cert_ref(CertArgs a) {
     const int lane = lane_id();
     for (int32_t gi = blockIdx.x; gi < a.ngraphs; gi += gridDim.x) {
@@ -260,7 +304,10 @@ __global__ __launch_bounds__(64) void k_cert_ref(CertArgs a) {
         for (int q = 0; q < MC_WAVE; q++) same += __shfl(h, q, MC_WAVE) == h;
         int32_t id = lane, aux = v;
         wave_argmax(same, id, aux);
-        if (lane == 0) a.ref[gi] = aux;
+        if (lane == 0) {
+            a.ref[gi] = aux;
+            a.near[gi] = same * 4 < 3 * MC_WAVE;
+        }
     }
 }
 
@@ -292,41 +339,72 @@ __global__ __launch_bounds__(256) void k_cert_member(CertArgs a) {
     }
 }
 
-// Members join the class's smallest vertex, each from its own root, so the
-// unions do not meet at one word; the others look among their first entries.
-// The workgroup counts its unions and adds them once.
-__global__ __launch_bounds__(256) void k_cert_join(CertArgs a) {
+// the workgroup's unions, added to the count once
+__device__ void add_marks(int32_t joined, unsigned long long* marks) {
     __shared__ int32_t sum[256 / MC_WAVE];
-    const int32_t n = a.g.n;
-    int32_t joined = 0;
-    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t inst = a.vinst ? a.vinst[v] : 0;
-        if (a.active && !a.active[inst]) continue;
-        if (a.member[v]) {
-            if (uf_union(a.parent, (int32_t)v, a.rep[inst])) joined++;
-            continue;
-        }
-        const int32_t k = a.count[inst];
-        if (k == 0) continue;
-        const int32_t o = a.g.off[v], l = a.g.len[v] < CERT_NEAR ? a.g.len[v] : CERT_NEAR;
-        for (int32_t j = 0; j < l; j++) {
-            const int32_t u = a.g.col[o + j];
-            if (a.member[u]) continue;
-            int i = 0;
-            while (i < k && a.own[(int64_t)i * n + v] == a.own[(int64_t)i * n + u]) i++;
-            if (i < k) continue;
-            if (uf_union(a.parent, (int32_t)v, u)) joined++;
-            break;
-        }
-    }
     joined = wave_sum_i32(joined);
     if (lane_id() == 0) sum[threadIdx.x / MC_WAVE] = joined;
     __syncthreads();
     if (threadIdx.x == 0) {
         int32_t t = 0;
         for (int q = 0; q < 256 / MC_WAVE; q++) t += sum[q];
-        if (t) atomicAdd(a.marks, (unsigned long long)t);
+        if (t) atomicAdd(marks, (unsigned long long)t);
     }
+}
+
+// Members join the class's smallest vertex. A member that is a root is hung
+// under it by a plain store: its only other writers are unions of its own
+// descendants with that same vertex, which hang it under that vertex's root,
+// an ancestor of what the store writes, and never hang that root under it
+// (roots are the smallest of their trees, so that root is smaller). 1.6
+// million members: 22 us, by compare-and-swap about 100 us.
+__global__ __launch_bounds__(256) void k_cert_join(CertArgs a) {
+    const int32_t n = a.g.n;
+    int32_t joined = 0;
+    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
+        const int32_t inst = a.vinst ? a.vinst[v] : 0;
+        if ((a.active && !a.active[inst]) || !a.member[v]) continue;
+        const int32_t rep = a.rep[inst];
+        if (v == rep) continue;
+        if (ld_acq(&a.parent[v]) == (int32_t)v) {
+            st_rel(&a.parent[v], rep);
+            joined++;
+        } else if (uf_union(a.parent, (int32_t)v, rep)) {
+            joined++;
+        }
+    }
+    add_marks(joined, a.marks);
+}
+
+// the others look for their class among their first entries (a launch of its
+// own: their unions may move any root)
+__global__ __launch_bounds__(256) void k_cert_near(CertArgs a) {
+    const int32_t n = a.g.n;
+    int32_t joined = 0;
+    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
+        const int32_t inst = a.vinst ? a.vinst[v] : 0;
+        if ((a.active && !a.active[inst]) || a.member[v]) continue;
+        const int32_t k = a.count[inst];
+        if (k == 0 || !a.near[inst]) continue;
+        // targets, memberships and first components of all of them in flight
+        const int32_t o = a.g.off[v], l = a.g.len[v] < CERT_NEAR ? a.g.len[v] : CERT_NEAR, mine = a.own[v];
+        int32_t u[CERT_NEAR], cu[CERT_NEAR];
+#pragma unroll
+        for (int j = 0; j < CERT_NEAR; j++) u[j] = j < l ? a.g.col[o + j] : -1;
+#pragma unroll
+        for (int j = 0; j < CERT_NEAR; j++) cu[j] = u[j] >= 0 && !a.member[u[j]] ? a.own[u[j]] : -1;
+        bool found = false;
+#pragma unroll
+        for (int j = 0; j < CERT_NEAR; j++) {
+            if (found || cu[j] != mine) continue;
+            int i = 1;
+            while (i < k && a.own[(int64_t)i * n + v] == a.own[(int64_t)i * n + u[j]]) i++;
+            if (i < k) continue;
+            found = true;
+            if (uf_union(a.parent, (int32_t)v, u[j])) joined++;
+        }
+    }
+    add_marks(joined, a.marks);
 }
 
 }  // namespace
@@ -335,7 +413,7 @@ __global__ __launch_bounds__(256) void k_cert_join(CertArgs a) {
 // that fit, at most CERT_KMAX. False when fewer than CERT_KMIN fit.
 bool cert_carve(CertArgs& a, void* base, size_t bytes) {
     const size_t n = (size_t)a.g.n, k = (size_t)a.ngraphs;
-    const size_t fixed = 2 * n + 20 * k + 10 * 256;   // the other arrays and their alignment
+    const size_t fixed = 2 * n + 24 * k + 13 * 256;   // the other arrays and their alignment
     if (bytes < fixed) return false;
     const size_t kc = (bytes - fixed) / (n * 2 * sizeof(int32_t));
     if (kc < (size_t)CERT_KMIN) return false;
@@ -348,6 +426,8 @@ bool cert_carve(CertArgs& a, void* base, size_t bytes) {
     a.count = m.take<int32_t>(k);
     a.ref = m.take<int32_t>(k);
     a.rep = m.take<int32_t>(k);
+    a.near = m.take<int32_t>(k);
+    a.more = m.take<int32_t>(CERT_KMAX);
     a.level = m.take<uint8_t>(n);
     a.member = m.take<uint8_t>(n);
     a.own = m.take<int32_t>(2 * (size_t)a.kc * n);
@@ -355,15 +435,16 @@ bool cert_carve(CertArgs& a, void* base, size_t bytes) {
 }
 
 // the first ny subgraphs: trees of the first round, joined by the second
-static void components(const CertArgs& a, int ny, hipStream_t s) {
-    const dim3 grid(grid_for(a.g.n, 256, 1024), ny);
-    k_cert_compress<<<grid, 256, 0, s>>>(a);
-    for (int sweep = 0; sweep < 2; sweep++) {
-        k_cert_join_trees<false><<<grid, 256, 0, s>>>(a);
-        k_cert_compress<<<grid, 256, 0, s>>>(a);
+static bool components(const CertArgs& a, int ny, hipStream_t s) {
+    const dim3 grid(grid_for(a.g.n, 256, 1024), ny), quarter(grid_for(a.g.n / 4 + 1, 256, 1024), ny);
+    if (!fill_i32(a.more, 0, a.kc, s)) return false;
+    k_cert_compress<<<grid, 256, 0, s>>>(a, 0);
+    for (int sweep = 1; sweep <= CERT_SWEEPS; sweep++) {
+        k_cert_sweep<<<sweep == 1 ? quarter : grid, 256, 0, s>>>(a, sweep);
+        k_cert_compress<<<grid, 256, 0, s>>>(a, sweep);
     }
-    k_cert_join_trees<true><<<grid, 256, 0, s>>>(a);
-    k_cert_compress<<<grid, 256, 0, s>>>(a);
+    MC_LAUNCHED("k_cert_sweep");
+    return true;
 }
 
 bool certify(const CertArgs& a, hipStream_t s) {
@@ -377,13 +458,14 @@ bool certify(const CertArgs& a, hipStream_t s) {
     // small graphs are bound by the launches: the probe's seven would cost
     // more than they can save
     if (n >= CERT_PROBE_N) {
-        components(a, 1, s);
+        if (!components(a, 1, s)) return false;
         k_cert_probe<<<gg, 64, 0, s>>>(a);
     }
-    components(a, a.kc, s);
+    if (!components(a, a.kc, s)) return false;
     k_cert_ref<<<gg, 64, 0, s>>>(a);
     k_cert_member<<<grid_for(n, 256), 256, 0, s>>>(a);
     k_cert_join<<<grid_for(n, 256, 1024), 256, 0, s>>>(a);
+    k_cert_near<<<grid_for(n, 256, 1024), 256, 0, s>>>(a);
     MC_LAUNCHED("certify");
     return true;
 }

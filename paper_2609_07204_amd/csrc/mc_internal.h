@@ -214,6 +214,8 @@ struct CertArgs {
     int32_t* count;          // [ngraphs] k <= kc
     int32_t* ref;            // [ngraphs] reference vertex
     int32_t* rep;            // [ngraphs] smallest vertex of the reference's class
+    int32_t* near;           // [ngraphs] other classes are looked for
+    int32_t* more;           // [kc] last sweep that found trees apart
     uint8_t* level;          // [n] degree class
     uint8_t* member;         // [n] in the reference's class
     int32_t* own;            // [2 kc][n] parents of the subgraphs, then the second round's targets
