@@ -55,6 +55,11 @@ __device__ __forceinline__ void l1_max(int64_t* lg, long long* ls, int32_t b, in
     else atomicMax((long long*)&lg[b], (long long)v);
 }
 
+constexpr int LDS_PT = 1024;
+constexpr int LDS_N = 8192;
+constexpr int64_t LDS_LAM = (int64_t)1 << 49;   // keys are packed above 13 bits of vertex
+__device__ __forceinline__ bool lds_pass(int32_t n, int64_t lam) { return n <= LDS_N && lam < LDS_LAM; }
+
 template <int PT>
 struct PassLds {
     static constexpr int PW = PT / MC_WAVE;
@@ -182,6 +187,7 @@ __global__ __launch_bounds__(PT) void k_capforest_private(PrivateArgs a) {
             }
             return;
         }
+        if (a.lds && lds_pass(n, a.plam[p])) return;   // k_capforest_lds runs it
         st = a.st;
         r = a.r;
         fifo = a.fifo + base;
@@ -191,6 +197,7 @@ __global__ __launch_bounds__(PT) void k_capforest_private(PrivateArgs a) {
         dlist = a.dlist + (base >> 6) + p;
         dbits = a.dbits + (base >> 11) + 2 * p;
     } else {
+        if (a.lds && lds_pass(n, *a.lam)) return;
         st = a.st + (int64_t)p * a.stride;
         r = a.r + (int64_t)p * a.stride;
         fifo = a.fifo + (int64_t)p * a.stride;
@@ -488,6 +495,143 @@ __global__ __launch_bounds__(PT) void k_capforest_private(PrivateArgs a) {
     }
 }
 
+// The same pass on a graph of at most LDS_N vertices, with r in LDS (-1: scanned,
+// -2: in the step's batch, 0: not reached). It needs no index over the queue:
+// each step reads all keys (8 a thread at most), reduces them by DPP moves and
+// takes every capped vertex, or else the one of the largest key. What is left
+// of a step's chain is three barriers and the round trip to the popped rows,
+// 1 to 2 us, where a single pop of the pass above is a chain of a dozen round
+// trips to HBM and barriers (5 to 7 us): a batch of 384 graphs whose last four
+// have 1,098 to 3,074 vertices, 3.5 ms a launch, 7.6 before.
+__global__ __launch_bounds__(LDS_PT) void k_capforest_lds(PrivateArgs a) {
+    extern __shared__ long long dyn[];
+    __shared__ uint64_t red[LDS_PT / MC_WAVE];
+    __shared__ int64_t sum[3];
+    __shared__ int32_t cnt[3];
+    const int tid = threadIdx.x, lane = lane_id(), wid = tid / MC_WAVE;
+    const int p = blockIdx.x;
+    int32_t base = 0, n = a.g.n;
+    int32_t* order = a.order + (int64_t)p * a.stride;
+    int64_t lam = a.plam ? a.plam[p] : *a.lam;
+    if (a.pvoff) {
+        base = a.pvoff[p];
+        n = a.pvoff[p + 1] - base;
+        order = a.order + base;
+        if (n < 3 || (a.prun && !a.prun[p])) return;       // answered by k_capforest_private
+    }
+    if (!lds_pass(n, lam)) return;
+    int64_t* const r = (int64_t*)dyn;          // [n]
+    int16_t* const list = (int16_t*)(r + n);   // [n] the step's vertices
+    for (int32_t v = tid; v < n; v += LDS_PT) r[v] = 0;
+    if (tid < 3) { sum[tid] = 0; cnt[tid] = 0; }
+    int32_t first = a.start >= 0 ? a.start - base : 0;
+    if (a.start < 0) {
+        const uint64_t h = splitmix64(a.seed ^ splitmix64(((uint64_t)(uint32_t)a.round << 32) | (uint32_t)p));
+        first = (int32_t)(((h >> 32) * (uint64_t)n) >> 32);
+    }
+    __syncthreads();
+    int64_t alpha = 0, best_alpha = INT64_MAX;
+    int32_t best_len = 0, nscan = 0, steps = 0;
+    int64_t marks = 0;
+    for (int s = 0;; s = s == 2 ? 0 : s + 1, steps++) {
+        const int32_t budget = a.len_cap > 0 ? a.len_cap - nscan : n;
+        if (budget <= 0) break;
+        // ---- the largest key
+        uint64_t key = 0;
+        for (int32_t v = tid; v < n; v += LDS_PT) {
+            const int64_t rv = r[v];
+            const uint64_t kv = rv > 0 ? ((uint64_t)(rv < lam ? rv : lam) << 13) + (uint64_t)(LDS_N - 1 - v) : 0;
+            key = kv > key ? kv : key;
+        }
+        key = wave_max_u64(key);
+        if (lane == 0) red[wid] = key;
+        __syncthreads();
+        key = wave_max_u64(lane < LDS_PT / MC_WAVE ? red[lane] : 0);
+        if (key == 0 && steps > 0) break;                      // queue empty
+        const bool batch = steps > 0 && (int64_t)(key >> 13) >= lam;
+        const int32_t x1 = steps > 0 ? LDS_N - 1 - (int32_t)(key & (LDS_N - 1)) : first;
+        // ---- the step's vertices (of a batch as many as the budget allows:
+        // any order among them is a valid one)
+        if (batch) {
+            int64_t part = 0;
+            for (int32_t v0 = 0; v0 < n; v0 += LDS_PT) {
+                const int32_t v = v0 + tid;
+                const int64_t rv = v < n ? r[v] : 0;
+                const unsigned long long m = __ballot(rv >= lam);
+                if (!m) continue;
+                int32_t at = 0;
+                if (lane == 0) at = atomicAdd(&cnt[s], (int32_t)__popcll(m));
+                at = __builtin_amdgcn_readfirstlane(at) + __popcll(m & ((1ULL << lane) - 1));
+                if (rv >= lam && at < budget) {
+                    list[at] = (int16_t)v;
+                    order[nscan + at] = base + v;
+                    part += a.g.deg[base + v] - 2 * rv;
+                    r[v] = -2;
+                }
+            }
+            part = wave_sum_i64(part);
+            if (lane == 0 && part) atomicAdd((unsigned long long*)&sum[s], (unsigned long long)part);
+        } else if (tid == 0) {
+            cnt[s] = 1;
+            list[0] = (int16_t)x1;
+            order[nscan] = base + x1;
+            sum[s] = a.g.deg[base + x1] - 2 * r[x1];
+            r[x1] = -2;
+        }
+        if (tid == 0) { const int z = s == 2 ? 0 : s + 1; sum[z] = 0; cnt[z] = 0; }
+        __syncthreads();
+        const int32_t b = cnt[s] < budget ? cnt[s] : budget;
+        // ---- their rows: one by all threads, or a row a wavefront
+        int64_t inside = 0;
+        auto entry = [&](int32_t x, int32_t j) {
+            const int32_t y = a.g.col[j] - base;
+            const int64_t c = a.g.w[j];
+            const int64_t ry = r[y];
+            if (ry < 0) {
+                if (ry == -2) inside += c;
+                return;
+            }
+            const int64_t old = (int64_t)atomicAdd((unsigned long long*)&r[y], (unsigned long long)c);
+            if (old < lam && lam <= old + c && uf_union(a.parent, base + x, base + y)) marks++;
+        };
+        if (b == 1) {
+            const int32_t x = list[0];
+            const int32_t o = a.g.off[base + x], l = a.g.len[base + x];
+            for (int32_t j = tid; j < l; j += LDS_PT) entry(x, o + j);
+        } else {
+            for (int32_t q = wid; q < b; q += LDS_PT / MC_WAVE) {
+                const int32_t x = list[q];
+                const int32_t o = a.g.off[base + x], l = a.g.len[base + x];
+                for (int32_t j = lane; j < l; j += MC_WAVE) entry(x, o + j);
+            }
+        }
+        if (inside) atomicAdd((unsigned long long*)&sum[s], (unsigned long long)-inside);
+        __syncthreads();
+        for (int32_t q = tid; q < b; q += LDS_PT) r[list[q]] = -1;
+        alpha += sum[s];
+        nscan += b;
+        if (nscan < n) {
+            if (alpha < best_alpha) { best_alpha = alpha; best_len = nscan; }
+            if (alpha < lam) lam = alpha;
+        }
+        __syncthreads();   // the next step's keys see the scanned vertices
+    }
+    marks = wave_sum_i64(marks);
+    if (tid == 0) sum[0] = 0;
+    __syncthreads();
+    if (lane == 0 && marks) atomicAdd((unsigned long long*)&sum[0], (unsigned long long)marks);
+    __syncthreads();
+    if (tid == 0) {
+        if (sum[0]) atomicAdd(a.marks, (unsigned long long)sum[0]);
+        if (a.pmarks) a.pmarks[p] = (unsigned long long)sum[0];
+        a.nscan[p] = nscan;
+        a.alpha[p] = best_alpha;
+        a.alpha_len[p] = best_len;
+        a.lam_out[p] = lam;
+        if (a.steps) a.steps[p] = steps;
+    }
+}
+
 __global__ void k_private_reset(int32_t* st, int64_t* r, int64_t count) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += (int64_t)gridDim.x * blockDim.x) {
         st[i] = 0;
@@ -512,6 +656,18 @@ static bool launch_private(const PrivateArgs& a, int32_t threads, size_t lds, hi
     return true;
 }
 
+// passes of at most n vertices with their state in LDS (the others return)
+static bool launch_lds(const PrivateArgs& a, int32_t n, hipStream_t s) {
+    const size_t lds = (size_t)n * (sizeof(long long) + sizeof(int16_t)) + 16;
+    if (lds > (64 << 10) && !mc_hip_ok(hipFuncSetAttribute((const void*)k_capforest_lds,
+                                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds),
+                                       "k_capforest_lds: LDS size"))
+        return false;
+    k_capforest_lds<<<a.passes, LDS_PT, lds, s>>>(a);
+    MC_LAUNCHED("k_capforest_lds");
+    return true;
+}
+
 bool capforest_private(const PrivateArgs& a, hipStream_t s, int32_t max_pass_n) {
     if (a.passes <= 0) return true;
     if (a.pvoff) {
@@ -525,7 +681,8 @@ bool capforest_private(const PrivateArgs& a, hipStream_t s, int32_t max_pass_n) 
         PrivateArgs b = a;
         b.l1_at = nb1 <= L1_LDS ? (nb2 > 0 ? nb2 : 1) : 0;
         const size_t lds = (size_t)((nb2 > 0 ? nb2 : 1) + (b.l1_at ? nb1 : 0)) * sizeof(long long);
-        return launch_private(b, a.threads > 0 ? a.threads : PT_INST, lds, s);
+        return launch_private(b, a.threads > 0 ? a.threads : PT_INST, lds, s) &&
+               (!a.lds || launch_lds(a, max_pass_n < LDS_N ? max_pass_n : LDS_N, s));
     }
     if (a.g.n > a.stride) {
         mc_hip_ok(hipErrorInvalidValue, "capforest_private: per-pass stride smaller than n");
@@ -539,7 +696,8 @@ bool capforest_private(const PrivateArgs& a, hipStream_t s, int32_t max_pass_n) 
     const int32_t nb1 = (a.g.n + 63) / 64;
     PrivateArgs b = a;
     b.l1_at = nb1 <= L1_LDS ? nb2 : 0;
-    return launch_private(b, a.threads > 0 ? a.threads : PT_SOLVE, (size_t)(nb2 + (b.l1_at ? nb1 : 0)) * sizeof(long long), s);
+    return launch_private(b, a.threads > 0 ? a.threads : PT_SOLVE, (size_t)(nb2 + (b.l1_at ? nb1 : 0)) * sizeof(long long), s) &&
+           (!a.lds || a.g.n > LDS_N || launch_lds(a, a.g.n, s));
 }
 
 bool capforest_private_reset(const PrivateArgs& a, hipStream_t s) {

@@ -331,30 +331,6 @@ __device__ PassOut fin_pass(FinLds& S, int32_t n, const int32_t* __restrict__ co
 }
 
 // ------------------------------------------------------------ batch pass
-// the largest value of the wavefront, in every lane (DPP moves: a shuffle
-// through LDS costs a few hundred cycles per step pair)
-template <int CTRL, int ROWS>
-__device__ __forceinline__ uint64_t dpp_max_step(uint64_t v) {
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, ROWS, 0xf, false);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), CTRL, ROWS, 0xf, false);
-    const uint64_t u = ((uint64_t)hi << 32) | lo;
-    return u > v ? u : v;
-}
-__device__ __forceinline__ uint64_t read_lane_u64(uint64_t v, int lane) {
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, lane);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), lane);
-    return ((uint64_t)hi << 32) | lo;
-}
-__device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) {
-    v = dpp_max_step<0x111, 0xf>(v);   // row_shr:1, 2, 4, 8: lane 15 of each row holds its row's
-    v = dpp_max_step<0x112, 0xf>(v);
-    v = dpp_max_step<0x114, 0xf>(v);
-    v = dpp_max_step<0x118, 0xf>(v);
-    v = dpp_max_step<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
-    v = dpp_max_step<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
-    return read_lane_u64(v, 63);
-}
-
 // One complete CAPFOREST pass by the whole workgroup, a thread per vertex.
 // Each step takes every queued vertex whose key has reached lam at once (they
 // tie at the largest key, so any order among them is one of the queue's;

@@ -681,7 +681,7 @@ constexpr int32_t TRI_NONE = INT32_MAX;
 
 __global__ __launch_bounds__(TRI_T) void k_pr34(DGraph g, const int64_t* lamp, const int32_t* vinst, int32_t D,
                                                int32_t* par, unsigned long long* marks, int32_t* part3,
-                                               uint8_t* flag4) {
+                                               uint8_t* flag4, const uint8_t* active) {
     __shared__ int32_t hk[TRI_T / TRI_SUB][TRI_SLOTS];
     __shared__ int64_t hv[TRI_T / TRI_SUB][TRI_SLOTS];
     const int64_t lam0 = *lamp;
@@ -695,7 +695,7 @@ __global__ __launch_bounds__(TRI_T) void k_pr34(DGraph g, const int64_t* lamp, c
     const int64_t top = ((int64_t)g.n + ngrp - 1) / ngrp * ngrp;
     for (int64_t v0 = (int64_t)blockIdx.x * (TRI_T / TRI_SUB) + grp; v0 < top; v0 += ngrp) {
         const int32_t v = (int32_t)v0;
-        const bool live = v0 < g.n && g.len[v] <= D && g.len[v] > 0;
+        const bool live = v0 < g.n && g.len[v] <= D && g.len[v] > 0 && (!active || active[vinst[v]]);
         const int32_t o = live ? g.off[v] : 0, l = live ? g.len[v] : 0;
         for (int k = sl; k < TRI_SLOTS; k += TRI_SUB) K[k] = -1;
         wave_sync();
@@ -1073,7 +1073,8 @@ bool pr12(const DGraph& g, const int64_t* lam, int32_t* parent, unsigned long lo
 }
 
 bool pr34(const DGraph& g, const int64_t* lam, int32_t D, int32_t* parent, unsigned long long* marks,
-          const int32_t* ptr2, Pr34WS& w, uint8_t* flag4, int32_t* acc3, hipStream_t s, const int32_t* vinst) {
+          const int32_t* ptr2, Pr34WS& w, uint8_t* flag4, int32_t* acc3, hipStream_t s, const int32_t* vinst,
+          const uint8_t* active) {
     if (D > TRI_MAXD) D = TRI_MAXD;
     if (!fill_i64((int64_t*)w.spread, 0, (int64_t)SPREAD * SPREAD_STRIDE, s) || !fill_i32(w.part3, TRI_NONE, g.n, s) ||
         !fill_u8(w.touch, 0, g.n, s))
@@ -1081,7 +1082,8 @@ bool pr34(const DGraph& g, const int64_t* lam, int32_t D, int32_t* parent, unsig
     if (flag4 && !fill_u8(flag4, 0, g.cap, s)) return false;
     k_pr2_touch<<<grid_for(g.n, 256), 256, 0, s>>>(ptr2, g.n, w.touch);
     MC_LAUNCHED("k_pr2_touch");
-    k_pr34<<<grid_for((int64_t)g.n * TRI_SUB, TRI_T), TRI_T, 0, s>>>(g, lam, vinst, D, parent, w.spread, w.part3, flag4);
+    k_pr34<<<grid_for((int64_t)g.n * TRI_SUB, TRI_T), TRI_T, 0, s>>>(g, lam, vinst, D, parent, w.spread, w.part3, flag4,
+                                                                            active);
     MC_LAUNCHED("k_pr34");
     k_pr3_accept<<<grid_for(g.n, 256), 256, 0, s>>>(w.part3, w.touch, g.n, parent, w.spread, acc3);
     MC_LAUNCHED("k_pr3_accept");

@@ -228,6 +228,7 @@ bool certify(const CertArgs& a, hipStream_t s);
 // D (<= 64) entries; test-4 edges and the accepted test-3 matching (mutual
 // smallest partners touching no test-2 pointer of ptr2) are unioned into
 // parent. Optional parity outputs: flag4[entry], acc3[vertex] (-1: none).
+// With active, only graphs i with active[i] take part (vinst).
 struct Pr34WS {
     int32_t* part3;   // [n] smallest test-3 partner
     uint8_t* touch;   // [n] test-2 pointer endpoints
@@ -237,7 +238,7 @@ struct Pr34WS {
 void pr34_ws_carve(Arena& a, int32_t n, Pr34WS& w);
 bool pr34(const DGraph& g, const int64_t* lam, int32_t D, int32_t* parent, unsigned long long* marks,
           const int32_t* ptr2, Pr34WS& w, uint8_t* flag4, int32_t* acc3, hipStream_t s,
-          const int32_t* vinst = nullptr);
+          const int32_t* vinst = nullptr, const uint8_t* active = nullptr);
 
 // ---------------------------------------------------- label propagation
 // Scratch of lp_round besides the contraction scratch it borrows (row
@@ -362,6 +363,7 @@ struct PrivateArgs {
     const int64_t* plam = nullptr;
     const uint8_t* prun = nullptr;
     unsigned long long* pmarks = nullptr;
+    bool lds = false;       // passes of small graphs keep their state in LDS (st, r and the lists but order unused)
     int32_t threads = 0;    // workgroup size of a pass (64..1024; 0 = 256 in instance mode, else 1024)
     // set by capforest_private: the level-1 index lives in LDS after the
     // l1_at level-2 entries (0: in HBM at l1)

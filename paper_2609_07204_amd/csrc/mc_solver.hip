@@ -587,11 +587,13 @@ struct Solver {
     // tests 1 and 2, then tests 3 and 4 while they keep finding at least
     // one contraction per 100 vertices (as repeated linear sweeps stop once
     // they stop shrinking the graph, App. A).
-    bool reduction_tests(const DGraph& g) {
-        const bool tri = tri_on && c->opt.pr_tri_deg_cap > 0;
-        if (!pr12(g, &w.sc->lam, w.parent, &w.sc->marks_pr, nullptr, tri ? w.tw.ptr2 : nullptr, w.prw, s))
-            return false;
-        if (!tri) return true;
+    bool tri() const { return tri_on && c->opt.pr_tri_deg_cap > 0; }
+    bool tests12(const DGraph& g) {
+        return pr12(g, &w.sc->lam, w.parent, &w.sc->marks_pr, nullptr, tri() ? w.tw.ptr2 : nullptr, w.prw, s);
+    }
+    bool reduction_tests(const DGraph& g) { return tests12(g) && tests34(g); }
+    bool tests34(const DGraph& g) {
+        if (!tri()) return true;
         if (!pr34(g, &w.sc->lam, c->opt.pr_tri_deg_cap, w.parent, &w.sc->marks_tri, w.tw.ptr2, w.tw, nullptr,
                   nullptr, s))
             return false;
@@ -801,6 +803,7 @@ static bool private_passes(Solver& S, const DGraph& g, int32_t round, int32_t pa
     pa.start = -1;
     pa.marks = &w.sc->marks_cf;
     pa.steps = w.psteps;
+    pa.lds = true;
     // A complete pass (len_cap 0, the fallback of Algorithm 2) of a graph
     // whose truncated passes were mostly single pops (many whole-GPU steps
     // of fewer than 8 vertices on average: heavy weights, a bound far above
@@ -974,7 +977,9 @@ static mc_status exact_rounds(Solver& S, int src) {
         prof_round_begin(S.in_heuristic ? 2 : 0, n, S.cur_m, s);
         k_reset_round<<<1, 1, 0, s>>>(w.sc);
         if (!uf_init(w.parent, n, s)) return MC_E_DEVICE;
-        if (!S.reduction_tests(*cur)) return MC_E_DEVICE;
+        // in the automatic mode tests 3 and 4 wait until a pass of CAPFOREST
+        // is to be saved
+        if (!S.tests12(*cur) || (!S.automatic && !S.tests34(*cur))) return MC_E_DEVICE;
         const bool det = S.c->opt.deterministic != 0;
         // when the reduction tests alone at least halve the graph, contract
         // now and leave CAPFOREST to the smaller graph of the next round
@@ -1029,7 +1034,12 @@ static mc_status exact_rounds(Solver& S, int src) {
                 note_bound = true;
             }
         }
-        S.tri_account(n);
+        if (!skip_cf && S.automatic && S.tri()) {
+            if (!S.tests34(*cur) || !S.readback()) return MC_E_DEVICE;
+            skip_cf = 2 * (int64_t)(S.c->hsc->marks_pr + S.c->hsc->marks_tri + S.c->hsc->marks_cert) >= n;
+            S.tri_account(n);
+        }
+        if (!S.automatic) S.tri_account(n);
         int used = CF_RUN_NONE;   // the CAPFOREST form whose results the round keeps last
         if (skip_cf) {
             S.stats.rounds_pr_only++;
