@@ -366,7 +366,7 @@ enum {
                                   513..2048 entries */
     MC_K_PR1_FIRST = 10,       /* k_pr1_first: link rounds of every row's first and second test-1
                                   entries */
-    MC_K_PR1_REST = 11,        /* k_pr1_trees (at most 255 trees) or k_pr1_rest: linking of the
+    MC_K_PR1_REST = 11,        /* k_pr1_rest: linking of the
                                   trees those rounds leave */
     MC_K_COUNT = 12
 };

@@ -346,22 +346,6 @@ __global__ void k_bg_bound(const int32_t* voff2, const int64_t* dmin, int32_t k,
 }
 
 // ----------------------------------------------------------- the engine
-// Labels of a round with dropped graphs: roots of live graphs are numbered
-// in vertex order; every vertex of a graph marked dead gets -1, so the
-// contraction removes it.
-__global__ void k_root_flag_live(const int32_t* par, const int32_t* vinst, const uint8_t* dead, int32_t n,
-                                 int32_t* flag) {
-    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x)
-        flag[v] = par[v] == v && !dead[vinst[v]];
-}
-
-__global__ void k_label_live(const int32_t* par, const int32_t* newid, const int32_t* vinst, const uint8_t* dead,
-                             int32_t n, int32_t* L, DevScalars* sc) {
-    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x)
-        L[v] = dead[vinst[v]] ? -1 : newid[par[v]];
-    if (blockIdx.x == 0 && threadIdx.x == 0) sc->n2 = newid[n];
-}
-
 // Append the staged (normal-form) graphs S behind the current graph: vertex
 // v of S becomes vbase + v, its row moves behind the current graph's last
 // window (ebase).
@@ -982,7 +966,7 @@ struct Engine {
         }
         EG_OK(uf_init(w.parent, n, s));
         // reduction tests with each graph's own bound
-        EG_OK(pr12(G, w.lam, w.parent, &w.sc->marks_pr, nullptr, tri_on ? w.tw.ptr2 : nullptr, w.prw, s, w.vinst));
+        EG_OK(pr12(G, w.lam, w.parent, &w.sc->marks_pr, nullptr, tri_on ? w.tw.ptr2 : nullptr, w.prw, s, w.vinst, cap.nmax));
         // tests 3 and 4 look at every pair of short rows: in the automatic mode
         // only on the graphs left for CAPFOREST (all of 384 graphs: 2.1 ms)
         const bool automatic = c->opt.capforest_mode == MC_CF_AUTO && !c->opt.deterministic;
@@ -1173,7 +1157,7 @@ struct Engine {
             char* const base = (char*)Gn.col;
             EG_OK(uf_init(par, nc, s));
             if (level > 0)
-                EG_OK(pr12(Gc, target, par, &w.sc->marks_cert, nullptr, nullptr, w.prw, s, vinst));
+                EG_OK(pr12(Gc, target, par, &w.sc->marks_cert, nullptr, nullptr, w.prw, s, vinst, cap.nmax));
             if (cert_carve(ca, base, (size_t)((char*)(Gn.w + Gn.cap) - base))) EG_OK(certify(ca, s));
             EG_OK(labels(par, left_out, nc, vinst));
             int32_t* const off2 = voff == w.voff2 ? w.h_off2 : w.voff2;
@@ -1203,15 +1187,11 @@ struct Engine {
         return MC_OK;
     }
 
-    // labels of the round: canonical components, -1 for dead graphs
+    // labels of the round: canonical components of the live graphs in vertex
+    // order, -1 for dead graphs, whose vertices the contraction removes
     bool labels(int32_t* parent, const uint8_t* dead) { return labels(parent, dead, n, w.vinst); }
     bool labels(int32_t* parent, const uint8_t* dead, int32_t nn, const int32_t* vinst) {
-        if (!uf_labels(parent, nn, w.L, w.flag, w.cw.scan_tmp, w.sc, s)) return false;   // compresses
-        k_root_flag_live<<<grid_for(nn, 256), 256, 0, s>>>(parent, vinst, dead, nn, w.flag);
-        if (!mc_hip_ok(hipGetLastError(), "k_root_flag_live")) return false;
-        if (!scan_i32(w.flag, w.flag, nn, w.cw.scan_tmp, s)) return false;
-        k_label_live<<<grid_for(nn, 256), 256, 0, s>>>(parent, w.flag, vinst, dead, nn, w.L, w.sc);
-        return mc_hip_ok(hipGetLastError(), "k_label_live");
+        return root_labels(parent, nn, vinst, dead, w.flag, w.L, w.cw.scan_tmp, w.sc, s);
     }
 
     // sides of graphs whose bound dropped to a pass's prefix this round

@@ -200,16 +200,6 @@ __global__ __launch_bounds__(256) void k_cert_rows(CertArgs a) {
     }
 }
 
-// Parents as the last launch left them, or newer: a load that the caches may
-// serve. Device-scope loads go past the L2 of the compute unit's die, which
-// made them the bound of these kernels. An old parent is an ancestor too.
-__device__ __forceinline__ int32_t ld_old(const int32_t* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-__device__ __forceinline__ void st_new(int32_t* p, int32_t v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
 // every vertex at its root, in every subgraph (blockIdx.y); after sweep
 // `sweep` only in those that it changed
 __global__ __launch_bounds__(256) void k_cert_compress(CertArgs a, int sweep) {

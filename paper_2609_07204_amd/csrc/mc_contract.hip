@@ -109,19 +109,17 @@ __global__ __launch_bounds__(GT_THREADS) void k_group_scatter(const int32_t* __r
     }
 }
 
-// row length of every member in perm order; positions past the kept
-// members (vertices dropped with label -1) get 0
-__global__ void k_member_len(const int32_t* __restrict__ len, const int32_t* __restrict__ perm, int32_t n,
-                             const int32_t* __restrict__ kept, int32_t* __restrict__ mlen) {
-    const int64_t nk = kept ? *kept : n;
-    for (int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; m < n; m += (int64_t)gridDim.x * blockDim.x)
-        mlen[m] = m < nk ? len[perm ? perm[m] : m] : 0;
-}
-
-__global__ void k_group_start(const int32_t* __restrict__ vstart, const int32_t* __restrict__ mstart, int32_t n2,
-                              int32_t* __restrict__ gstart) {
-    for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g <= n2; g += (int64_t)gridDim.x * blockDim.x)
-        gstart[g] = mstart[vstart[g]];
+// counters of a contraction, cleared: members per group and their cursors
+// (with labels), dense accumulators, mid groups
+__global__ void k_contract_clear(int32_t* gcnt, int32_t* gcur, int32_t n2, int32_t* dinfo, int32_t* mcnt) {
+    const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i0 == 0) dinfo[0] = 0;
+    if (i0 < 2) mcnt[i0] = 0;
+    if (!gcnt) return;
+    for (int64_t i = i0; i <= n2; i += (int64_t)gridDim.x * blockDim.x) {
+        gcnt[i] = 0;
+        if (i < n2) gcur[i] = 0;
+    }
 }
 
 // Split groups into the chunk path and the large-group path; every group
@@ -152,15 +150,22 @@ constexpr int MID_HALF = 1024;
 // mid-group workgroup stages all of them at once and takes the entries flat.
 constexpr int MERGE_MANY = 32;
 
-__global__ void k_classify(const int32_t* __restrict__ gstart, const int32_t* __restrict__ vstart, int32_t n2,
+// mstart: the entry prefix over the members; the groups' starts go to gstart
+// (without labels gstart is mstart itself).
+__global__ void k_classify(const int32_t* mstart, const int32_t* __restrict__ vstart, int32_t* gstart, int32_t n2,
                            int32_t nd_max, int32_t* __restrict__ tsize, int32_t* __restrict__ bigm,
                            int32_t* __restrict__ bcur, int32_t* __restrict__ dslot, int32_t* __restrict__ dinfo,
                            int32_t* __restrict__ mlist, int32_t* __restrict__ mcnt, int32_t* __restrict__ ssize,
                            DGraph dst) {
     const int64_t dense_min = n2 / 4;
     for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < n2; g += (int64_t)gridDim.x * blockDim.x) {
-        int32_t s = gstart[g + 1] - gstart[g];
-        dst.off[g] = gstart[g];
+        const int32_t gs = mstart[vstart ? vstart[g] : g], ge = mstart[vstart ? vstart[g + 1] : g + 1];
+        const int32_t s = ge - gs;
+        if (vstart) {
+            gstart[g] = gs;
+            if (g == n2 - 1) gstart[n2] = ge;
+        }
+        dst.off[g] = gs;
         dslot[g] = -1;
         const int32_t members = vstart ? vstart[g + 1] - vstart[g] : 1;
         const bool mid = members <= MID_MEM && (s > SMALL_MAX ? s <= MID_MAX : members > MERGE_MANY);
@@ -230,10 +235,9 @@ constexpr int NSUB = MERGE_THREADS / SUB;
 // sstart the prefix of the small groups' entry counts (larger groups count
 // as empty, so no chunk is spent on their entries); one independent search
 // per thread, so their latencies overlap
-__global__ void k_chunk_start(const int32_t* __restrict__ sstart, int32_t n2, int64_t nchunks,
-                              int32_t* __restrict__ cg) {
-    for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c <= nchunks; c += (int64_t)gridDim.x * blockDim.x)
-        cg[c] = first_key_ge(sstart, n2, c * CHUNK);
+__device__ __forceinline__ void chunk_start(const int32_t* __restrict__ sstart, int32_t n2, int64_t nchunks,
+                                            int32_t* __restrict__ cg, int64_t i0, int64_t step) {
+    for (int64_t c = i0; c <= nchunks; c += step) cg[c] = first_key_ge(sstart, n2, c * CHUNK);
 }
 
 // One member row u of group g (chunk-local gl) into the chunk's LDS table,
@@ -505,15 +509,6 @@ __global__ __launch_bounds__(MID_T) void k_mid_merge(DGraph src, const int32_t* 
     if (pb) prof_add(pb, bytes);
 }
 
-__global__ void k_big_clear(const int32_t* __restrict__ total_p, int32_t* __restrict__ tkey,
-                            int64_t* __restrict__ tval) {
-    const int64_t total = *total_p;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-        tkey[i] = -1;
-        tval[i] = 0;
-    }
-}
-
 // Large groups: their entries form one flattened space (bebase = prefix
 // of the entry counts of large groups). A workgroup takes a tile of
 // BIG_TILE entries, combines equal (group, target) pairs in an LDS hash, and
@@ -526,11 +521,11 @@ constexpr int BIG_WIN = 1024;            // members whose row offsets a segment 
 
 // group and first member of every tile's first entry, searched for all
 // tiles at once so the searches' latencies overlap
-__global__ void k_big_tiles(const int32_t* __restrict__ vstart, const int32_t* __restrict__ mstart,
-                            const int32_t* __restrict__ gstart, const int32_t* __restrict__ bebase, int32_t n2,
-                            int32_t* __restrict__ tinfo) {
+__device__ __forceinline__ void big_tiles(const int32_t* __restrict__ vstart, const int32_t* __restrict__ mstart,
+                                          const int32_t* __restrict__ gstart, const int32_t* __restrict__ bebase,
+                                          int32_t n2, int32_t* __restrict__ tinfo, int64_t i0, int64_t step) {
     const int64_t ntiles = ((int64_t)bebase[n2] + BIG_TILE - 1) / BIG_TILE;
-    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < ntiles; t += (int64_t)gridDim.x * blockDim.x) {
+    for (int64_t t = i0; t < ntiles; t += step) {
         const int64_t e = t * BIG_TILE;
         const int32_t g = last_le(bebase, n2, e);
         const int32_t m0 = vstart ? vstart[g] : g;
@@ -538,6 +533,34 @@ __global__ void k_big_tiles(const int32_t* __restrict__ vstart, const int32_t* _
         tinfo[2 * t] = g;
         tinfo[2 * t + 1] = m0 + last_le(mstart + m0, mc, gstart[g] + (int32_t)(e - bebase[g]));
     }
+}
+
+// What the merges start from, once the prefixes over the groups are known:
+// first groups of the chunks, first members of the large groups' tiles, groups
+// of the table tiles, and the tables and dense accumulators in use, zeroed.
+// Five independent loops of one launch: on small graphs each of them is a
+// launch's latency and little else (2,000 vertices: 1.5 to 4 us each).
+__global__ __launch_bounds__(256) void k_merge_plan(const int32_t* __restrict__ sstart, int64_t nchunks,
+                                                   int32_t* __restrict__ cg, const int32_t* __restrict__ vstart,
+                                                   const int32_t* __restrict__ mstart,
+                                                   const int32_t* __restrict__ gstart,
+                                                   const int32_t* __restrict__ bebase,
+                                                   const int32_t* __restrict__ tbase, int32_t n2,
+                                                   int32_t* __restrict__ tinfo, int32_t* __restrict__ xg,
+                                                   int32_t* __restrict__ tkey, int64_t* __restrict__ tval,
+                                                   const int32_t* __restrict__ dinfo, int32_t nd_max,
+                                                   int64_t* __restrict__ dense) {
+    const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+    chunk_start(sstart, n2, nchunks, cg, i0, step);
+    big_tiles(vstart, mstart, gstart, bebase, n2, tinfo, i0, step);
+    const int64_t slots = tbase[n2];
+    for (int64_t t = i0; t < slots / TILE_SLOTS; t += step) xg[t] = last_le(tbase, n2, t * TILE_SLOTS);
+    for (int64_t i = i0; i < slots; i += step) {
+        tkey[i] = -1;
+        tval[i] = 0;
+    }
+    const int64_t acc = (int64_t)(dinfo[0] < nd_max ? dinfo[0] : nd_max) * n2;
+    for (int64_t i = i0; i < acc; i += step) dense[i] = 0;
 }
 
 __global__ __launch_bounds__(BIG_T) void k_big_insert(DGraph src, const int32_t* __restrict__ L,
@@ -716,14 +739,6 @@ __global__ __launch_bounds__(BIG_T) void k_big_insert(DGraph src, const int32_t*
     if (pb) prof_add(pb, nin * (L ? 16 : 12));
 }
 
-// group of every 256-slot table tile (tables are whole tiles), searched for
-// all tiles at once so the searches' latencies overlap
-__global__ void k_big_xtiles(const int32_t* __restrict__ tbase, int32_t n2, int32_t* __restrict__ xg) {
-    const int64_t ntiles = tbase[n2] / TILE_SLOTS;
-    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < ntiles; t += (int64_t)gridDim.x * blockDim.x)
-        xg[t] = last_le(tbase, n2, t * TILE_SLOTS);
-}
-
 // One wavefront emits the valid slots of a unit of group g (PERL slots per
 // lane): a wave prefix sum places them, and one atomic per unit reserves
 // their room in the row (one more adds their weight to the degree). The
@@ -764,12 +779,12 @@ __device__ __forceinline__ void wave_emit(int32_t g, const bool (&take)[PERL], c
 constexpr int EX_T = 256;   // threads of the extraction kernels: four waves, one unit each
 static_assert(TILE_SLOTS == 4 * MC_WAVE, "a table tile is one wave's unit");
 
-__global__ __launch_bounds__(EX_T) void k_big_extract(const int32_t* __restrict__ tbase,
-                                                      const int32_t* __restrict__ gstart, int32_t n2,
-                                                      const int32_t* __restrict__ xg,
-                                                      const int32_t* __restrict__ tkey,
-                                                      const int64_t* __restrict__ tval,
-                                                      int32_t* __restrict__ bcur, DGraph dst) {
+// hash tables of the large groups (xg: group of every table tile; tables are
+// whole tiles)
+__device__ __forceinline__ void table_extract(const int32_t* __restrict__ tbase, const int32_t* __restrict__ gstart,
+                                              int32_t n2, const int32_t* __restrict__ xg,
+                                              const int32_t* __restrict__ tkey, const int64_t* __restrict__ tval,
+                                              int32_t* __restrict__ bcur, DGraph& dst) {
     const int64_t ntiles = tbase[n2] / TILE_SLOTS;
     const int64_t wid = (int64_t)blockIdx.x * (EX_T / MC_WAVE) + threadIdx.x / MC_WAVE;
     const int64_t nw = (int64_t)gridDim.x * (EX_T / MC_WAVE);
@@ -794,22 +809,12 @@ __global__ __launch_bounds__(EX_T) void k_big_extract(const int32_t* __restrict_
     }
 }
 
-// the dense accumulators the giant groups of this contraction use, zeroed
-// once their count is known (no earlier reset needed)
-__global__ void k_dense_clear(const int32_t* __restrict__ dinfo, int32_t nd_max, int32_t n2,
-                              int64_t* __restrict__ dense) {
-    const int32_t nd = dinfo[0] < nd_max ? dinfo[0] : nd_max;
-    const int64_t total = (int64_t)nd * n2;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x)
-        dense[i] = 0;
-}
-
 // dense accumulators of the giant groups: stream over n2 targets and emit
 // the non-zero ones
-__global__ __launch_bounds__(EX_T) void k_dense_extract(const int32_t* __restrict__ dinfo, int32_t nd_max,
-                                                        const int32_t* __restrict__ gstart, int32_t n2,
-                                                        const int64_t* __restrict__ dense, int32_t* __restrict__ bcur,
-                                                        DGraph dst) {
+__device__ __forceinline__ void dense_extract(const int32_t* __restrict__ dinfo, int32_t nd_max,
+                                              const int32_t* __restrict__ gstart, int32_t n2,
+                                              const int64_t* __restrict__ dense, int32_t* __restrict__ bcur,
+                                              DGraph& dst) {
     constexpr int PERL = 16;                       // a unit is 1024 targets
     constexpr int UNIT = PERL * MC_WAVE;
     const int32_t nd = dinfo[0] < nd_max ? dinfo[0] : nd_max;
@@ -837,64 +842,94 @@ __global__ __launch_bounds__(EX_T) void k_dense_extract(const int32_t* __restric
     }
 }
 
-__global__ void k_big_finalize(const int32_t* __restrict__ bebase, int32_t n2, const int32_t* __restrict__ bcur,
-                               DGraph dst) {
-    for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < n2; g += (int64_t)gridDim.x * blockDim.x)
-        if (bebase[g + 1] > bebase[g]) dst.len[g] = bcur[g];
+__global__ __launch_bounds__(EX_T) void k_big_extract(const int32_t* __restrict__ tbase,
+                                                      const int32_t* __restrict__ gstart, int32_t n2,
+                                                      const int32_t* __restrict__ xg,
+                                                      const int32_t* __restrict__ tkey,
+                                                      const int64_t* __restrict__ tval,
+                                                      const int32_t* __restrict__ dinfo, int32_t nd_max,
+                                                      const int64_t* __restrict__ dense,
+                                                      int32_t* __restrict__ bcur, DGraph dst) {
+    table_extract(tbase, gstart, n2, xg, tkey, tval, bcur, dst);
+    dense_extract(dinfo, nd_max, gstart, n2, dense, bcur, dst);
 }
 
-// minimum degree, ties to the smallest vertex, the entry count and the
-// maximum degree: per-block partials, then one block folds them
-__global__ __launch_bounds__(256) void k_min_deg_blocks(const int64_t* __restrict__ deg,
-                                                       const int32_t* __restrict__ len, int32_t n,
-                                                       int64_t* __restrict__ rv, int32_t* __restrict__ ri,
-                                                       int64_t* __restrict__ rm, int64_t* __restrict__ rd) {
-    __shared__ int64_t sv[4], sm[4], sd[4];
-    __shared__ int32_t si[4];
-    int64_t best = 0, m = 0, dmax = 0;
-    int32_t bid = -1;
-    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
-        int64_t d = deg[v];
-        m += len[v];
-        dmax = d > dmax ? d : dmax;
-        if (bid < 0 || d < best) { best = d; bid = (int32_t)v; }
-    }
-    wave_argmin(best, bid);
-    m = wave_sum_i64(m);
-    dmax = wave_max_i64(dmax);
-    if (lane_id() == 0) {
-        const int wv = threadIdx.x / MC_WAVE;
-        sv[wv] = best; si[wv] = bid; sm[wv] = m; sd[wv] = dmax;
-    }
+// Minimum degree, ties to the smallest vertex, the entry count, the longest
+// row and the maximum degree: per-block partials, then one block folds them;
+// of at most MIN_DEG_ONE vertices one block alone. With bebase the large
+// groups' row lengths are taken from their cursors first.
+struct MinDeg {
+    int64_t d, m, dmax;
+    int32_t id, row;
+};
+constexpr int MIN_DEG_T = 1024;
+constexpr int32_t MIN_DEG_ONE = 16 * MIN_DEG_T;
+__device__ __forceinline__ void min_deg_take(MinDeg& a, int64_t d, int32_t id, int64_t m, int64_t dmax, int32_t row) {
+    a.m += m;
+    a.dmax = dmax > a.dmax ? dmax : a.dmax;
+    a.row = row > a.row ? row : a.row;
+    if (id >= 0 && (a.id < 0 || d < a.d || (d == a.d && id < a.id))) { a.d = d; a.id = id; }
+}
+// the workgroup's fold, in thread 0
+__device__ __forceinline__ void min_deg_fold(MinDeg& a) {
+    __shared__ MinDeg part[MIN_DEG_T / MC_WAVE];
+    auto wave = [](MinDeg& x) {
+        for (int o = MC_WAVE / 2; o > 0; o >>= 1)
+            min_deg_take(x, __shfl_xor(x.d, o, MC_WAVE), __shfl_xor(x.id, o, MC_WAVE), __shfl_xor(x.m, o, MC_WAVE),
+                         __shfl_xor(x.dmax, o, MC_WAVE), __shfl_xor(x.row, o, MC_WAVE));
+    };
+    wave(a);
+    if (lane_id() == 0) part[threadIdx.x / MC_WAVE] = a;
     __syncthreads();
-    if (threadIdx.x < MC_WAVE) {
-        int64_t b = threadIdx.x < 4 ? sv[threadIdx.x] : 0;
-        int32_t i = threadIdx.x < 4 ? si[threadIdx.x] : -1;
-        wave_argmin(b, i);
-        if (threadIdx.x == 0) {
-            rv[blockIdx.x] = b; ri[blockIdx.x] = i;
-            rm[blockIdx.x] = sm[0] + sm[1] + sm[2] + sm[3];
-            const int64_t a = sd[0] > sd[1] ? sd[0] : sd[1], b = sd[2] > sd[3] ? sd[2] : sd[3];
-            rd[blockIdx.x] = a > b ? a : b;
-        }
+    if (threadIdx.x >= MC_WAVE) return;
+    a = {0, 0, 0, -1, 0};
+    if (threadIdx.x < blockDim.x / MC_WAVE) a = part[threadIdx.x];
+    wave(a);
+}
+__device__ __forceinline__ void min_deg_store(const MinDeg& a, DevScalars* sc) {
+    sc->dmin = a.d;
+    sc->dmin_arg = a.id;
+    sc->m2 = a.m;
+    sc->dmax = a.dmax;
+    sc->max_row = a.row;
+}
+
+__global__ __launch_bounds__(MIN_DEG_T) void k_min_deg_blocks(const int64_t* __restrict__ deg, int32_t* __restrict__ len,
+                                                             int32_t n, const int32_t* __restrict__ bebase,
+                                                             const int32_t* __restrict__ bcur,
+                                                             int64_t* __restrict__ rv, int32_t* __restrict__ ri,
+                                                             int64_t* __restrict__ rm, int64_t* __restrict__ rd,
+                                                             DevScalars* sc) {
+    MinDeg a{0, 0, 0, -1, 0};
+    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t d = deg[v];
+        int32_t l;
+        if (bebase && bebase[v + 1] > bebase[v]) len[v] = l = bcur[v];
+        else l = len[v];
+        min_deg_take(a, d, (int32_t)v, l, d, l);
+    }
+    min_deg_fold(a);
+    if (threadIdx.x != 0) return;
+    if (gridDim.x == 1) {
+        min_deg_store(a, sc);
+    } else {
+        rv[blockIdx.x] = a.d;
+        ri[blockIdx.x] = a.id;
+        rm[blockIdx.x] = (int64_t)a.row << 32 | a.m;   // fewer than 2^31 entries in all
+        rd[blockIdx.x] = a.dmax;
     }
 }
 
-__global__ __launch_bounds__(64) void k_min_deg_final(const int64_t* __restrict__ rv, const int32_t* __restrict__ ri,
-                                                     const int64_t* __restrict__ rm, const int64_t* __restrict__ rd,
-                                                     int nblocks, DevScalars* sc) {
-    int64_t best = 0, m = 0, dmax = 0;
-    int32_t bid = -1;
-    for (int i = threadIdx.x; i < nblocks; i += MC_WAVE) {
-        int32_t id = ri[i];
-        m += rm[i];
-        dmax = rd[i] > dmax ? rd[i] : dmax;
-        if (id >= 0 && (bid < 0 || rv[i] < best || (rv[i] == best && id < bid))) { best = rv[i]; bid = id; }
-    }
-    wave_argmin(best, bid);
-    m = wave_sum_i64(m);
-    dmax = wave_max_i64(dmax);
-    if (threadIdx.x == 0) { sc->dmin = best; sc->dmin_arg = bid; sc->m2 = m; sc->dmax = dmax; }
+__global__ __launch_bounds__(MIN_DEG_T) void k_min_deg_final(const int64_t* __restrict__ rv,
+                                                            const int32_t* __restrict__ ri,
+                                                            const int64_t* __restrict__ rm,
+                                                            const int64_t* __restrict__ rd, int nblocks,
+                                                            DevScalars* sc) {
+    MinDeg a{0, 0, 0, -1, 0};
+    for (int i = threadIdx.x; i < nblocks; i += MIN_DEG_T)
+        min_deg_take(a, rv[i], ri[i], rm[i] & 0xffffffff, rd[i], (int32_t)(rm[i] >> 32));
+    min_deg_fold(a);
+    if (threadIdx.x == 0) min_deg_store(a, sc);
 }
 
 inline int grid_for(int64_t count, int threads, int cap = 8192) {
@@ -944,13 +979,20 @@ void contract_ws_carve(Arena& a, int32_t n, int64_t cap, ContractWS& ws, bool so
 }
 
 
-bool min_degree(const DGraph& g, ContractWS& ws, DevScalars* sc, hipStream_t s) {
-    int nb = grid_for(g.n, 256, 1024);
-    k_min_deg_blocks<<<nb, 256, 0, s>>>(g.deg, g.len, g.n, ws.red_val, ws.red_id, ws.red_m, ws.red_d);
+static bool min_degree(const DGraph& g, const int32_t* bebase, const int32_t* bcur, ContractWS& ws, DevScalars* sc,
+                       hipStream_t s) {
+    const int nb = g.n <= MIN_DEG_ONE ? 1 : grid_for(g.n, 4 * 256, 1024);
+    k_min_deg_blocks<<<nb, nb == 1 ? MIN_DEG_T : 256, 0, s>>>(g.deg, g.len, g.n, bebase, bcur, ws.red_val, ws.red_id,
+                                                             ws.red_m, ws.red_d, sc);
     MC_LAUNCHED("k_min_deg_blocks");
-    k_min_deg_final<<<1, 64, 0, s>>>(ws.red_val, ws.red_id, ws.red_m, ws.red_d, nb, sc);
+    if (nb == 1) return true;
+    k_min_deg_final<<<1, MIN_DEG_T, 0, s>>>(ws.red_val, ws.red_id, ws.red_m, ws.red_d, nb, sc);
     MC_LAUNCHED("k_min_deg_final");
     return true;
+}
+
+bool min_degree(const DGraph& g, ContractWS& ws, DevScalars* sc, hipStream_t s) {
+    return min_degree(g, nullptr, nullptr, ws, sc, s);
 }
 
 bool contract(const DGraph& src, const int32_t* L, int32_t n2, DGraph& dst, ContractWS& ws, DevScalars* sc,
@@ -960,9 +1002,10 @@ bool contract(const DGraph& src, const int32_t* L, int32_t n2, DGraph& dst, Cont
     dst.n = n2;
     const int32_t* perm = nullptr;
     const int32_t* vstart = nullptr;
+    k_contract_clear<<<L ? grid_for((int64_t)n2 + 1, 256) : 1, 256, 0, s>>>(L ? ws.gcnt : nullptr, ws.gcur, n2, ws.dinfo,
+                                                                          ws.mcnt);
+    MC_LAUNCHED("k_contract_clear");
     if (L) {
-        if (!fill_i32(ws.gcnt, 0, (int64_t)n2 + 1, s)) return false;
-        if (!fill_i32(ws.gcur, 0, n2, s)) return false;
         const int gtiles = grid_for(n, GT, 4096);
         prof_begin(PK_GROUP_COUNT, s);
         k_group_count<<<gtiles, GT_THREADS, 0, s>>>(L, n, ws.gcnt);
@@ -978,33 +1021,24 @@ bool contract(const DGraph& src, const int32_t* L, int32_t n2, DGraph& dst, Cont
         perm = ws.perm;
         vstart = ws.vstart;
     }
-    k_member_len<<<grid_for(n, 256), 256, 0, s>>>(src.len, perm, n, vstart ? vstart + n2 : nullptr, ws.mstart);
-    MC_LAUNCHED("k_member_len");
-    if (!scan_i32(ws.mstart, ws.mstart, n, ws.scan_tmp, s)) return false;
-    const int32_t* gstart = ws.mstart;
-    if (L) {
-        k_group_start<<<grid_for((int64_t)n2 + 1, 256), 256, 0, s>>>(vstart, ws.mstart, n2, ws.gstart);
-        MC_LAUNCHED("k_group_start");
-        gstart = ws.gstart;
-    }
+    if (!scan_member_len(src.len, perm, vstart ? vstart + n2 : nullptr, ws.mstart, n, ws.scan_tmp, s)) return false;
+    int32_t* const gstart = L ? ws.gstart : ws.mstart;
     const int64_t ndm = ws.dense_elems / (n2 > 0 ? n2 : 1);
     const int32_t nd_max = (int32_t)(ndm < DENSE_MAX ? ndm : DENSE_MAX);
-    if (!fill_i32(ws.dinfo, 0, 1, s) || !fill_i32(ws.mcnt, 0, 2, s)) return false;
-    k_classify<<<grid_for(n2, 256), 256, 0, s>>>(gstart, vstart, n2, nd_max, ws.tsize, ws.bigm, ws.bcur, ws.dslot,
-                                                 ws.dinfo, ws.mlist, ws.mcnt, ws.sstart, dst);
+    k_classify<<<grid_for(n2, 256), 256, 0, s>>>(ws.mstart, vstart, gstart, n2, nd_max, ws.tsize, ws.bigm, ws.bcur,
+                                                 ws.dslot, ws.dinfo, ws.mlist, ws.mcnt, ws.sstart, dst);
     MC_LAUNCHED("k_classify");
-    if (nd_max > 0) {
-        k_dense_clear<<<grid_for((int64_t)nd_max * n2, 256, 4096), 256, 0, s>>>(ws.dinfo, nd_max, n2, ws.dense);
-        MC_LAUNCHED("k_dense_clear");
-    }
-    if (!scan_i32(ws.tsize, ws.tsize, n2, ws.scan_tmp, s)) return false;  // -> tbase
-    if (!scan_i32(ws.bigm, ws.bigm, n2, ws.scan_tmp, s)) return false;    // -> bebase
-    if (!scan_i32(ws.sstart, ws.sstart, n2, ws.scan_tmp, s)) return false;  // small-group entry prefix
+    // table bases, large-group entry prefix, small-group entry prefix; the
+    // groups' cursors are free again
+    if (!scan3_i32(ws.tsize, ws.bigm, ws.sstart, n2, ws.gcur, s)) return false;
     // at most this many chunks hold small groups; the rest of the grid finds
     // no group and returns
     const int64_t chunks = (src.cap + (int64_t)GROUP_W * n2) / CHUNK + 2;
-    k_chunk_start<<<grid_for(chunks + 1, 256), 256, 0, s>>>(ws.sstart, n2, chunks, ws.cg);
-    MC_LAUNCHED("k_chunk_start");
+    // a thread for every chunk and four table slots, and no more workgroups than that fills
+    k_merge_plan<<<grid_for(std::max(chunks + 1, src.cap / 2), 256, 4096), 256, 0, s>>>(
+        ws.sstart, chunks, ws.cg, vstart, ws.mstart, gstart, ws.bigm, ws.tsize, n2, ws.tinfo, ws.xg, ws.tkey, ws.tval,
+        ws.dinfo, nd_max, ws.dense);
+    MC_LAUNCHED("k_merge_plan");
     prof_begin(PK_MERGE_SMALL, s);
     k_merge_small<<<(unsigned)chunks, MERGE_THREADS, 0, s>>>(src, L, perm, vstart, gstart, n2, ws.cg, dst,
                                                              prof_dev_bytes(PK_MERGE_SMALL));
@@ -1018,24 +1052,13 @@ bool contract(const DGraph& src, const int32_t* L, int32_t n2, DGraph& dst, Cont
                                                        n2, dst, prof_dev_bytes(PK_MID_MERGE));
     MC_LAUNCHED("k_mid_merge");
     prof_end(PK_MID_MERGE, s);
-    k_big_clear<<<2048, 256, 0, s>>>(ws.tsize + n2, ws.tkey, ws.tval);
-    MC_LAUNCHED("k_big_clear");
-    k_big_tiles<<<grid_for(src.cap / BIG_TILE + 1, 256), 256, 0, s>>>(vstart, ws.mstart, gstart, ws.bigm, n2,
-                                                                      ws.tinfo);
-    MC_LAUNCHED("k_big_tiles");
     prof_begin(PK_BIG_INSERT, s);
     k_big_insert<<<4096 * 256 / BIG_T, BIG_T, 0, s>>>(src, L, perm, vstart, ws.mstart, gstart, ws.bigm, ws.tsize, n2, ws.tkey,
                                       ws.tval, ws.dslot, ws.dense, ws.tinfo, dst, prof_dev_bytes(PK_BIG_INSERT));
     MC_LAUNCHED("k_big_insert");
     prof_end(PK_BIG_INSERT, s);
-    k_big_xtiles<<<grid_for((src.cap * 5 / 2) / TILE_SLOTS + 8, 256), 256, 0, s>>>(ws.tsize, n2, ws.xg);
-    MC_LAUNCHED("k_big_xtiles");
-    k_big_extract<<<4096, EX_T, 0, s>>>(ws.tsize, gstart, n2, ws.xg, ws.tkey, ws.tval, ws.bcur, dst);
+    k_big_extract<<<4096, EX_T, 0, s>>>(ws.tsize, gstart, n2, ws.xg, ws.tkey, ws.tval, ws.dinfo, nd_max, ws.dense,
+                                        ws.bcur, dst);
     MC_LAUNCHED("k_big_extract");
-    k_dense_extract<<<grid_for((int64_t)nd_max * n2, 16 * EX_T, 4096), EX_T, 0, s>>>(ws.dinfo, nd_max, gstart, n2, ws.dense,
-                                                                              ws.bcur, dst);
-    MC_LAUNCHED("k_dense_extract");
-    k_big_finalize<<<grid_for(n2, 256), 256, 0, s>>>(ws.bigm, n2, ws.bcur, dst);
-    MC_LAUNCHED("k_big_finalize");
-    return min_degree(dst, ws, sc, s);
+    return min_degree(dst, ws.bigm, ws.bcur, ws, sc, s);
 }

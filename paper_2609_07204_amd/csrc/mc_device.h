@@ -39,6 +39,7 @@ struct DevScalars {
     int32_t err;            // validation error code (0 = fine)
     int32_t noncanon;       // 1: the input CSR needs the merging normalisation
     int64_t dmax;           // maximum degree of the graph the last min_degree read
+    int32_t max_row;        // longest row of that graph
     int64_t gmax;           // batched form: the largest total degree of one graph of the batch
 };
 
@@ -57,6 +58,18 @@ __device__ __forceinline__ void st64_dev(int64_t* p, int64_t v) {
 }
 __device__ __forceinline__ int64_t atomic_add_i64(int64_t* p, int64_t v) {
     return (int64_t)atomicAdd((unsigned long long*)p, (unsigned long long)v);
+}
+
+// Parents as the last launch left them, or newer: a load that the caches may
+// serve. Device-scope loads go past the L2 of the compute unit's die, which
+// makes them the bound of kernels that compress or link many trees. Only where
+// no union of this launch moves a root under a thread that must see it: an old
+// parent is an ancestor too.
+__device__ __forceinline__ int32_t ld_old(const int32_t* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void st_new(int32_t* p, int32_t v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 // ------------------------------------------------------- union-find

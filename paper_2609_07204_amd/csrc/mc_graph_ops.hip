@@ -20,7 +20,7 @@ inline int grid_for(int64_t count, int threads, int cap = 8192) {
 }
 
 constexpr int SUB = 16;  // lanes per row for row-wise kernels
-// test-1 trees that the byte-label linking handles (k_pr1_trees) and
+// test-1 trees that the byte-label linking handles (pr1_trees) and
 // the words of its tree-pair bit matrix
 constexpr int PR1_TREES = 255;
 constexpr int PR1_WORDS = 256 * 256 / 32;
@@ -82,15 +82,17 @@ __global__ __launch_bounds__(256) void k_uf_root_min(DGraph g, int32_t* par) {
 
 // The root most of 1024 sampled vertices lie under, counted in an LDS hash
 // table (1024 reads of all samples by every thread took 20 us).
-__global__ __launch_bounds__(1024) void k_uf_sample_mode(const int32_t* par, int32_t n, int32_t* mode) {
+__global__ __launch_bounds__(1024) void k_uf_sample_mode(const int32_t* par, int32_t n, int32_t* mode,
+                                                        const int32_t* ntree = nullptr) {
+    if (ntree && *ntree <= 1) return;   // nothing left to link
     constexpr int SLOTS = 2048;
     __shared__ int32_t key[SLOTS], cnt[SLOTS];
     __shared__ int64_t wbest[1024 / MC_WAVE];
     for (int i = threadIdx.x; i < SLOTS; i += 1024) { key[i] = -1; cnt[i] = 0; }
     const uint32_t h = hash32(threadIdx.x * 2654435761u + 12345u);
     const int32_t v = (int32_t)(((uint64_t)h * (uint64_t)n) >> 32);
-    int32_t x = v, p = ld_acq(&par[x]);
-    while (p != x) { x = p; p = ld_acq(&par[x]); }
+    int32_t x = v, p = ld_old(&par[x]);
+    while (p != x) { x = p; p = ld_old(&par[x]); }
     __syncthreads();
     // the wavefront's lanes of one root are counted by the first of them
     int32_t mine = 0;
@@ -129,9 +131,7 @@ __global__ __launch_bounds__(1024) void k_uf_sample_mode(const int32_t* par, int
 
 // After a compress: snap[v] = v's root, inbig[v] = 1 iff that root is the
 // root of the largest sampled component.
-__global__ void k_uf_snapshot(const int32_t* par, int32_t n, const int32_t* mode, uint8_t* inbig, int32_t* snap,
-                              const int32_t* ntree = nullptr) {
-    if (ntree && *ntree <= PR1_TREES) return;   // the trees are linked by k_pr1_trees
+__global__ void k_uf_snapshot(const int32_t* par, int32_t n, const int32_t* mode, uint8_t* inbig, int32_t* snap) {
     const int32_t big = *mode;
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
         const int32_t r = par[v];
@@ -167,21 +167,11 @@ __global__ __launch_bounds__(256) void k_uf_link_rest(DGraph g, int32_t* par, co
 // its own entry, so concurrent finds still see valid ancestors.
 __global__ void k_uf_compress(int32_t* par, int32_t n) {
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
-        int32_t x = (int32_t)v, p = ld_acq(&par[x]);
-        while (p != x) { x = p; p = ld_acq(&par[x]); }
-        st_rel(&par[v], x);
+        const int32_t first = ld_old(&par[v]);
+        int32_t x = first, p = ld_old(&par[x]);
+        while (p != x) { x = p; p = ld_old(&par[x]); }
+        if (x != first) st_rel(&par[v], x);
     }
-}
-
-__global__ void k_root_flag(const int32_t* par, int32_t n, int32_t* flag) {
-    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x)
-        flag[v] = par[v] == v;
-}
-
-__global__ void k_label(const int32_t* par, const int32_t* newid, int32_t n, int32_t* L, DevScalars* sc) {
-    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x)
-        L[v] = newid[par[v]];
-    if (blockIdx.x == 0 && threadIdx.x == 0) sc->n2 = newid[n];
 }
 
 // Padberg-Rinaldi tests on the current graph with bound lam:
@@ -362,16 +352,24 @@ __global__ __launch_bounds__(256) void k_pr1_first(const int32_t* __restrict__ n
 // these graphs: the trees are angular sectors, and the entries between
 // them are few and spread over all rows.)
 
-// tree number of every vertex (trees numbered by root, so in the order of
-// their smallest vertex) and the root of every tree; tscan holds the
-// exclusive prefix count of the roots
-__global__ void k_tree_label(const int32_t* __restrict__ par, const int32_t* __restrict__ tscan, int32_t n,
-                             uint8_t* lab8, int32_t* troot) {
-    if (tscan[n] <= 1 || tscan[n] > PR1_TREES) return;
+// What the linking reads of every vertex: with at most PR1_TREES trees its
+// tree's number (trees numbered by root, so in the order of their smallest
+// vertex; troot holds the roots), with more its root and whether that is the
+// sampled tree's. tscan holds the exclusive prefix count of the roots.
+__global__ void k_pr1_label(const int32_t* __restrict__ par, const int32_t* __restrict__ tscan, int32_t n,
+                            const int32_t* mode, uint8_t* inbig, int32_t* snap, int32_t* troot) {
+    const int32_t T = tscan[n];
+    if (T <= 1) return;
+    const int32_t big = *mode;
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
         const int32_t r = par[v];
-        lab8[v] = (uint8_t)tscan[r];
-        if (r == v) troot[tscan[v]] = (int32_t)v;
+        if (T <= PR1_TREES) {
+            inbig[v] = (uint8_t)tscan[r];
+            if (r == v) troot[tscan[v]] = (int32_t)v;
+        } else {
+            snap[v] = r;
+            inbig[v] = r == big;
+        }
     }
 }
 
@@ -380,12 +378,10 @@ __global__ void k_tree_label(const int32_t* __restrict__ par, const int32_t* __r
 // from the smaller endpoint or from outside into the sampled tree.
 // As in k_pr12, 16 lanes take 16 consecutive rows, whose metadata comes in
 // one load, and each lane keeps four entries and their trees in flight.
-__global__ __launch_bounds__(256) void k_pr1_trees(DGraph g, const int64_t* lamp, const int32_t* vinst,
-                                                  const int32_t* __restrict__ heavy_cnt,
-                                                  const uint8_t* __restrict__ lab8,
-                                                  const int32_t* __restrict__ tscan, const int32_t* mode,
-                                                  uint32_t* bits, unsigned long long* pb) {
-    if (tscan[g.n] <= 1 || tscan[g.n] > PR1_TREES) return;
+__device__ __forceinline__ void pr1_trees(const DGraph& g, const int64_t* lamp, const int32_t* vinst,
+                                          const int32_t* __restrict__ heavy_cnt, const uint8_t* __restrict__ lab8,
+                                          const int32_t* __restrict__ tscan, const int32_t* mode, uint32_t* bits,
+                                          unsigned long long* pb) {
     __shared__ uint32_t sb[PR1_WORDS];
     for (int i = threadIdx.x; i < PR1_WORDS; i += blockDim.x) sb[i] = 0;
     __syncthreads();
@@ -453,66 +449,13 @@ __global__ __launch_bounds__(256) void k_pr1_trees(DGraph g, const int64_t* lamp
     if (pb) prof_add(pb, bytes);
 }
 
-// one workgroup: components of the tree graph by a lock-free union-find
-// on the tree numbers in LDS (the smaller number as root), one thread per
-// word of the bit matrix; then the root vertex of each tree's component.
-// Counts the joins as marks.
-__device__ __forceinline__ int32_t lds_ld(const int32_t* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-__global__ __launch_bounds__(256) void k_tree_join(const int32_t* __restrict__ tscan, int32_t n,
-                                                  const uint32_t* __restrict__ bits, const int32_t* __restrict__ troot,
-                                                  int32_t* tmap, unsigned long long* marks) {
-    const int32_t T = tscan[n];
-    if (T <= 1 || T > PR1_TREES) return;
-    __shared__ int32_t tp[256];
-    __shared__ unsigned long long sj;
-    for (int t = threadIdx.x; t < 256; t += blockDim.x) tp[t] = t;
-    if (threadIdx.x == 0) sj = 0;
-    __syncthreads();
-    unsigned long long joined = 0;
-    for (int i = threadIdx.x; i < PR1_WORDS; i += blockDim.x) {
-        for (uint32_t m = bits[i]; m; m &= m - 1) {
-            const int bit = i * 32 + __ffs(m) - 1;
-            int32_t x = bit >> 8, y = bit & 255;
-            for (;;) {
-                for (int32_t p = lds_ld(&tp[x]); p != x; p = lds_ld(&tp[x])) x = p;
-                for (int32_t p = lds_ld(&tp[y]); p != y; p = lds_ld(&tp[y])) y = p;
-                if (x == y) break;
-                if (x > y) { const int32_t t = x; x = y; y = t; }
-                if (atomicCAS(&tp[y], y, x) == y) { joined++; break; }
-            }
-        }
-    }
-    if (joined) atomicAdd(&sj, joined);
-    __syncthreads();
-    for (int t = threadIdx.x; t < T; t += blockDim.x) {
-        int32_t x = t;
-        while (tp[x] != x) x = tp[x];
-        tmap[t] = troot[x];
-    }
-    if (threadIdx.x == 0 && sj) atomicAdd(marks, sj);
-}
-
-// every vertex points at the root of its tree's component
-__global__ void k_tree_apply(const int32_t* __restrict__ tscan, const uint8_t* __restrict__ lab8,
-                             const int32_t* __restrict__ tmap, int32_t n, int32_t* par) {
-    if (tscan[n] <= 1 || tscan[n] > PR1_TREES) return;
-    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t r = tmap[lab8[v]];
-        if (par[v] != r) par[v] = r;
-    }
-}
-
 // rows with more than two test-1 entries, outside the sampled
 // component: union all of them (an edge into that component from a row
 // inside it is seen from this side)
-__global__ __launch_bounds__(256) void k_pr1_rest(DGraph g, const int64_t* lamp, const int32_t* vinst, int32_t* par,
-                                                 const int32_t* __restrict__ heavy_cnt,
-                                                 const uint8_t* __restrict__ inbig, const int32_t* __restrict__ snap,
-                                                 const int32_t* ntree, unsigned long long* marks,
-                                                 unsigned long long* pb) {
-    if (*ntree <= PR1_TREES) return;   // the trees are linked by k_pr1_trees
+__device__ __forceinline__ void pr1_snap(const DGraph& g, const int64_t* lamp, const int32_t* vinst, int32_t* par,
+                                         const int32_t* __restrict__ heavy_cnt, const uint8_t* __restrict__ inbig,
+                                         const int32_t* __restrict__ snap, unsigned long long* marks,
+                                         unsigned long long* pb) {
     const int64_t lam0 = *lamp;
     const int64_t nsub = (int64_t)gridDim.x * (blockDim.x / SUB);
     const int sl = threadIdx.x % SUB;
@@ -542,34 +485,112 @@ __global__ __launch_bounds__(256) void k_pr1_rest(DGraph g, const int64_t* lamp,
     }
 }
 
-// fold the partial counters of k_pr12 into the round's mark count
-__global__ __launch_bounds__(64) void k_pr12_fold(unsigned long long* spread, unsigned long long* marks) {
+__global__ __launch_bounds__(256) void k_pr1_rest(DGraph g, const int64_t* lamp, const int32_t* vinst, int32_t* par,
+                                                 const int32_t* __restrict__ heavy_cnt,
+                                                 const uint8_t* __restrict__ inbig, const int32_t* __restrict__ snap,
+                                                 const int32_t* __restrict__ tscan, const int32_t* mode, uint32_t* bits,
+                                                 unsigned long long* marks, unsigned long long* pb) {
+    const int32_t T = tscan[g.n];
+    if (T <= 1) return;
+    if (T <= PR1_TREES) pr1_trees(g, lamp, vinst, heavy_cnt, inbig, tscan, mode, bits, pb);
+    else pr1_snap(g, lamp, vinst, par, heavy_cnt, inbig, snap, marks, pb);
+}
+
+// fold the partial counters of k_pr12 or k_pr34 into the round's mark count
+__device__ __forceinline__ void pr_fold(const unsigned long long* spread, unsigned long long* marks) {
     const int64_t v = wave_sum_i64((int64_t)spread[(size_t)threadIdx.x * SPREAD_STRIDE]);
     if (threadIdx.x == 0 && v) atomicAdd(marks, (unsigned long long)v);
 }
+static_assert(SPREAD == MC_WAVE, "one lane per partial counter");
+__global__ __launch_bounds__(64) void k_pr12_fold(const unsigned long long* spread, unsigned long long* marks) {
+    pr_fold(spread, marks);
+}
 
-// task offsets of the long rows: ceil(len / PR_CHUNK) tasks each
-__global__ __launch_bounds__(1024) void k_pr12_long_scan(const DGraph g, const int32_t* long_list,
-                                                        const int32_t* long_cnt, int32_t* task_off) {
-    __shared__ int32_t part[1024];
-    const int32_t nl = *long_cnt;
-    const int32_t per = (nl + 1023) / 1024;
+// task offsets of the long rows, ceil(len / PR_CHUNK) tasks each (one
+// workgroup of 256 threads)
+__device__ __forceinline__ void pr12_long_scan(const DGraph& g, const int32_t* long_list, int32_t nl, int32_t* task_off) {
+    __shared__ int32_t part[256 / MC_WAVE];
+    const int32_t per = (nl + 255) / 256;
     const int32_t b = threadIdx.x * per, e = b + per < nl ? b + per : nl;
     int32_t s = 0;
     for (int32_t i = b; i < e; i++) s += (g.len[long_list[i]] + PR_CHUNK - 1) / PR_CHUNK;
-    part[threadIdx.x] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int32_t run = 0;
-        for (int k = 0; k < 1024; k++) { int32_t t = part[k]; part[k] = run; run += t; }
-        task_off[nl] = run;
+    int32_t incl = s;
+    for (int k = 1; k < MC_WAVE; k <<= 1) {
+        const int32_t y = __shfl_up(incl, k, MC_WAVE);
+        if (lane_id() >= k) incl += y;
     }
+    if (lane_id() == MC_WAVE - 1) part[threadIdx.x / MC_WAVE] = incl;
     __syncthreads();
-    int32_t run = part[threadIdx.x];
+    int32_t run = incl - s;
+    for (int k = 0; k < (int)threadIdx.x / MC_WAVE; k++) run += part[k];
     for (int32_t i = b; i < e; i++) {
         task_off[i] = run;
         run += (g.len[long_list[i]] + PR_CHUNK - 1) / PR_CHUNK;
     }
+    if (threadIdx.x == 255) task_off[nl] = run;   // no rows after the last thread's
+}
+
+// The trees that k_pr1_rest found side by side become one: every workgroup
+// finds the components of the tree graph for itself, by a lock-free
+// union-find on the tree numbers in LDS (the smaller number as root), one
+// thread per word of the bit matrix, and points its vertices at the root
+// vertex of their tree's component. The first workgroup counts the joins as
+// marks, folds the partial counters of the launches before and lays out the
+// long rows' tasks: work that took a launch each, of 1.5 to 9 us.
+constexpr int PR1_APPLY = 512;   // workgroups, each of which joins the trees
+__device__ __forceinline__ int32_t lds_ld(const int32_t* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__global__ __launch_bounds__(256) void k_pr1_apply(DGraph g, const int32_t* __restrict__ tscan,
+                                                  const uint32_t* __restrict__ bits, const int32_t* __restrict__ troot,
+                                                  const uint8_t* __restrict__ lab8, int32_t* par,
+                                                  const unsigned long long* spread, unsigned long long* marks,
+                                                  const int32_t* long_list, const int32_t* long_cnt, int32_t* task_off) {
+    const int32_t n = g.n, T = tscan[n];
+    if (blockIdx.x == 0) {
+        if (threadIdx.x < MC_WAVE) pr_fold(spread, marks);
+        if (*long_cnt > 0) pr12_long_scan(g, long_list, *long_cnt, task_off);
+    }
+    if (T <= 1 || T > PR1_TREES) return;
+    __shared__ int32_t tp[256], tmap[256];
+    __shared__ unsigned long long sj;
+    for (int t = threadIdx.x; t < 256; t += blockDim.x) tp[t] = t;
+    if (threadIdx.x == 0) sj = 0;
+    __syncthreads();
+    unsigned long long joined = 0;
+    for (int i = threadIdx.x; i < PR1_WORDS; i += blockDim.x) {
+        for (uint32_t m = bits[i]; m; m &= m - 1) {
+            const int bit = i * 32 + __ffs(m) - 1;
+            int32_t x = bit >> 8, y = bit & 255;
+            for (;;) {
+                for (int32_t p = lds_ld(&tp[x]); p != x; p = lds_ld(&tp[x])) x = p;
+                for (int32_t p = lds_ld(&tp[y]); p != y; p = lds_ld(&tp[y])) y = p;
+                if (x == y) break;
+                if (x > y) { const int32_t t = x; x = y; y = t; }
+                if (atomicCAS(&tp[y], y, x) == y) { joined++; break; }
+            }
+        }
+    }
+    if (joined) atomicAdd(&sj, joined);
+    __syncthreads();
+    for (int t = threadIdx.x; t < T; t += blockDim.x) {
+        int32_t x = t;
+        while (tp[x] != x) x = tp[x];
+        tmap[t] = troot[x];
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0 && sj) atomicAdd(marks, sj);
+    __syncthreads();
+    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
+        const int32_t r = tmap[lab8[v]];
+        if (par[v] != r) par[v] = r;
+    }
+}
+
+// the counters, partial counters and tree-pair bits of a launch sequence, cleared
+__global__ __launch_bounds__(1024) void k_pr12_clear(int32_t* counters, unsigned long long* spread, uint32_t* tbits) {
+    if (threadIdx.x < 4) counters[threadIdx.x] = 0;
+    for (int i = threadIdx.x; i < SPREAD * SPREAD_STRIDE; i += 1024) spread[i] = 0;
+    for (int i = threadIdx.x; i < PR1_WORDS; i += 1024) tbits[i] = 0;
 }
 
 __device__ __forceinline__ int32_t last_le_g(const int32_t* a, int32_t n, int64_t key) {
@@ -592,7 +613,7 @@ __global__ __launch_bounds__(256) void k_pr12_long(DGraph g, const int64_t* lamp
     __shared__ int32_t s_rv;
     const int64_t lam0 = *lamp;
     const int32_t nl = *long_cnt;
-    const int32_t ntask = task_off[nl];
+    const int32_t ntask = nl > 0 ? task_off[nl] : 0;
     unsigned long long joined = 0;
     for (int32_t t = blockIdx.x; t < ntask; t += gridDim.x) {
         const int32_t i = last_le_g(task_off, nl, t);
@@ -980,14 +1001,7 @@ bool uf_connectivity(const DGraph& g, int32_t* parent, int32_t* tmp, uint8_t* in
 
 bool uf_labels(int32_t* parent, int32_t n, int32_t* L, int32_t* flag_tmp, int32_t* scan_tmp, DevScalars* sc,
                hipStream_t s) {
-    k_uf_compress<<<grid_for(n, 256), 256, 0, s>>>(parent, n);
-    MC_LAUNCHED("k_uf_compress");
-    k_root_flag<<<grid_for(n, 256), 256, 0, s>>>(parent, n, flag_tmp);
-    MC_LAUNCHED("k_root_flag");
-    if (!scan_i32(flag_tmp, flag_tmp, n, scan_tmp, s)) return false;
-    k_label<<<grid_for(n, 256), 256, 0, s>>>(parent, flag_tmp, n, L, sc);
-    MC_LAUNCHED("k_label");
-    return true;
+    return root_labels(parent, n, nullptr, nullptr, flag_tmp, L, scan_tmp, sc, s);
 }
 
 void pr12_ws_carve(Arena& a, int32_t n, int64_t cap, Pr12WS& w) {
@@ -1010,13 +1024,12 @@ void pr12_ws_carve(Arena& a, int32_t n, int64_t cap, Pr12WS& w) {
     w.scan_tmp = a.take<int32_t>(scan_tmp_elems((int64_t)n) + 1);
     w.tbits = a.take<uint32_t>(PR1_WORDS);
     w.troot = a.take<int32_t>(256);
-    w.tmap = a.take<int32_t>(256);
 }
 
 bool pr12(const DGraph& g, const int64_t* lam, int32_t* parent, unsigned long long* marks, uint8_t* flag1,
-          int32_t* ptr2, Pr12WS& w, hipStream_t s, const int32_t* vinst) {
-    if (!fill_i32(w.counters, 0, 4, s)) return false;
-    if (!fill_i64((int64_t*)w.spread, 0, (int64_t)SPREAD * SPREAD_STRIDE, s)) return false;
+          int32_t* ptr2, Pr12WS& w, hipStream_t s, const int32_t* vinst, int32_t max_row) {
+    k_pr12_clear<<<1, 1024, 0, s>>>(w.counters, w.spread, w.tbits);
+    MC_LAUNCHED("k_pr12_clear");
     prof_begin(PK_PR12, s);
     k_pr12<<<grid_for(g.n, 256), 256, 0, s>>>(g, lam, vinst, parent, w.spread, flag1, ptr2, w.long_list,
                                                             w.counters, w.first, w.second, w.heavy,
@@ -1029,40 +1042,29 @@ bool pr12(const DGraph& g, const int64_t* lam, int32_t* parent, unsigned long lo
                                                       prof_dev_bytes(PK_PR1_FIRST));
         MC_LAUNCHED("k_pr1_first");
         prof_end(PK_PR1_FIRST, s);
-        k_uf_compress<<<grid_for(g.n, 256), 256, 0, s>>>(parent, g.n);
-        MC_LAUNCHED("k_uf_compress");
+        if (round == 0) {
+            k_uf_compress<<<grid_for(g.n, 256), 256, 0, s>>>(parent, g.n);
+            MC_LAUNCHED("k_uf_compress");
+        }
     }
-    // trees numbered by root: with at most PR1_TREES of them the byte-label
-    // path links them (k_pr1_trees ... k_tree_apply), otherwise the
-    // snapshot path (k_uf_snapshot, k_pr1_rest); each kernel of the path
-    // not taken returns at once
-    k_root_flag<<<grid_for(g.n, 256), 256, 0, s>>>(parent, g.n, w.tscan);
-    MC_LAUNCHED("k_root_flag");
-    if (!scan_i32(w.tscan, w.tscan, g.n, w.scan_tmp, s)) return false;
-    if (!fill_i32((int32_t*)w.tbits, 0, PR1_WORDS, s)) return false;
-    k_uf_sample_mode<<<1, 1024, 0, s>>>(parent, g.n, w.mode);
+    // trees numbered by root: at most PR1_TREES of them are linked through
+    // byte labels and the tree graph (pr1_trees, k_pr1_apply), more against
+    // the snapshot (pr1_snap)
+    if (!root_ranks(parent, g.n, w.tscan, w.scan_tmp, s)) return false;
+    k_uf_sample_mode<<<1, 1024, 0, s>>>(parent, g.n, w.mode, w.tscan + g.n);
     MC_LAUNCHED("k_uf_sample_mode");
-    k_tree_label<<<grid_for(g.n, 256), 256, 0, s>>>(parent, w.tscan, g.n, w.inbig, w.troot);
-    MC_LAUNCHED("k_tree_label");
-    k_uf_snapshot<<<grid_for(g.n, 256), 256, 0, s>>>(parent, g.n, w.mode, w.inbig, w.snap, w.tscan + g.n);
-    MC_LAUNCHED("k_uf_snapshot");
+    k_pr1_label<<<grid_for(g.n, 256), 256, 0, s>>>(parent, w.tscan, g.n, w.mode, w.inbig, w.snap, w.troot);
+    MC_LAUNCHED("k_pr1_label");
     prof_begin(PK_PR1_REST, s);
-    k_pr1_trees<<<grid_for((int64_t)g.n * SUB, 256), 256, 0, s>>>(g, lam, vinst, w.heavy, w.inbig, w.tscan, w.mode,
-                                                                 w.tbits, prof_dev_bytes(PK_PR1_REST));
-    MC_LAUNCHED("k_pr1_trees");
     k_pr1_rest<<<grid_for((int64_t)g.n * SUB, 256), 256, 0, s>>>(g, lam, vinst, parent, w.heavy, w.inbig, w.snap,
-                                                                w.tscan + g.n, w.spread,
+                                                                w.tscan, w.mode, w.tbits, w.spread,
                                                                 prof_dev_bytes(PK_PR1_REST));
     MC_LAUNCHED("k_pr1_rest");
     prof_end(PK_PR1_REST, s);
-    k_tree_join<<<1, 256, 0, s>>>(w.tscan, g.n, w.tbits, w.troot, w.tmap, marks);
-    MC_LAUNCHED("k_tree_join");
-    k_tree_apply<<<grid_for(g.n, 256), 256, 0, s>>>(w.tscan, w.inbig, w.tmap, g.n, parent);
-    MC_LAUNCHED("k_tree_apply");
-    k_pr12_fold<<<1, SPREAD, 0, s>>>(w.spread, marks);
-    MC_LAUNCHED("k_pr12_fold");
-    k_pr12_long_scan<<<1, 1024, 0, s>>>(g, w.long_list, w.counters, w.task_off);
-    MC_LAUNCHED("k_pr12_long_scan");
+    k_pr1_apply<<<grid_for(g.n, 256, PR1_APPLY), 256, 0, s>>>(g, w.tscan, w.tbits, w.troot, w.inbig, parent, w.spread,
+                                                             marks, w.long_list, w.counters, w.task_off);
+    MC_LAUNCHED("k_pr1_apply");
+    if (max_row <= PR_LONG) return true;   // no row is that long
     k_pr12_long<<<2048, 256, 0, s>>>(g, lam, vinst, parent, marks, flag1, w.long_list, w.counters, w.task_off, w.part_w,
                                      w.part_x);
     MC_LAUNCHED("k_pr12_long");

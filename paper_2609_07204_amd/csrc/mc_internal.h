@@ -58,6 +58,19 @@ struct Arena {
 // the total. in and out may alias. tmp must hold scan_tmp_elems(count).
 size_t scan_tmp_elems(int64_t count);
 bool scan_i32(const int32_t* in, int32_t* out, int64_t count, int32_t* tmp, hipStream_t s);
+// Three arrays in place at once; tmp: 3 (count / 2048 + 2) ints or scan_tmp_elems(count).
+bool scan3_i32(int32_t* a, int32_t* b, int32_t* c, int64_t count, int32_t* tmp, hipStream_t s);
+// The prefix of the row lengths in perm order (perm null: in vertex order),
+// 0 for positions past *kept (kept null: none).
+bool scan_member_len(const int32_t* len, const int32_t* perm, const int32_t* kept, int32_t* out, int64_t count,
+                     int32_t* tmp, hipStream_t s);
+// Compress parent[]; rank[v] = roots before v, rank[n] = roots. The roots of
+// graphs with dead[vinst[v]] do not count (dead null: all do).
+bool root_ranks(int32_t* parent, int32_t n, int32_t* rank, int32_t* tmp, hipStream_t s);
+// The same, and with L the label (its root's rank; -1 in a dead graph) of
+// every vertex and sc->n2 = the number of labels.
+bool root_labels(int32_t* parent, int32_t n, const int32_t* vinst, const uint8_t* dead, int32_t* rank, int32_t* L,
+                 int32_t* tmp, DevScalars* sc, hipStream_t s);
 
 // ------------------------------------------------------- fill / misc
 bool fill_i32(int32_t* p, int32_t v, int64_t count, hipStream_t s);
@@ -182,13 +195,14 @@ struct Pr12WS {
     int32_t* scan_tmp;    // scratch of the prefix count
     uint32_t* tbits;      // [256 * 256 / 32] pairs of trees joined by a test-1 entry
     int32_t* troot;       // [256] root vertex of each tree
-    int32_t* tmap;        // [256] root vertex of each tree's component
 };
 void pr12_ws_carve(Arena& a, int32_t n, int64_t cap, Pr12WS& w);
 // With vinst (per-vertex instance) the bound of vertex v is lam[vinst[v]]
-// (batched solves of many graphs in one union graph); else lam[0].
+// (batched solves of many graphs in one union graph); else lam[0]. max_row:
+// no row is longer, if known.
 bool pr12(const DGraph& g, const int64_t* lam, int32_t* parent, unsigned long long* marks,
-          uint8_t* flag1, int32_t* ptr2, Pr12WS& w, hipStream_t s, const int32_t* vinst = nullptr);
+          uint8_t* flag1, int32_t* ptr2, Pr12WS& w, hipStream_t s, const int32_t* vinst = nullptr,
+          int32_t max_row = INT32_MAX);
 
 // Reduction test by edge-disjoint subgraphs (mc_certify.hip): the vertices
 // connected in every one of k subgraphs whose units of weight c >= lam / k

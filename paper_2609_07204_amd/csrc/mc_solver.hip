@@ -579,6 +579,7 @@ struct Solver {
     int32_t small_passes = 0;     // passes of small rounds now (0: the first round's count)
     int64_t pv_stride = 0;        // stride of the last private launch (its pass orders)
     int64_t cur_m = 0;            // entries of the current graph
+    int32_t in_max_row = INT32_MAX;   // longest row of the input
     int32_t last_cf_steps = 0;    // whole-GPU steps of the round's last CAPFOREST launch
     int64_t last_cf_scans = 0;    // and the vertices it scanned
     mc_stats stats{};
@@ -588,10 +589,11 @@ struct Solver {
     // one contraction per 100 vertices (as repeated linear sweeps stop once
     // they stop shrinking the graph, App. A).
     bool tri() const { return tri_on && c->opt.pr_tri_deg_cap > 0; }
-    bool tests12(const DGraph& g) {
-        return pr12(g, &w.sc->lam, w.parent, &w.sc->marks_pr, nullptr, tri() ? w.tw.ptr2 : nullptr, w.prw, s);
+    bool tests12(const DGraph& g, int32_t max_row) {
+        return pr12(g, &w.sc->lam, w.parent, &w.sc->marks_pr, nullptr, tri() ? w.tw.ptr2 : nullptr, w.prw, s, nullptr,
+                    max_row);
     }
-    bool reduction_tests(const DGraph& g) { return tests12(g) && tests34(g); }
+    bool reduction_tests(const DGraph& g) { return tests12(g, INT32_MAX) && tests34(g); }
     bool tests34(const DGraph& g) {
         if (!tri()) return true;
         if (!pr34(g, &w.sc->lam, c->opt.pr_tri_deg_cap, w.parent, &w.sc->marks_tri, w.tw.ptr2, w.tw, nullptr,
@@ -609,7 +611,7 @@ struct Solver {
 
     // The edge-disjoint subgraphs' test on g at the bound in sc->lam, in the
     // memory of the graph the next contraction will write.
-    bool certificates(const DGraph& g, const DGraph& free_graph) {
+    bool certificates(const DGraph& g, const DGraph& free_graph, bool read) {
         CertArgs a{};
         a.g = g;
         a.lam = &w.sc->lam;
@@ -618,7 +620,7 @@ struct Solver {
         a.marks = &w.sc->marks_cert;
         char* const base = (char*)free_graph.col;
         if (!cert_carve(a, base, (size_t)((char*)(free_graph.w + free_graph.cap) - base))) return true;
-        return certify(a, s) && readback();
+        return certify(a, s) && (!read || readback());
     }
 
     // passes of the private form on an n-vertex round
@@ -924,6 +926,7 @@ static mc_status threshold_bound(Solver& S, int32_t round) {
     hipStream_t s = S.s;
     const int64_t m0 = S.cur_m;
     const int64_t target = S.lam / kBoundShare;
+    int32_t max_row = S.in_max_row;
     if (target < 1) return MC_OK;
     DGraph* cur = &w.g[0];
     int nxt_idx = 1;
@@ -933,8 +936,8 @@ static mc_status threshold_bound(Solver& S, int32_t round) {
         k_reset_round<<<1, 1, 0, s>>>(w.sc);
         k_set_lam<<<1, 1, 0, s>>>(w.sc, target);
         if (!uf_init(w.parent, n, s) ||
-            !pr12(*cur, &w.sc->lam, w.parent, &w.sc->marks_pr, nullptr, nullptr, w.prw, s) ||
-            !S.certificates(*cur, w.g[nxt_idx]) || !uf_labels(w.parent, n, w.L, w.flag, w.cw.scan_tmp, w.sc, s) ||
+            !pr12(*cur, &w.sc->lam, w.parent, &w.sc->marks_pr, nullptr, nullptr, w.prw, s, nullptr, max_row) ||
+            !S.certificates(*cur, w.g[nxt_idx], false) || !uf_labels(w.parent, n, w.L, w.flag, w.cw.scan_tmp, w.sc, s) ||
             !S.set_lam(S.lam) || !S.readback())
             return MC_E_DEVICE;
         const int32_t n2 = S.c->hsc->n2;
@@ -943,6 +946,7 @@ static mc_status threshold_bound(Solver& S, int32_t round) {
         if (n2 < 2 || (int64_t)n2 * 20 > (int64_t)n * 19) break;
         cur = contract_and_bound(S, cur, n2, &nxt_idx, &err);
         if (!cur) return err;
+        max_row = S.c->hsc->max_row;
     }
     if (cur != &w.g[0]) {
         if (cur->n > 2 && cur->n <= finish_max_n(S.c) && (err = finish(S, cur, round)) != MC_OK) return err;
@@ -964,6 +968,7 @@ static mc_status exact_rounds(Solver& S, int src) {
     int nxt_idx = src == 1 ? 2 : 1;
     int32_t round = 0;
     const int64_t m_first = S.cur_m;
+    int32_t max_row = src == 0 ? S.in_max_row : INT32_MAX;   // longest row of cur
     bool note_bound = false;      // the tests' contraction of the input takes the heuristic's place
     while (cur->n > 2 && S.lam > 0) {
         if (cur->n <= finish_max_n(S.c)) {
@@ -979,7 +984,7 @@ static mc_status exact_rounds(Solver& S, int src) {
         if (!uf_init(w.parent, n, s)) return MC_E_DEVICE;
         // in the automatic mode tests 3 and 4 wait until a pass of CAPFOREST
         // is to be saved
-        if (!S.tests12(*cur) || (!S.automatic && !S.tests34(*cur))) return MC_E_DEVICE;
+        if (!S.tests12(*cur, max_row) || (!S.automatic && !S.tests34(*cur))) return MC_E_DEVICE;
         const bool det = S.c->opt.deterministic != 0;
         // when the reduction tests alone at least halve the graph, contract
         // now and leave CAPFOREST to the smaller graph of the next round
@@ -990,7 +995,7 @@ static mc_status exact_rounds(Solver& S, int src) {
         // before CAPFOREST; when both kinds of tests together halve the
         // graph, CAPFOREST is left out
         if (!skip_cf && S.automatic && n <= S.cert_max_n) {
-            if (!S.certificates(*cur, *nxt)) return MC_E_DEVICE;
+            if (!S.certificates(*cur, *nxt, true)) return MC_E_DEVICE;
             // left out until the graph is smaller by a quarter once it joins
             // fewer than one vertex in 32
             if (S.c->hsc->marks_cert * 32 < (unsigned long long)n) S.cert_max_n = n - n / 4;
@@ -1104,10 +1109,11 @@ static mc_status exact_rounds(Solver& S, int src) {
                 used = CF_RUN_PRIVATE;
             }
         }
-        if (!S.readback()) return MC_E_DEVICE;
+        // without a pass of CAPFOREST the marks are those read back last
+        if (used != CF_RUN_NONE && !S.readback()) return MC_E_DEVICE;
         if (S.debug) debug_round(S, *cur, round, used == CF_RUN_PRIVATE ? std::min(w.pv.passes, S.passes_for(n)) : 0);
         if (!S.apply_alpha(used, n)) return MC_E_DEVICE;
-        if (!S.readback()) return MC_E_DEVICE;
+        if (used != CF_RUN_NONE && !S.readback()) return MC_E_DEVICE;
         DevScalars h = *S.c->hsc;
         S.stats.marks_pr += (int64_t)(h.marks_pr + h.marks_tri + h.marks_cert);
         S.stats.marks_capforest += (int64_t)h.marks_cf;
@@ -1164,6 +1170,7 @@ static mc_status exact_rounds(Solver& S, int src) {
         if (!S.readback()) return MC_E_DEVICE;
         h = *S.c->hsc;
         S.cur_m = h.m2;
+        max_row = h.max_row;
         // a small round that removed fewer than one vertex in ten: more
         // passes from now on (small_pass_max)
         if (used == CF_RUN_PRIVATE && n < levels_min_n(S.c) && (int64_t)n2 * 10 > (int64_t)n * 9)
@@ -1406,6 +1413,7 @@ static mc_status solve(mc_ctx* c, const mc_csr* g, void* dev_ws, size_t ws_bytes
     S.stats.n_input = n;
     const int64_t m_input = h.m2;   // entries of the normalised input (read by min_degree)
     S.cur_m = m_input;
+    S.in_max_row = h.max_row;
     int64_t result = 0;
     if (S.disconnected) {
         result = 0;   // check_connected set the side
