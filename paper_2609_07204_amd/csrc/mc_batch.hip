@@ -480,7 +480,6 @@ struct EngineWS {
     uint8_t *lowered, *dead2; // [K] threshold bounds: graphs lowered, graphs left out (in gerr, free after the checks)
     PrivateArgs pv;
     unsigned long long* pmarks;
-    unsigned long long* vpart;
     int32_t *flist, *fdrop, *frounds, *ferr;   // finisher: graphs, lowered bound, rounds, error and work-queue ticket
     uint8_t* fside;           // [N] the finisher's side over the current vertices
 };
@@ -563,7 +562,6 @@ void carve_engine(Arena& a, const Caps& cp, EngineWS& w) {
     pv.alpha_len = a.take<int32_t>((size_t)K);
     pv.lam_out = a.take<int64_t>((size_t)K);
     w.pmarks = a.take<unsigned long long>((size_t)K);
-    w.vpart = a.take<unsigned long long>(1024);
     w.flist = a.take<int32_t>((size_t)K + 1);
     w.fdrop = a.take<int32_t>((size_t)K + 1);
     w.frounds = a.take<int32_t>((size_t)K + 1);
@@ -707,7 +705,9 @@ struct Engine {
         DGraph S = w.stage;
         S.n = NS;
         S.cap = CS;
-        EG_OK(canon_check(w.in_rp, w.in_col, w.in_w, NS, 0, w.stage.len, w.stage.deg, &w.sc->noncanon, nullptr, nullptr, nullptr, s));
+        CanonParts parts;
+        EG_OK(canon_check(w.in_rp, w.in_col, w.in_w, NS, (int32_t)CS, w.stage.len, w.stage.deg, &w.sc->noncanon, nullptr, nullptr,
+                          w.cw, parts, s));
         // the largest graph's total degree (of the input rows, loops and
         // parallel entries counted: an upper bound) decides whether the
         // label-propagation rounds may keep 32-bit sums

@@ -47,7 +47,7 @@ constexpr int32_t CERT_ROW = 512;    // entries of a row looked at (a long row i
 constexpr int CERT_NEAR = 8;
 constexpr int CERT_SWEEPS = 4;
 constexpr int64_t CERT_EASY = 5;
-constexpr int32_t CERT_PROBE_N = 1 << 15;
+constexpr int CERT_WEDGES = 256;
 
 inline int grid_for(int64_t count, int threads, int cap = 8192) {
     int64_t b = (count + threads - 1) / threads;
@@ -55,6 +55,9 @@ inline int grid_for(int64_t count, int threads, int cap = 8192) {
     if (b > cap) b = cap;
     return (int)b;
 }
+
+// subgraph i of a single graph that has no more than i
+__device__ __forceinline__ bool unused(const CertArgs& a, int i) { return !a.vinst && i >= a.count[0]; }
 
 __device__ __forceinline__ bool inactive(const CertArgs& a, int64_t v) {
     return a.active && !a.active[a.vinst[v]];
@@ -72,16 +75,51 @@ __global__ void k_cert_plan(CertArgs a) {
         const int64_t c = lam > kc ? (lam + kc - 1) / kc : 1;
         a.unit[i] = c;
         a.count[i] = lam > 0 ? (int32_t)((lam + c - 1) / c) : 0;
+        if (a.sorted && a.total[1] * 4 >= CERT_WEDGES && a.total[0] / CERT_EASY / a.g.n < lam) a.count[i] = 0;
         a.rep[i] = INT32_MAX;
     }
+}
+
+// Whether two neighbours of a vertex are neighbours, for one of CERT_WEDGES
+// sampled vertices (sorted rows). Where a quarter of them are, units that go
+// round among a vertex's neighbours join patches and not the graph, and a graph
+// whose mean degree is below CERT_EASY times the bound is left out before its
+// rows are read (k = 0; hyperbolic 2^21, 32-core, 0.5 and more of the wedges
+// closed: 0.36 ms of rows and components for the probe to say no; Chung-Lu and
+// Erdos-Renyi graphs close fewer than one in ten). One workgroup beside those
+// that class the degrees, in their time.
+__device__ __forceinline__ bool wedge_closed(const DGraph& g, int i) {
+    const int32_t v = (int32_t)(((uint64_t)hash32(i * 2654435761u + 99u) * (uint64_t)g.n) >> 32);
+    const int32_t l = g.len[v];
+    if (l < 2) return false;
+    const uint32_t h = hash32(i * 2246822519u + 7u);
+    const int32_t p = (int32_t)(((uint64_t)h * (uint64_t)l) >> 32);
+    int32_t q = (int32_t)(((uint64_t)hash32(h) * (uint64_t)(l - 1)) >> 32);
+    q += q >= p;
+    int32_t x = g.col[g.off[v] + p], y = g.col[g.off[v] + q];
+    if (g.len[y] < g.len[x]) { const int32_t t = x; x = y; y = t; }
+    const int32_t o = g.off[x];
+    int32_t lo = 0, hi = g.len[x];
+    while (lo < hi) {
+        const int32_t mid = (lo + hi) / 2;
+        if (g.col[o + mid] < y) lo = mid + 1; else hi = mid;
+    }
+    return lo < g.len[x] && g.col[o + lo] == y;
 }
 
 // degree class: two bits below the leading one, so degrees within 25 % of
 // each other may share a class; the sum of the degrees
 __global__ __launch_bounds__(256) void k_cert_level(CertArgs a) {
+    static_assert(CERT_WEDGES == 256, "one thread a wedge");
     __shared__ int64_t sum[256 / MC_WAVE];
     int64_t t = 0;
-    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < a.g.n; v += (int64_t)gridDim.x * blockDim.x) {
+    if (a.sorted && blockIdx.x == gridDim.x - 1) {
+        const int closed = __popcll(__ballot(wedge_closed(a.g, threadIdx.x)));
+        if (lane_id() == 0) atomicAdd((unsigned long long*)&a.total[1], (unsigned long long)closed);
+        return;
+    }
+    const int64_t step = (int64_t)(gridDim.x - a.sorted) * blockDim.x;
+    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < a.g.n; v += step) {
         const uint64_t d = (uint64_t)a.g.deg[v] | 1;
         const int e = 63 - __clzll((long long)d);
         a.level[v] = (uint8_t)((e << 2) | (int)((e >= 2 ? d >> (e - 2) : d << (2 - e)) & 3));
@@ -112,6 +150,7 @@ __global__ __launch_bounds__(256) void k_cert_rows(CertArgs a) {
     __shared__ int32_t tile[ROWS][2 * CERT_KMAX + 1];
     // a single graph writes the words of its own k subgraphs only
     const int km = a.vinst ? a.kc : a.count[0];
+    if (km == 0) return;
     const int sl = threadIdx.x % SUB, sub = threadIdx.x / SUB;
     const int32_t n = a.g.n;
     for (int64_t v0 = (int64_t)blockIdx.x * ROWS; v0 < n; v0 += (int64_t)gridDim.x * ROWS) {
@@ -205,7 +244,7 @@ __global__ __launch_bounds__(256) void k_cert_rows(CertArgs a) {
 __global__ __launch_bounds__(256) void k_cert_compress(CertArgs a, int sweep) {
     const int32_t n = a.g.n;
     const int i = blockIdx.y;
-    if (sweep > 0 && a.more[i] != sweep) return;
+    if ((sweep > 0 && a.more[i] != sweep) || unused(a, i)) return;
     int32_t* par = a.own + (int64_t)i * n;
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
         if (inactive(a, v) || i >= a.count[a.vinst ? a.vinst[v] : 0]) continue;
@@ -229,7 +268,7 @@ __global__ __launch_bounds__(256) void k_cert_compress(CertArgs a, int sweep) {
 __global__ __launch_bounds__(256) void k_cert_sweep(CertArgs a, int sweep) {
     const int32_t n = a.g.n;
     const int i = blockIdx.y;
-    if (sweep > 1 && a.more[i] != sweep - 1) return;
+    if ((sweep > 1 && a.more[i] != sweep - 1) || unused(a, i)) return;
     int32_t* par = a.own + (int64_t)i * n;
     const int32_t* next = a.own + (int64_t)(a.kc + i) * n;
     bool apart = false;
@@ -303,6 +342,7 @@ __global__ __launch_bounds__(64) void k_cert_ref(CertArgs a) {
 
 __global__ __launch_bounds__(256) void k_cert_member(CertArgs a) {
     const int32_t n = a.g.n;
+    if (unused(a, 0)) return;
     for (int64_t v0 = (int64_t)blockIdx.x * blockDim.x; v0 < n; v0 += (int64_t)gridDim.x * blockDim.x) {
         const int64_t v = v0 + threadIdx.x;
         bool in = false;
@@ -350,6 +390,7 @@ __device__ void add_marks(int32_t joined, unsigned long long* marks) {
 // million members: 22 us, by compare-and-swap about 100 us.
 __global__ __launch_bounds__(256) void k_cert_join(CertArgs a) {
     const int32_t n = a.g.n;
+    if (unused(a, 0)) return;
     int32_t joined = 0;
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
         const int32_t inst = a.vinst ? a.vinst[v] : 0;
@@ -370,6 +411,7 @@ __global__ __launch_bounds__(256) void k_cert_join(CertArgs a) {
 // own: their unions may move any root)
 __global__ __launch_bounds__(256) void k_cert_near(CertArgs a) {
     const int32_t n = a.g.n;
+    if (unused(a, 0)) return;
     int32_t joined = 0;
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
         const int32_t inst = a.vinst ? a.vinst[v] : 0;
@@ -411,7 +453,7 @@ bool cert_carve(CertArgs& a, void* base, size_t bytes) {
     Arena m;
     m.base = (char*)base;
     m.size = bytes;
-    a.total = m.take<int64_t>(1);
+    a.total = m.take<int64_t>(2);
     a.unit = m.take<int64_t>(k);
     a.count = m.take<int32_t>(k);
     a.ref = m.take<int32_t>(k);
@@ -440,8 +482,8 @@ static bool components(const CertArgs& a, int ny, hipStream_t s) {
 bool certify(const CertArgs& a, hipStream_t s) {
     const int32_t n = a.g.n;
     const int gg = a.ngraphs < 4096 ? a.ngraphs : 4096;
-    if (!fill_i64(a.total, 0, 1, s)) return false;
-    k_cert_level<<<grid_for(n, 256, 1024), 256, 0, s>>>(a);
+    if (!fill_i64(a.total, 0, 2, s)) return false;
+    k_cert_level<<<grid_for(n, 256, 1024) + a.sorted, 256, 0, s>>>(a);
     k_cert_plan<<<grid_for(a.ngraphs, 256), 256, 0, s>>>(a);
     k_cert_rows<<<grid_for(n, ROWS), 256, 0, s>>>(a);
     MC_LAUNCHED("k_cert_rows");

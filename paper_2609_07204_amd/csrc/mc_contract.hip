@@ -115,6 +115,7 @@ __global__ void k_contract_clear(int32_t* gcnt, int32_t* gcur, int32_t n2, int32
     const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i0 == 0) dinfo[0] = 0;
     if (i0 < 2) mcnt[i0] = 0;
+    if (i0 == 2) mcnt[2] = -1;   // giant group
     if (!gcnt) return;
     for (int64_t i = i0; i <= n2; i += (int64_t)gridDim.x * blockDim.x) {
         gcnt[i] = 0;
@@ -153,10 +154,10 @@ constexpr int MERGE_MANY = 32;
 // mstart: the entry prefix over the members; the groups' starts go to gstart
 // (without labels gstart is mstart itself).
 __global__ void k_classify(const int32_t* mstart, const int32_t* __restrict__ vstart, int32_t* gstart, int32_t n2,
-                           int32_t nd_max, int32_t* __restrict__ tsize, int32_t* __restrict__ bigm,
+                           int32_t nd_max, bool by_rows, int32_t* __restrict__ tsize, int32_t* __restrict__ bigm,
                            int32_t* __restrict__ bcur, int32_t* __restrict__ dslot, int32_t* __restrict__ dinfo,
                            int32_t* __restrict__ mlist, int32_t* __restrict__ mcnt, int32_t* __restrict__ ssize,
-                           DGraph dst) {
+                           const int32_t* total, DGraph dst) {
     const int64_t dense_min = n2 / 4;
     for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < n2; g += (int64_t)gridDim.x * blockDim.x) {
         const int32_t gs = mstart[vstart ? vstart[g] : g], ge = mstart[vstart ? vstart[g + 1] : g + 1];
@@ -188,6 +189,13 @@ __global__ void k_classify(const int32_t* mstart, const int32_t* __restrict__ vs
             else mlist[n2 - (base_b + __popcll(mbk & below))] = (int32_t)g;
             tsize[g] = 0;
             bigm[g] = 0;
+        } else if (total && s > MID_MAX && 2 * (int64_t)s >= *total && atomicCAS(&mcnt[2], -1, (int32_t)g) == -1) {
+            // half of all entries: its row is the others' column (k_giant_row)
+            tsize[g] = 0;
+            bigm[g] = 0;
+            bcur[g] = 0;
+            dst.len[g] = 0;
+            dst.deg[g] = 0;
         } else if (s > SMALL_MAX) {
             int32_t d = -1;
             if (s >= dense_min && nd_max > 0) {
@@ -196,7 +204,7 @@ __global__ void k_classify(const int32_t* mstart, const int32_t* __restrict__ vs
             }
             const int64_t t = ((2 * (int64_t)s + TILE_SLOTS - 1) / TILE_SLOTS) * TILE_SLOTS;
             tsize[g] = d >= 0 ? 0 : (int32_t)t;
-            bigm[g] = s;
+            bigm[g] = d >= 0 && by_rows ? 0 : s;   // entries of the tile path
             bcur[g] = 0;
             dst.len[g] = 0;
             dst.deg[g] = 0;
@@ -739,6 +747,101 @@ __global__ __launch_bounds__(BIG_T) void k_big_insert(DGraph src, const int32_t*
     if (pb) prof_add(pb, nin * (L ? 16 : 12));
 }
 
+// Giant groups, row by row in vertex order: a wavefront takes 64 rows, lays
+// their entries side by side (a prefix of the lengths, searched in LDS) and reads
+// target and label of 256 entries at a time, and the weight only of those that
+// leave the group; these are summed in a small table of the workgroup's, or
+// straight in the accumulator when the table has no place for them. Where a
+// contraction joins most of the graph nearly every entry stays inside, and the
+// tile path paid for each as if it did not: a table of 8192 slots cleared and
+// flushed per 4096 entries, with one workgroup a compute unit to hide a dozen
+// dependent loads (Chung-Lu 2^22, 10-core, 51 million entries, 340 groups left:
+// 926 us there, 680 us here; Erdos-Renyi, 300,000 vertices: 103 and 44 us). A row of more than DENSE_ROW entries would keep
+// its wavefront alone at the end, so graphs with such rows take the tile path.
+constexpr int32_t DENSE_ROW = 8192;
+constexpr int DR_T = 256;
+constexpr int DR_SLOTS = 1024;
+constexpr int DR_PER = 4;
+__global__ __launch_bounds__(DR_T) void k_dense_rows(DGraph src, const int32_t* __restrict__ L, int32_t n2,
+                                                    const int32_t* __restrict__ dslot, const int32_t* __restrict__ dinfo,
+                                                    int64_t* __restrict__ dense, unsigned long long* pb) {
+    constexpr int WAVES = DR_T / MC_WAVE;
+    __shared__ int32_t key[DR_SLOTS];
+    __shared__ unsigned long long val[DR_SLOTS];
+    __shared__ int32_t pre[WAVES][MC_WAVE], pos[WAVES][MC_WAVE], grp[WAVES][MC_WAVE], acc[WAVES][MC_WAVE];
+    if (dinfo[0] == 0) return;
+    for (int i = threadIdx.x; i < DR_SLOTS; i += DR_T) { key[i] = -1; val[i] = 0; }
+    __syncthreads();
+    const int lane = lane_id(), wv = threadIdx.x / MC_WAVE;
+    const int32_t n = src.n;
+    int64_t bytes = 0;
+    for (int64_t u0 = ((int64_t)blockIdx.x * WAVES + wv) * MC_WAVE; u0 < n; u0 += (int64_t)gridDim.x * WAVES * MC_WAVE) {
+        const int64_t u = u0 + lane;
+        int32_t l = 0, o = 0, g = -1, d = -1;
+        if (u < n) {
+            g = L ? L[u] : (int32_t)u;
+            d = g >= 0 ? dslot[g] : -1;
+            if (d >= 0) { l = src.len[u]; o = src.off[u]; }
+        }
+        int32_t incl = l;
+        for (int k = 1; k < MC_WAVE; k <<= 1) {
+            const int32_t y = __shfl_up(incl, k, MC_WAVE);
+            if (lane >= k) incl += y;
+        }
+        const int32_t total = __shfl(incl, MC_WAVE - 1, MC_WAVE);
+        bytes += 8 + (l > 0 ? 8 : 0);
+        if (total == 0) continue;
+        wave_sync();
+        pre[wv][lane] = incl - l;
+        pos[wv][lane] = o - (incl - l);
+        grp[wv][lane] = g;
+        acc[wv][lane] = d;
+        wave_sync();
+        for (int32_t e0 = 0; e0 < total; e0 += DR_PER * MC_WAVE) {
+            int32_t row[DR_PER], x[DR_PER], t[DR_PER];
+            int64_t c[DR_PER];
+#pragma unroll
+            for (int q = 0; q < DR_PER; q++) {
+                const int32_t e = e0 + q * MC_WAVE + lane;
+                int32_t r = 0;   // the last row that starts at or before e
+#pragma unroll
+                for (int b = MC_WAVE / 2; b > 0; b >>= 1)
+                    if (pre[wv][r + b] <= e) r += b;
+                row[q] = r;
+                x[q] = e < total ? src.col[pos[wv][r] + e] : -1;
+            }
+#pragma unroll
+            for (int q = 0; q < DR_PER; q++) t[q] = x[q] >= 0 ? (L ? L[x[q]] : x[q]) : grp[wv][row[q]];
+#pragma unroll
+            for (int q = 0; q < DR_PER; q++) {
+                const bool leaves = t[q] >= 0 && t[q] != grp[wv][row[q]];
+                c[q] = leaves ? src.w[pos[wv][row[q]] + e0 + q * MC_WAVE + lane] : 0;
+                bytes += (x[q] >= 0 ? 8 : 0) + (leaves ? 8 : 0);
+            }
+#pragma unroll
+            for (int q = 0; q < DR_PER; q++) {
+                if (c[q] <= 0) continue;   // inside the group, no entry, or of weight zero
+                const int64_t at = (int64_t)acc[wv][row[q]] * n2 + t[q];   // below 2^26 (the accumulators' budget)
+                uint32_t h = hash32((uint32_t)at) & (DR_SLOTS - 1);
+                bool held = false;
+                for (int k = 0; k < 4 && !held; k++, h = (h + 1) & (DR_SLOTS - 1)) {
+                    int32_t old = key[h];
+                    if (old == -1) old = atomicCAS(&key[h], -1, (int32_t)at);
+                    if (old == -1 || old == (int32_t)at) {
+                        atomicAdd(&val[h], (unsigned long long)c[q]);
+                        held = true;
+                    }
+                }
+                if (!held) atomic_add_i64(&dense[at], c[q]);
+            }
+        }
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < DR_SLOTS; i += DR_T)
+        if (key[i] >= 0) atomic_add_i64(&dense[key[i]], (int64_t)val[i]);
+    if (pb) prof_add(pb, bytes);
+}
+
 // One wavefront emits the valid slots of a unit of group g (PERL slots per
 // lane): a wave prefix sum places them, and one atomic per unit reserves
 // their room in the row (one more adds their weight to the degree). The
@@ -854,6 +957,81 @@ __global__ __launch_bounds__(EX_T) void k_big_extract(const int32_t* __restrict_
     dense_extract(dinfo, nd_max, gstart, n2, dense, bcur, dst);
 }
 
+// The row of a group that holds half of all entries, from the column of the
+// others: the graph is symmetric, so what leaves the group is what enters it
+// from the rows that are merged anyway, and the group's own entries, nearly all
+// of which stay inside it, are not read (Chung-Lu 2^22, 10-core, 51 million
+// entries of which 51 million lie inside: 680 us by rows, 90 us). An accumulator or a
+// table is asked for the group, a short row is searched. Finds are collected in
+// LDS and take their places in the row with one atomic for up to GR_BUF of them.
+constexpr int GR_T = 256;
+constexpr int GR_ROWS = 2;       // rows a lane group takes between two looks at the buffer
+constexpr int GR_BUF = 1024;
+__global__ __launch_bounds__(GR_T) void k_giant_row(const int32_t* __restrict__ giant, const int32_t* __restrict__ gstart,
+                                                   const int32_t* __restrict__ tbase, const int32_t* __restrict__ tkey,
+                                                   const int64_t* __restrict__ tval, const int32_t* __restrict__ dslot,
+                                                   const int64_t* __restrict__ dense, int32_t n2,
+                                                   int32_t* __restrict__ bcur, DGraph dst) {
+    constexpr int GROUPS = GR_T / SUB;
+    static_assert(GR_BUF >= 2 * GROUPS * GR_ROWS, "room for a step's finds");
+    __shared__ int32_t bh[GR_BUF];
+    __shared__ int64_t bw[GR_BUF];
+    __shared__ int32_t cnt, at;
+    const int32_t G = *giant;
+    if (G < 0) return;
+    const int32_t g0 = gstart[G], room = gstart[G + 1] - g0;
+    const int sl = threadIdx.x % SUB, grp = threadIdx.x / SUB;
+    int64_t sum = 0;
+    if (threadIdx.x == 0) cnt = 0;
+    const int64_t step = GROUPS * GR_ROWS;
+    for (int64_t h0 = blockIdx.x * step;; h0 += gridDim.x * step) {
+        const bool last = h0 >= n2;
+        __syncthreads();
+        if (cnt > GR_BUF - (int32_t)step || (last && cnt > 0)) {
+            if (threadIdx.x == 0) at = atomicAdd(&bcur[G], cnt);
+            __syncthreads();
+            for (int i = threadIdx.x; i < cnt; i += GR_T) {
+                if (at + i >= room) continue;   // (not in a symmetric graph)
+                dst.col[g0 + at + i] = bh[i];
+                dst.w[g0 + at + i] = bw[i];
+                sum += bw[i];
+            }
+            __syncthreads();
+            if (threadIdx.x == 0) cnt = 0;
+            __syncthreads();
+        }
+        if (last) break;
+        for (int r = 0; r < GR_ROWS; r++) {
+            const int64_t h = h0 + r * GROUPS + grp;
+            if (h >= n2 || h == G) continue;
+            int64_t w = 0;
+            if (dslot[h] >= 0) {
+                if (sl == 0) w = dense[(int64_t)dslot[h] * n2 + G];
+            } else if (tbase[h + 1] > tbase[h]) {
+                if (sl == 0) {
+                    const int32_t b = tbase[h], slots = tbase[h + 1] - b;
+                    uint32_t p = (uint32_t)(((uint64_t)hash32((uint32_t)G) * (uint32_t)slots) >> 32);
+                    int32_t k;
+                    while ((k = tkey[b + p]) != -1 && k != G)   // a table is at most half full
+                        if (++p == (uint32_t)slots) p = 0;
+                    if (k == G) w = tval[b + p];
+                }
+            } else {
+                const int32_t o = dst.off[h], l = dst.len[h];
+                for (int32_t j = sl; j < l; j += SUB)
+                    if (dst.col[o + j] == G) w = dst.w[o + j];
+            }
+            if (w != 0) {
+                const int32_t i = atomicAdd(&cnt, 1);
+                bh[i] = (int32_t)h;
+                bw[i] = w;
+            }
+        }
+    }
+    sum = wave_sum_i64(sum);
+    if (lane_id() == 0 && sum) atomic_add_i64(&dst.deg[G], sum);
+}
+
 // Minimum degree, ties to the smallest vertex, the entry count, the longest
 // row and the maximum degree: per-block partials, then one block folds them;
 // of at most MIN_DEG_ONE vertices one block alone. With bebase the large
@@ -886,6 +1064,29 @@ __device__ __forceinline__ void min_deg_fold(MinDeg& a) {
     if (threadIdx.x < blockDim.x / MC_WAVE) a = part[threadIdx.x];
     wave(a);
 }
+// the input pass's partials, folded by the whole workgroup
+__device__ __forceinline__ void fold_parts(const CanonParts& p, DevScalars* sc) {
+    __shared__ unsigned long long ps[MIN_DEG_T / MC_WAVE];
+    __shared__ int64_t pt[MIN_DEG_T / MC_WAVE];
+    auto add = [](unsigned long long a, unsigned long long b) { return a + b >= WCAP ? WCAP : a + b; };
+    unsigned long long sum = 0;
+    int64_t top = 0;
+    for (int i = threadIdx.x; i < p.count; i += blockDim.x) {
+        sum = add(sum, p.sums[i]);
+        top = p.tops[i] > top ? p.tops[i] : top;
+    }
+    for (int o = MC_WAVE / 2; o > 0; o >>= 1) sum = add(sum, __shfl_xor(sum, o, MC_WAVE));
+    top = wave_max_i64(top);
+    if (lane_id() == 0) { ps[threadIdx.x / MC_WAVE] = sum; pt[threadIdx.x / MC_WAVE] = top; }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (int q = 1; q < (int)blockDim.x / MC_WAVE; q++) {
+        sum = add(sum, ps[q]);
+        top = pt[q] > top ? pt[q] : top;
+    }
+    sc->wmax = top;
+    if (p.check && sum >= WCAP) set_err(sc, MC_E_OVERFLOW);
+}
 __device__ __forceinline__ void min_deg_store(const MinDeg& a, DevScalars* sc) {
     sc->dmin = a.d;
     sc->dmin_arg = a.id;
@@ -896,18 +1097,21 @@ __device__ __forceinline__ void min_deg_store(const MinDeg& a, DevScalars* sc) {
 
 __global__ __launch_bounds__(MIN_DEG_T) void k_min_deg_blocks(const int64_t* __restrict__ deg, int32_t* __restrict__ len,
                                                              int32_t n, const int32_t* __restrict__ bebase,
+                                                             const int32_t* __restrict__ dslot,
+                                                             const int32_t* __restrict__ giant,
                                                              const int32_t* __restrict__ bcur,
                                                              int64_t* __restrict__ rv, int32_t* __restrict__ ri,
                                                              int64_t* __restrict__ rm, int64_t* __restrict__ rd,
-                                                             DevScalars* sc) {
+                                                             CanonParts parts, DevScalars* sc) {
     MinDeg a{0, 0, 0, -1, 0};
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
         const int64_t d = deg[v];
         int32_t l;
-        if (bebase && bebase[v + 1] > bebase[v]) len[v] = l = bcur[v];
+        if (bebase && (bebase[v + 1] > bebase[v] || dslot[v] >= 0 || v == *giant)) len[v] = l = bcur[v];
         else l = len[v];
         min_deg_take(a, d, (int32_t)v, l, d, l);
     }
+    if (gridDim.x == 1 && parts.count > 0) fold_parts(parts, sc);
     min_deg_fold(a);
     if (threadIdx.x != 0) return;
     if (gridDim.x == 1) {
@@ -924,10 +1128,11 @@ __global__ __launch_bounds__(MIN_DEG_T) void k_min_deg_final(const int64_t* __re
                                                             const int32_t* __restrict__ ri,
                                                             const int64_t* __restrict__ rm,
                                                             const int64_t* __restrict__ rd, int nblocks,
-                                                            DevScalars* sc) {
+                                                            CanonParts parts, DevScalars* sc) {
     MinDeg a{0, 0, 0, -1, 0};
     for (int i = threadIdx.x; i < nblocks; i += MIN_DEG_T)
         min_deg_take(a, rv[i], ri[i], rm[i] & 0xffffffff, rd[i], (int32_t)(rm[i] >> 32));
+    if (parts.count > 0) fold_parts(parts, sc);
     min_deg_fold(a);
     if (threadIdx.x == 0) min_deg_store(a, sc);
 }
@@ -979,24 +1184,25 @@ void contract_ws_carve(Arena& a, int32_t n, int64_t cap, ContractWS& ws, bool so
 }
 
 
-static bool min_degree(const DGraph& g, const int32_t* bebase, const int32_t* bcur, ContractWS& ws, DevScalars* sc,
-                       hipStream_t s) {
+static bool min_degree(const DGraph& g, const int32_t* bebase, const int32_t* dslot, const int32_t* giant,
+                       const int32_t* bcur, const CanonParts& parts, ContractWS& ws,
+                       DevScalars* sc, hipStream_t s) {
     const int nb = g.n <= MIN_DEG_ONE ? 1 : grid_for(g.n, 4 * 256, 1024);
-    k_min_deg_blocks<<<nb, nb == 1 ? MIN_DEG_T : 256, 0, s>>>(g.deg, g.len, g.n, bebase, bcur, ws.red_val, ws.red_id,
-                                                             ws.red_m, ws.red_d, sc);
+    k_min_deg_blocks<<<nb, nb == 1 ? MIN_DEG_T : 256, 0, s>>>(g.deg, g.len, g.n, bebase, dslot, giant, bcur, ws.red_val, ws.red_id,
+                                                             ws.red_m, ws.red_d, parts, sc);
     MC_LAUNCHED("k_min_deg_blocks");
     if (nb == 1) return true;
-    k_min_deg_final<<<1, MIN_DEG_T, 0, s>>>(ws.red_val, ws.red_id, ws.red_m, ws.red_d, nb, sc);
+    k_min_deg_final<<<1, MIN_DEG_T, 0, s>>>(ws.red_val, ws.red_id, ws.red_m, ws.red_d, nb, parts, sc);
     MC_LAUNCHED("k_min_deg_final");
     return true;
 }
 
-bool min_degree(const DGraph& g, ContractWS& ws, DevScalars* sc, hipStream_t s) {
-    return min_degree(g, nullptr, nullptr, ws, sc, s);
+bool min_degree(const DGraph& g, ContractWS& ws, DevScalars* sc, hipStream_t s, const CanonParts& parts) {
+    return min_degree(g, nullptr, nullptr, nullptr, nullptr, parts, ws, sc, s);
 }
 
 bool contract(const DGraph& src, const int32_t* L, int32_t n2, DGraph& dst, ContractWS& ws, DevScalars* sc,
-              hipStream_t s) {
+              hipStream_t s, int32_t max_row, bool symmetric) {
     if (ws.sorted) return contract_sorted(src, L, n2, dst, ws, sc, s);
     const int32_t n = src.n;
     dst.n = n2;
@@ -1025,8 +1231,12 @@ bool contract(const DGraph& src, const int32_t* L, int32_t n2, DGraph& dst, Cont
     int32_t* const gstart = L ? ws.gstart : ws.mstart;
     const int64_t ndm = ws.dense_elems / (n2 > 0 ? n2 : 1);
     const int32_t nd_max = (int32_t)(ndm < DENSE_MAX ? ndm : DENSE_MAX);
-    k_classify<<<grid_for(n2, 256), 256, 0, s>>>(ws.mstart, vstart, gstart, n2, nd_max, ws.tsize, ws.bigm, ws.bcur,
-                                                 ws.dslot, ws.dinfo, ws.mlist, ws.mcnt, ws.sstart, dst);
+    // (not without labels, where a group is one row)
+    const bool giant = symmetric && L;
+    const bool by_rows = max_row <= DENSE_ROW && ws.dense_elems < INT32_MAX;
+    k_classify<<<grid_for(n2, 256), 256, 0, s>>>(ws.mstart, vstart, gstart, n2, nd_max, by_rows, ws.tsize, ws.bigm, ws.bcur,
+                                                 ws.dslot, ws.dinfo, ws.mlist, ws.mcnt, ws.sstart, giant ? ws.mstart + n : nullptr,
+                                                 dst);
     MC_LAUNCHED("k_classify");
     // table bases, large-group entry prefix, small-group entry prefix; the
     // groups' cursors are free again
@@ -1056,9 +1266,19 @@ bool contract(const DGraph& src, const int32_t* L, int32_t n2, DGraph& dst, Cont
     k_big_insert<<<4096 * 256 / BIG_T, BIG_T, 0, s>>>(src, L, perm, vstart, ws.mstart, gstart, ws.bigm, ws.tsize, n2, ws.tkey,
                                       ws.tval, ws.dslot, ws.dense, ws.tinfo, dst, prof_dev_bytes(PK_BIG_INSERT));
     MC_LAUNCHED("k_big_insert");
+    if (by_rows) {
+        k_dense_rows<<<grid_for(n, DR_T, 2048), DR_T, 0, s>>>(src, L, n2, ws.dslot, ws.dinfo, ws.dense,
+                                                             prof_dev_bytes(PK_BIG_INSERT));
+        MC_LAUNCHED("k_dense_rows");
+    }
     prof_end(PK_BIG_INSERT, s);
     k_big_extract<<<4096, EX_T, 0, s>>>(ws.tsize, gstart, n2, ws.xg, ws.tkey, ws.tval, ws.dinfo, nd_max, ws.dense,
                                         ws.bcur, dst);
     MC_LAUNCHED("k_big_extract");
-    return min_degree(dst, ws.bigm, ws.bcur, ws, sc, s);
+    if (giant) {
+        k_giant_row<<<grid_for(n2, GR_T / SUB * GR_ROWS, 1024), GR_T, 0, s>>>(ws.mcnt + 2, gstart, ws.tsize, ws.tkey, ws.tval, ws.dslot,
+                                                           ws.dense, n2, ws.bcur, dst);
+        MC_LAUNCHED("k_giant_row");
+    }
+    return min_degree(dst, ws.bigm, ws.dslot, ws.mcnt + 2, ws.bcur, CanonParts(), ws, sc, s);
 }

@@ -40,6 +40,7 @@ struct DevScalars {
     int32_t noncanon;       // 1: the input CSR needs the merging normalisation
     int64_t dmax;           // maximum degree of the graph the last min_degree read
     int32_t max_row;        // longest row of that graph
+    int64_t wmax;           // heaviest entry of the checked input; INT64_MAX: unknown, or a row passes test 2
     int64_t gmax;           // batched form: the largest total degree of one graph of the batch
 };
 
@@ -71,6 +72,10 @@ __device__ __forceinline__ int32_t ld_old(const int32_t* p) {
 __device__ __forceinline__ void st_new(int32_t* p, int32_t v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
+
+// ------------------------------------------------------ input checks
+constexpr unsigned long long WCAP = 1ULL << 62;   // a graph's total weight stays below
+__device__ __forceinline__ void set_err(DevScalars* sc, int32_t code) { atomicCAS(&sc->err, 0, code); }
 
 // ------------------------------------------------------- union-find
 // Concurrent union-find over parent[] with the invariant parent[v] <= v:

@@ -20,6 +20,29 @@ inline int grid_for(int64_t count, int threads, int cap = 8192) {
 }
 
 constexpr int SUB = 16;  // lanes per row for row-wise kernels
+
+// The rows that a group of SUB lanes takes, up to 16 at a time, one lane
+// holding the bounds of each; the entries of one row are read by all of them,
+// and the next row's loads wait for this row's reduction. Such a chain of 16
+// rows hides its bounds' latency where every compute unit has waves to spare;
+// a graph of fewer than 16 * GROUPS rows is spread over more groups of fewer
+// rows (Chung-Lu 60,000: the
+// input pass 46 us with 16 rows a group, 21 us with 2; tests 1 and 2 49 and 23 us).
+constexpr int GROUPS = 1 << 15;   // groups of 8 wavefronts a SIMD
+inline int rows_per_group(int64_t n) {
+    int per = 1;
+    while (per < SUB && (int64_t)per * GROUPS < n) per *= 2;
+    return per;
+}
+inline int group_grid(int64_t n, int per, int cap = 8192) { return grid_for((n + per - 1) / per * SUB, 256, cap); }
+struct GroupRows {
+    int per;
+    int64_t step, first;
+    __device__ __forceinline__ GroupRows(int per_)
+        : per(per_), step((int64_t)gridDim.x * (blockDim.x / SUB) * per_),
+          first(((int64_t)blockIdx.x * (blockDim.x / SUB) + threadIdx.x / SUB) * per_) {}
+};
+
 // test-1 trees that the byte-label linking handles (pr1_trees) and
 // the words of its tree-pair bit matrix
 constexpr int PR1_TREES = 255;
@@ -195,25 +218,25 @@ constexpr int32_t PR_CHUNK = 4096;
 // Algorithmic bytes (profiling): 12 B per entry (col, w) and 16 B per row
 // (off, len, deg) of the rows this kernel tests.
 __global__ __launch_bounds__(256) void k_pr12(DGraph g, const int64_t* lamp, const int32_t* vinst, int32_t* par,
-                                             unsigned long long* marks, uint8_t* flag1, int32_t* ptr2,
+                                             unsigned long long* marks, uint8_t* flag1, int32_t* ptr2, int per,
                                              int32_t* long_list, int32_t* long_cnt, int32_t* first, int32_t* second,
                                              int32_t* heavy_cnt, unsigned long long* pb) {
-    // 16 lanes take 16 consecutive rows: the rows' offsets, lengths,
+    // 16 lanes take 16 rows: the rows' offsets, lengths,
     // degrees and bounds come in one load, each lane then loads up to four
     // entries of a row at once, and the rows' results (test-2 unions
     // included) are written by one lane each, all 16 at the same time
     const int64_t lam0 = *lamp;
-    const int64_t nsub = (int64_t)gridDim.x * (blockDim.x / SUB);
+    const GroupRows at(per);
     const int sl = threadIdx.x % SUB;
     unsigned long long joined = 0;
     int64_t bytes = 0;
-    for (int64_t v0 = ((int64_t)blockIdx.x * (blockDim.x / SUB) + threadIdx.x / SUB) * SUB; v0 < g.n;
-         v0 += nsub * SUB) {
-        const int32_t rows = g.n - v0 < SUB ? (int32_t)(g.n - v0) : SUB;
+    for (int64_t v0 = at.first; v0 < g.n; v0 += at.step) {
+        const int32_t rows = g.n - v0 < per ? (int32_t)(g.n - v0) : per;
+        const bool mine = sl < rows;
         const int32_t mv = (int32_t)v0 + sl;
         int32_t my_o = 0, my_l = 0;
         int64_t my_lam = lam0, my_deg = 0;
-        if (sl < rows) {
+        if (mine) {
             my_o = g.off[mv];
             my_l = g.len[mv];
             my_deg = g.deg[mv];
@@ -277,7 +300,7 @@ __global__ __launch_bounds__(256) void k_pr12(DGraph g, const int64_t* lamp, con
             if (sl == r) { my_bw = bw; my_bx = bx; my_hj = hj; my_hj2 = hj2; my_hn = hn; }
             if (sl == 0) bytes += 16 + 12 * (int64_t)l;
         }
-        if (sl < rows && my_l <= PR_LONG) {
+        if (mine && my_l <= PR_LONG) {
             const bool take = my_bx >= 0 && 2 * my_bw >= my_deg;
             if (ptr2) ptr2[mv] = take ? my_bx : -1;
             first[mv] = my_hj != INT32_MAX ? g.col[my_o + my_hj] : -1;
@@ -299,9 +322,12 @@ __global__ __launch_bounds__(256) void k_pr12(DGraph g, const int64_t* lamp, con
 // Joins u and v as Afforest's link does: climb from their parents and
 // hang the larger root under the smaller with a CAS. Finds write nothing
 // here (a compress pass follows), so many threads climbing one tree do not
-// contend on its nodes. True if this call joined two trees.
+// contend on its nodes; nor do the first reads, which the caches may serve
+// (an old parent is an ancestor, and the CAS tells whether it is still a root):
+// the rows of a hub's neighbours all start at the hub. True if this call
+// joined two trees.
 __device__ __forceinline__ bool uf_link(int32_t* par, int32_t u, int32_t v) {
-    int32_t p1 = ld_acq(&par[u]), p2 = ld_acq(&par[v]);
+    int32_t p1 = ld_old(&par[u]), p2 = ld_old(&par[v]);
     while (p1 != p2) {
         const int32_t high = p1 > p2 ? p1 : p2, low = p1 + p2 - high;
         const int32_t ph = ld_acq(&par[high]);
@@ -376,12 +402,12 @@ __global__ void k_pr1_label(const int32_t* __restrict__ par, const int32_t* __re
 // the test-1 entries of rows with more than two of them (a row with at
 // most two was joined by k_pr1_first) that join two trees, as bits (a < b),
 // from the smaller endpoint or from outside into the sampled tree.
-// As in k_pr12, 16 lanes take 16 consecutive rows, whose metadata comes in
+// As in k_pr12, 16 lanes take 16 rows, whose metadata comes in
 // one load, and each lane keeps four entries and their trees in flight.
 __device__ __forceinline__ void pr1_trees(const DGraph& g, const int64_t* lamp, const int32_t* vinst,
                                           const int32_t* __restrict__ heavy_cnt, const uint8_t* __restrict__ lab8,
                                           const int32_t* __restrict__ tscan, const int32_t* mode, uint32_t* bits,
-                                          unsigned long long* pb) {
+                                          int per, unsigned long long* pb) {
     __shared__ uint32_t sb[PR1_WORDS];
     for (int i = threadIdx.x; i < PR1_WORDS; i += blockDim.x) sb[i] = 0;
     __syncthreads();
@@ -390,16 +416,16 @@ __device__ __forceinline__ void pr1_trees(const DGraph& g, const int64_t* lamp, 
     // smaller endpoint
     const int32_t big = 2 * mode[1] >= 1024 ? tscan[mode[0]] : -1;
     const int64_t lam0 = *lamp;
-    const int64_t nsub = (int64_t)gridDim.x * (blockDim.x / SUB);
+    const GroupRows at(per);
     const int sl = threadIdx.x % SUB;
     int64_t bytes = 0;
-    for (int64_t v0 = ((int64_t)blockIdx.x * (blockDim.x / SUB) + threadIdx.x / SUB) * SUB; v0 < g.n;
-         v0 += nsub * SUB) {
-        const int32_t rows = g.n - v0 < SUB ? (int32_t)(g.n - v0) : SUB;
+    for (int64_t v0 = at.first; v0 < g.n; v0 += at.step) {
+        const int32_t rows = g.n - v0 < per ? (int32_t)(g.n - v0) : per;
+        const bool mine = sl < rows;
         const int32_t mv = (int32_t)v0 + sl;
         int32_t my_o = 0, my_l = 0, my_lv = 0;
         int64_t my_lam = lam0;
-        if (sl < rows) {
+        if (mine) {
             my_lv = lab8[mv];
             if (heavy_cnt[mv] > 2 && my_lv != big) {
                 my_o = g.off[mv];
@@ -407,7 +433,7 @@ __device__ __forceinline__ void pr1_trees(const DGraph& g, const int64_t* lamp, 
                 if (vinst) my_lam = lamp[vinst[mv]];   // bound of the row's instance
             }
         }
-        if (sl == 0) bytes += 5 * (int64_t)rows;   // test-1 count and tree of every row
+        if (mine) bytes += 5;   // test-1 count and tree of every row
         for (int32_t r = 0; r < rows; r++) {
             const int32_t l = __shfl(my_l, r, SUB);
             if (l == 0) continue;
@@ -489,10 +515,10 @@ __global__ __launch_bounds__(256) void k_pr1_rest(DGraph g, const int64_t* lamp,
                                                  const int32_t* __restrict__ heavy_cnt,
                                                  const uint8_t* __restrict__ inbig, const int32_t* __restrict__ snap,
                                                  const int32_t* __restrict__ tscan, const int32_t* mode, uint32_t* bits,
-                                                 unsigned long long* marks, unsigned long long* pb) {
+                                                 int per, unsigned long long* marks, unsigned long long* pb) {
     const int32_t T = tscan[g.n];
     if (T <= 1) return;
-    if (T <= PR1_TREES) pr1_trees(g, lamp, vinst, heavy_cnt, inbig, tscan, mode, bits, pb);
+    if (T <= PR1_TREES) pr1_trees(g, lamp, vinst, heavy_cnt, inbig, tscan, mode, bits, per, pb);
     else pr1_snap(g, lamp, vinst, par, heavy_cnt, inbig, snap, marks, pb);
 }
 
@@ -844,28 +870,6 @@ __global__ void k_csr_to_padded(const int32_t* rp, int32_t n, int32_t* off, int3
     }
 }
 
-constexpr unsigned long long WCAP = 1ULL << 62;
-
-__device__ void set_err(DevScalars* sc, int32_t code) { atomicCAS(&sc->err, 0, code); }
-
-// saturating sum of the block partials (each at most WCAP, so a pairwise
-// sum fits in 64 bits before it saturates)
-__global__ __launch_bounds__(256) void k_validate_sum(const unsigned long long* part, int nb, DevScalars* sc) {
-    __shared__ unsigned long long bs[256];
-    unsigned long long t = 0;
-    for (int k = threadIdx.x; k < nb; k += 256) { t += part[k]; if (t >= WCAP) t = WCAP; }
-    bs[threadIdx.x] = t;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if (threadIdx.x < o) {
-            unsigned long long u = bs[threadIdx.x] + bs[threadIdx.x + o];
-            bs[threadIdx.x] = u >= WCAP ? WCAP : u;
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0 && bs[0] >= WCAP) set_err(sc, MC_E_OVERFLOW);
-}
-
 // Normalisation fast path: a row whose targets strictly increase, with no
 // loop and only positive weights, is already in normal form (a simple
 // graph, nothing to merge). Writes len and the degrees of every row, and
@@ -873,97 +877,195 @@ __global__ __launch_bounds__(256) void k_validate_sum(const unsigned long long* 
 // same pass checks the input: row bounds within
 // [0, nnz] and non-decreasing (a row that fails is not read), targets in
 // range, weights non-negative, and the weights' sum, saturated at WCAP, into
-// part[blockIdx.x] for k_validate_sum. With lp1, the same pass writes the
+// sums[block] (min_degree folds them). With lp1, the same pass writes the
 // first label-propagation round from singleton labels (Section 2.1
 // heuristic): every row's heaviest neighbour, the smallest on ties, or the
 // row itself when it has none; it is that round's result when the input is
-// in normal form (the caller drops it otherwise).
+// in normal form (the caller drops it otherwise). What tests 1 and 2 need
+// to know of a row is then known too: tops[block] is the heaviest entry of the
+// block's rows, or INT64_MAX where a row passes test 2 (2 w >= degree).
+//
+// Rows of more than CANON_LONG entries go through a list to k_canon_long, a
+// workgroup each: 16 lanes take 64 entries a round trip, and the hubs of
+// power-law graphs lie side by side.
+constexpr int32_t CANON_LONG = 512;
+constexpr int CANON_BLOCKS = 4096;
+constexpr int CANON_LBLOCKS = 512;
+constexpr int CANON_LT = 512;
+
+struct CanonRow {
+    int64_t d, bw;             // degree, heaviest entry
+    unsigned long long wsum;   // weights so far, this row's and those before
+    int32_t bx;                // its target, INT32_MAX: none
+    bool bad;
+};
+__device__ __forceinline__ CanonRow canon_row(unsigned long long wsum) { return {0, 0, wsum, INT32_MAX, false}; }
+// four entries j0 + u * step of row v = [o, o + l)
+__device__ __forceinline__ void canon_take(CanonRow& R, const int32_t* __restrict__ col, const int64_t* __restrict__ w,
+                                           int32_t v, int32_t o, int32_t l, int32_t j0, int32_t step, int32_t n,
+                                           DevScalars* sc) {
+    int32_t x[4], xp[4];
+    int64_t c[4];
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+        const int32_t j = j0 + u * step;
+        x[u] = j < l ? col[o + j] : INT32_MAX;
+        xp[u] = j > 0 && j < l ? col[o + j - 1] : -1;
+        c[u] = j < l ? w[o + j] : 1;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+        if (j0 + u * step >= l) continue;
+        R.d += c[u];
+        R.bad |= x[u] == v || c[u] <= 0 || xp[u] >= x[u];
+        if (x[u] != v && c[u] > 0 && (c[u] > R.bw || (c[u] == R.bw && x[u] < R.bx))) {
+            R.bw = c[u];
+            R.bx = x[u];
+        }
+        if (sc) {
+            if (x[u] < 0 || x[u] >= n || c[u] < 0) set_err(sc, MC_E_BAD_GRAPH);
+            if (c[u] > 0) {
+                R.wsum += (unsigned long long)c[u];
+                if (R.wsum >= WCAP || (unsigned long long)c[u] >= WCAP) R.wsum = WCAP;
+            }
+        }
+    }
+}
+// degree and heaviest neighbour over the lanes of a group
+__device__ __forceinline__ void canon_fold(CanonRow& R, int lanes, bool heaviest) {
+    for (int k = lanes / 2; k > 0; k >>= 1) R.d += __shfl_xor(R.d, k, lanes);
+    if (!heaviest) return;
+    for (int k = lanes / 2; k > 0; k >>= 1) {
+        const int64_t w2 = __shfl_xor(R.bw, k, lanes);
+        const int32_t x2 = __shfl_xor(R.bx, k, lanes);
+        if (w2 > R.bw || (w2 == R.bw && x2 < R.bx)) { R.bw = w2; R.bx = x2; }
+    }
+}
+// the workgroup's weight sum (each at most WCAP, so a sum of two fits) and top entry
+__device__ __forceinline__ void canon_parts(unsigned long long wsum, int64_t top, unsigned long long* sums, int64_t* tops) {
+    __shared__ unsigned long long ps[1024 / MC_WAVE];
+    __shared__ int64_t pt[1024 / MC_WAVE];
+    for (int k = MC_WAVE / 2; k > 0; k >>= 1) {
+        wsum += __shfl_xor(wsum, k, MC_WAVE);
+        if (wsum >= WCAP) wsum = WCAP;
+    }
+    top = wave_max_i64(top);
+    if (lane_id() == 0) { ps[threadIdx.x / MC_WAVE] = wsum; pt[threadIdx.x / MC_WAVE] = top; }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int q = 1; q < (int)blockDim.x / MC_WAVE; q++) {
+            wsum += ps[q];
+            if (wsum >= WCAP) wsum = WCAP;
+            top = pt[q] > top ? pt[q] : top;
+        }
+        *sums = wsum;
+        *tops = top;
+    }
+}
+// what a row means to tests 1 and 2
+__device__ __forceinline__ int64_t canon_top(const CanonRow& R) {
+    return R.bx != INT32_MAX && 2 * R.bw >= R.d ? INT64_MAX : R.bw;
+}
+
 __global__ __launch_bounds__(256) void k_canon(const int32_t* __restrict__ rp, const int32_t* __restrict__ col,
                                               const int64_t* __restrict__ w, int32_t n, int32_t nnz,
                                               int32_t* __restrict__ len, int64_t* __restrict__ deg,
-                                              int32_t* noncanon, DevScalars* sc, unsigned long long* part,
-                                              int32_t* __restrict__ lp1) {
-    // 16 lanes take 16 consecutive rows: their offsets come in one load,
-    // and each lane then loads up to four entries of a row at once
-    const int64_t nsub = (int64_t)gridDim.x * (blockDim.x / SUB);
+                                              int32_t* noncanon, DevScalars* sc, int32_t* __restrict__ lp1, int per,
+                                              int32_t* __restrict__ long_list, int32_t* long_cnt,
+                                              unsigned long long* sums, int64_t* tops) {
+    // 16 lanes take 16 rows: their offsets come in one load, and each lane
+    // then loads up to four entries of a row at once
+    const GroupRows at(per);
     const int sl = threadIdx.x % SUB;
     bool bad_any = false;
     unsigned long long wsum = 0;
+    int64_t top = lp1 ? 0 : INT64_MAX;
     if (sc && blockIdx.x == 0 && threadIdx.x == 0 && (rp[0] != 0 || rp[n] != nnz)) set_err(sc, MC_E_BAD_GRAPH);
-    for (int64_t v0 = ((int64_t)blockIdx.x * (blockDim.x / SUB) + threadIdx.x / SUB) * SUB; v0 < n; v0 += nsub * SUB) {
-        int32_t my_o = v0 + sl <= n ? rp[v0 + sl] : 0;
-        int32_t my_e = v0 + sl < n ? rp[v0 + sl + 1] : my_o;
-        if (sc && v0 + sl < n && (my_o < 0 || my_e < my_o || my_e > nnz)) {
+    for (int64_t v0 = at.first; v0 < n; v0 += at.step) {
+        const int32_t rows = n - v0 < per ? (int32_t)(n - v0) : per;
+        const bool mine = sl < rows;
+        const int32_t mv = (int32_t)v0 + sl;
+        int32_t my_o = mine ? rp[mv] : 0;
+        int32_t my_e = mine ? rp[mv + 1] : 0;
+        if (sc && mine && (my_o < 0 || my_e < my_o || my_e > nnz)) {
             set_err(sc, MC_E_BAD_GRAPH);
             my_e = my_o = 0;
         }
         int64_t my_d = 0;
         int32_t my_lp = INT32_MAX;
-        const int32_t rows = n - v0 < SUB ? (int32_t)(n - v0) : SUB;
+        const bool is_long = my_e - my_o > CANON_LONG;
+        if (is_long) long_list[atomicAdd(long_cnt, 1)] = mv;
         for (int32_t r = 0; r < rows; r++) {
             const int32_t v = (int32_t)v0 + r;
             const int32_t o = __shfl(my_o, r, SUB), e = __shfl(my_e, r, SUB), l = e - o;
-            int64_t d = 0;
-            int64_t bw = 0;
-            int32_t bx = INT32_MAX;
-            bool bad = false;
-            for (int32_t j0 = 0; j0 < l; j0 += 4 * SUB) {
-                int32_t x[4], xp[4];
-                int64_t c[4];
-#pragma unroll
-                for (int u = 0; u < 4; u++) {
-                    const int32_t j = j0 + u * SUB + sl;
-                    x[u] = j < l ? col[o + j] : INT32_MAX;
-                    xp[u] = j > 0 && j < l ? col[o + j - 1] : -1;
-                    c[u] = j < l ? w[o + j] : 1;
-                }
-#pragma unroll
-                for (int u = 0; u < 4; u++) {
-                    if (j0 + u * SUB + sl < l) {
-                        d += c[u];
-                        bad |= x[u] == v || c[u] <= 0 || xp[u] >= x[u];
-                        if (x[u] != v && c[u] > 0 && (c[u] > bw || (c[u] == bw && x[u] < bx))) {
-                            bw = c[u];
-                            bx = x[u];
-                        }
-                        if (sc) {
-                            if (x[u] < 0 || x[u] >= n || c[u] < 0) set_err(sc, MC_E_BAD_GRAPH);
-                            if (c[u] > 0) {
-                                wsum += (unsigned long long)c[u];
-                                if (wsum >= WCAP || (unsigned long long)c[u] >= WCAP) wsum = WCAP;
-                            }
-                        }
-                    }
-                }
-            }
-            for (int k = SUB / 2; k > 0; k >>= 1) d += __shfl_xor(d, k, SUB);
+            if (l > CANON_LONG) continue;
+            CanonRow R = canon_row(wsum);
+            for (int32_t j0 = 0; j0 < l; j0 += 4 * SUB) canon_take(R, col, w, v, o, l, j0 + sl, SUB, n, sc);
+            canon_fold(R, SUB, lp1 != nullptr);
+            wsum = R.wsum;
+            if (sl == r) { my_d = R.d; my_lp = R.bx; }
+            bad_any |= R.bad;
             if (lp1) {
-                for (int k = SUB / 2; k > 0; k >>= 1) {
-                    const int64_t w2 = __shfl_xor(bw, k, SUB);
-                    const int32_t x2 = __shfl_xor(bx, k, SUB);
-                    if (w2 > bw || (w2 == bw && x2 < bx)) { bw = w2; bx = x2; }
-                }
+                const int64_t t = canon_top(R);
+                top = t > top ? t : top;
             }
-            if (sl == r) { my_d = d; my_lp = bx; }
-            bad_any |= bad;
         }
-        if (v0 + sl < n) {
-            len[v0 + sl] = my_e - my_o;
-            deg[v0 + sl] = my_d;
-            if (lp1) lp1[v0 + sl] = my_lp != INT32_MAX ? my_lp : (int32_t)(v0 + sl);
+        if (mine) {
+            len[mv] = my_e - my_o;
+            if (!is_long) {
+                deg[mv] = my_d;
+                if (lp1) lp1[mv] = my_lp != INT32_MAX ? my_lp : mv;
+            }
         }
     }
     if (__ballot(bad_any) && lane_id() == 0 && ld_acq(noncanon) == 0) st_rel(noncanon, 1);
-    if (sc) {
-        __shared__ unsigned long long bs[256];
-        bs[threadIdx.x] = wsum;
+    canon_parts(wsum, top, sums + blockIdx.x, tops + blockIdx.x);
+}
+
+// the long rows, one workgroup each
+__global__ __launch_bounds__(CANON_LT) void k_canon_long(const int32_t* __restrict__ rp, const int32_t* __restrict__ col,
+                                                        const int64_t* __restrict__ w, int32_t n,
+                                                        int64_t* __restrict__ deg, int32_t* noncanon, DevScalars* sc,
+                                                        int32_t* __restrict__ lp1,
+                                                        const int32_t* __restrict__ long_list, const int32_t* long_cnt,
+                                                        unsigned long long* sums, int64_t* tops) {
+    constexpr int WAVES = CANON_LT / MC_WAVE;
+    __shared__ CanonRow part[WAVES];
+    const int32_t nl = *long_cnt;
+    bool bad_any = false;
+    unsigned long long wsum = 0;
+    int64_t top = lp1 ? 0 : INT64_MAX;
+    for (int32_t i = blockIdx.x; i < nl; i += gridDim.x) {
+        const int32_t v = long_list[i], o = rp[v], l = rp[v + 1] - o;
+        CanonRow R = canon_row(wsum);
+        for (int32_t j0 = threadIdx.x; j0 < l; j0 += 4 * CANON_LT) canon_take(R, col, w, v, o, l, j0, CANON_LT, n, sc);
+        wsum = R.wsum;
+        bad_any |= R.bad;
+        canon_fold(R, MC_WAVE, true);
+        if (lane_id() == 0) part[threadIdx.x / MC_WAVE] = R;
         __syncthreads();
-        if (threadIdx.x == 0) {
-            unsigned long long t = 0;
-            for (int k = 0; k < 256; k++) { t += bs[k]; if (t >= WCAP) t = WCAP; }
-            part[blockIdx.x] = t;
+        if (threadIdx.x < MC_WAVE) {
+            R = canon_row(0);
+            if (threadIdx.x < WAVES) R = part[threadIdx.x];
+            canon_fold(R, MC_WAVE, true);
+            if (threadIdx.x == 0) {
+                deg[v] = R.d;
+                if (lp1) {
+                    lp1[v] = R.bx != INT32_MAX ? R.bx : v;
+                    const int64_t t = canon_top(R);
+                    top = t > top ? t : top;
+                }
+            }
         }
+        __syncthreads();
     }
+    if (__ballot(bad_any) && lane_id() == 0 && ld_acq(noncanon) == 0) st_rel(noncanon, 1);
+    canon_parts(wsum, top, sums + blockIdx.x, tops + blockIdx.x);
+}
+
+__global__ void k_canon_clear(int32_t* noncanon, int32_t* long_cnt) {
+    *noncanon = 0;
+    *long_cnt = 0;
 }
 
 }  // namespace
@@ -1031,7 +1133,8 @@ bool pr12(const DGraph& g, const int64_t* lam, int32_t* parent, unsigned long lo
     k_pr12_clear<<<1, 1024, 0, s>>>(w.counters, w.spread, w.tbits);
     MC_LAUNCHED("k_pr12_clear");
     prof_begin(PK_PR12, s);
-    k_pr12<<<grid_for(g.n, 256), 256, 0, s>>>(g, lam, vinst, parent, w.spread, flag1, ptr2, w.long_list,
+    const int per = rows_per_group(g.n);
+    k_pr12<<<group_grid(g.n, per), 256, 0, s>>>(g, lam, vinst, parent, w.spread, flag1, ptr2, per, w.long_list,
                                                             w.counters, w.first, w.second, w.heavy,
                                                             prof_dev_bytes(PK_PR12));
     MC_LAUNCHED("k_pr12");
@@ -1057,7 +1160,7 @@ bool pr12(const DGraph& g, const int64_t* lam, int32_t* parent, unsigned long lo
     MC_LAUNCHED("k_pr1_label");
     prof_begin(PK_PR1_REST, s);
     k_pr1_rest<<<grid_for((int64_t)g.n * SUB, 256), 256, 0, s>>>(g, lam, vinst, parent, w.heavy, w.inbig, w.snap,
-                                                                w.tscan, w.mode, w.tbits, w.spread,
+                                                                w.tscan, w.mode, w.tbits, per, w.spread,
                                                                 prof_dev_bytes(PK_PR1_REST));
     MC_LAUNCHED("k_pr1_rest");
     prof_end(PK_PR1_REST, s);
@@ -1142,16 +1245,27 @@ bool csr_to_padded(const int32_t* row_ptr, int32_t n, int32_t* off, int32_t* len
 }
 
 bool canon_check(const int32_t* row_ptr, const int32_t* col, const int64_t* w, int32_t n, int32_t nnz, int32_t* len,
-                 int64_t* deg, int32_t* noncanon, DevScalars* sc, unsigned long long* part, int32_t* lp1,
+                 int64_t* deg, int32_t* noncanon, DevScalars* sc, int32_t* lp1, ContractWS& cw, CanonParts& parts,
                  hipStream_t s) {
-    if (!fill_i32(noncanon, 0, 1, s)) return false;
-    // with checks, at most 1024 blocks (the partial sums of the weights)
-    const int nb = grid_for(((int64_t)n + SUB - 1) / SUB * SUB, 256, sc ? 1024 : 8192);
-    k_canon<<<nb, 256, 0, s>>>(row_ptr, col, w, n, nnz, len, deg, noncanon, sc, part, lp1);
+    // the contraction's scratch is free here: its permutation lists the long
+    // rows, its dense accumulators (of at least 4 (n + 1) words) take the
+    // blocks' partials; a small graph's few go to the fold's own
+    int32_t *const list = cw.perm, *const cnt = cw.mcnt + 3;
+    const bool small = 4 * ((int64_t)n + 1) < 2 * (CANON_BLOCKS + CANON_LBLOCKS);
+    const int per = rows_per_group(n), nb = group_grid(n, per, CANON_BLOCKS);
+    const int nl = (int)std::min<int64_t>(small ? 256 : CANON_LBLOCKS, nnz / CANON_LONG);   // blocks for long rows
+    parts.sums = small ? (unsigned long long*)cw.red_val : (unsigned long long*)cw.dense;
+    parts.tops = small ? cw.red_d : cw.dense + CANON_BLOCKS + CANON_LBLOCKS;
+    parts.count = nb + nl;
+    k_canon_clear<<<1, 1, 0, s>>>(noncanon, cnt);
+    MC_LAUNCHED("k_canon_clear");
+    k_canon<<<nb, 256, 0, s>>>(row_ptr, col, w, n, nnz, len, deg, noncanon, sc, lp1, per, list, cnt, parts.sums,
+                               parts.tops);
     MC_LAUNCHED("k_canon");
-    if (sc) {
-        k_validate_sum<<<1, 256, 0, s>>>(part, nb, sc);
-        MC_LAUNCHED("k_validate_sum");
+    if (nl > 0) {
+        k_canon_long<<<nl, CANON_LT, 0, s>>>(row_ptr, col, w, n, deg, noncanon, sc, lp1, list, cnt, parts.sums + nb,
+                                             parts.tops + nb);
+        MC_LAUNCHED("k_canon_long");
     }
     return true;
 }

@@ -146,8 +146,10 @@ inline DGraph entries_view(const DGraph& g, int64_t m) {
     if (m >= 0 && m < v.cap) v.cap = m;
     return v;
 }
+// max_row: no row of src is longer, if known; symmetric: each entry has its
+// reverse.
 bool contract(const DGraph& src, const int32_t* L, int32_t n2, DGraph& dst, ContractWS& ws,
-              DevScalars* sc, hipStream_t s);
+              DevScalars* sc, hipStream_t s, int32_t max_row = INT32_MAX, bool symmetric = false);
 
 // contract() by a radix sort of the contracted entries and a segmented
 // reduction (rows sorted by target); needs ws.sw.
@@ -156,7 +158,16 @@ bool contract_sorted(const DGraph& src, const int32_t* L, int32_t n2, DGraph& ds
 
 // Minimum degree of g (ties: smallest vertex) into sc->dmin / dmin_arg, its
 // entry count into sc->m2 and its maximum degree into sc->dmax.
-bool min_degree(const DGraph& g, ContractWS& ws, DevScalars* sc, hipStream_t s);
+// With parts, what the input pass left of every workgroup is folded too: the
+// heaviest entry to sc->wmax and, if check, a total weight of 2^62 or more to
+// sc->err.
+struct CanonParts {
+    unsigned long long* sums = nullptr;
+    int64_t* tops = nullptr;
+    int count = 0;
+    bool check = false;
+};
+bool min_degree(const DGraph& g, ContractWS& ws, DevScalars* sc, hipStream_t s, const CanonParts& parts = CanonParts());
 
 // --------------------------------------------------------- union-find
 bool uf_init(int32_t* parent, int32_t n, hipStream_t s);
@@ -212,6 +223,7 @@ bool pr12(const DGraph& g, const int64_t* lam, int32_t* parent, unsigned long lo
 // voff[i+1]), vinst their graph, and only graphs with active[i] take part.
 constexpr int CERT_KMAX = 32;
 constexpr int CERT_KMIN = 8;
+constexpr int32_t CERT_PROBE_N = 1 << 15;   // smaller graphs are not probed first
 struct CertArgs {
     DGraph g;
     const int64_t* lam;      // [ngraphs]
@@ -223,6 +235,7 @@ struct CertArgs {
     unsigned long long* marks;
     // carved by cert_carve
     int32_t kc;              // subgraphs there is room for
+    bool sorted;          // single form: the rows are sorted (a normal input)
     int64_t* total;          // sum of the degrees
     int64_t* unit;           // [ngraphs] c
     int32_t* count;          // [ngraphs] k <= kc
@@ -492,12 +505,13 @@ bool csr_to_padded(const int32_t* row_ptr, int32_t n, int32_t* off, int32_t* len
 // increasing, no loop, positive weights). With sc (device inputs) the same
 // pass checks the input into sc->err as an mc_status code: row bounds in
 // [0, nnz] and non-decreasing (a row that fails is not read), targets in
-// range, non-negative weights, total weight below 2^62 (part: 1024 partial
-// sums). With lp1 (n entries) it also writes every row's heaviest
+// range, non-negative weights, and the blocks' partial sums of the weights
+// for min_degree to fold. With lp1 (n entries) it also writes every row's heaviest
 // neighbour (smallest on ties; the row itself when it has none): the first
 // label-propagation round from singleton labels when the input is normal.
+// cw's permutation, dense accumulators and fold partials are its scratch.
 bool canon_check(const int32_t* row_ptr, const int32_t* col, const int64_t* w, int32_t n, int32_t nnz, int32_t* len,
-                 int64_t* deg, int32_t* noncanon, DevScalars* sc, unsigned long long* part, int32_t* lp1,
+                 int64_t* deg, int32_t* noncanon, DevScalars* sc, int32_t* lp1, ContractWS& cw, CanonParts& parts,
                  hipStream_t s);
 
 // mc_mincut of a graph that check_host_csr has passed
