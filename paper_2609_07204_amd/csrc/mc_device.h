@@ -41,6 +41,8 @@ struct DevScalars {
     int64_t dmax;           // maximum degree of the graph the last min_degree read
     int32_t max_row;        // longest row of that graph
     int64_t wmax;           // heaviest entry of the checked input; INT64_MAX: unknown, or a row passes test 2
+    int64_t fin_lam;        // finisher: bound out
+    int32_t fin[4];         // finisher: dropped, rounds, error, work-queue ticket
     int64_t gmax;           // batched form: the largest total degree of one graph of the batch
 };
 

@@ -44,6 +44,33 @@ __global__ void k_reset_round(DevScalars* sc) {
     sc->best_pass = -1;
     sc->best_alpha = INT64_MAX;
 }
+// a round's start: counters cleared, every vertex its own tree; lam: the bound, if it is set anew
+__global__ void k_round_start(DevScalars* sc, int64_t lam, int32_t* parent, int32_t n) {
+    const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i0 == 0) {
+        sc->marks_pr = sc->marks_cf = sc->marks_tri = sc->marks_cert = 0;
+        sc->err = 0;
+        sc->best_pass = -1;
+        sc->best_alpha = INT64_MAX;
+        if (lam >= 0) sc->lam = lam;
+    }
+    for (int64_t v = i0; v < n; v += (int64_t)gridDim.x * blockDim.x) parent[v] = (int32_t)v;
+}
+// A solve's start: every input vertex its own, and the vertex of smallest
+// degree as the bound and the side. Small solves are bound by launches and
+// waits: this stands for four launches, k_round_start for two or three a round,
+// and the finisher's results come with the scalars instead of two copies to
+// pageable memory (planted, 128 vertices, host input: 256 and 208 us).
+__global__ void k_solve_start(DevScalars* sc, int32_t* map0, int32_t* claim, uint8_t* side, int32_t n) {
+    const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int32_t arg = sc->dmin_arg;
+    if (i0 == 0) sc->lam = sc->dmin;
+    for (int64_t v = i0; v < n; v += (int64_t)gridDim.x * blockDim.x) {
+        map0[v] = (int32_t)v;
+        claim[v] = 0;
+        side[v] = v == arg;
+    }
+}
 __global__ void k_uf_pairs(const int32_t* a, const int32_t* b, int64_t np, int32_t* par) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < np; i += (int64_t)gridDim.x * blockDim.x)
         uf_union(par, a[i], b[i]);
@@ -389,8 +416,6 @@ struct SolveWS {
     DevScalars* sc = nullptr;
     unsigned long long* vpart = nullptr;
     int32_t* vpart_i32() { return reinterpret_cast<int32_t*>(vpart); }
-    int64_t* fin64 = nullptr;     // [2] finisher: bound in, bound out
-    int32_t* fin32 = nullptr;     // [4] finisher: dropped, rounds, error, work-queue ticket
     int32_t* fx_col[2] = {nullptr, nullptr};   // finisher scratch graphs
     int64_t* fx_w[2] = {nullptr, nullptr};
 };
@@ -492,8 +517,6 @@ void carve(Arena& a, int32_t n, int64_t cap, int32_t passes, int32_t ppasses, in
     w.calen = a.take<int32_t>(1);
     w.clamout = a.take<int64_t>(1);
     w.vpart = a.take<unsigned long long>(1024);
-    w.fin64 = a.take<int64_t>(2);
-    w.fin32 = a.take<int32_t>(4);
     // a simple graph of at most FIN_N vertices has at most FIN_N (FIN_N - 1)
     // entries, and never more than the input
     const int64_t fx = std::min<int64_t>(cap, (int64_t)FIN_N * (FIN_N - 1)) + 1;
@@ -862,11 +885,11 @@ static mc_status finish(Solver& S, DGraph* cur, int32_t round) {
     fa.gvoff = nullptr;
     fa.glist = nullptr;
     fa.lam_in = &w.sc->lam;
-    fa.lam_out = w.fin64;
-    fa.dropped = w.fin32;
-    fa.rounds = w.fin32 + 1;
-    fa.err = w.fin32 + 2;
-    fa.qnext = w.fin32 + 3;
+    fa.lam_out = &w.sc->fin_lam;
+    fa.dropped = w.sc->fin;
+    fa.rounds = w.sc->fin + 1;
+    fa.err = w.sc->fin + 2;
+    fa.qnext = w.sc->fin + 3;
     fa.fside = w.flag8;
     for (int q = 0; q < 2; q++) {
         fa.xcol[q] = w.fx_col[q];
@@ -875,20 +898,17 @@ static mc_status finish(Solver& S, DGraph* cur, int32_t round) {
     fa.xwindow = 0;
     fa.seed = S.c->opt.seed ^ ((uint64_t)(uint32_t)round << 20);
     fa.qmode = S.c->opt.deterministic ? 2 : S.c->opt.queue;
-    if (!fill_i32(w.fin32, 0, 4, s) || !finish_graphs(fa, 1, S.c->cus, s)) return MC_E_DEVICE;
-    int64_t lam_out = 0;
-    int32_t r32[4] = {0, 0, 0, 0};
-    if (hipMemcpyAsync(&lam_out, w.fin64, sizeof(int64_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipMemcpyAsync(r32, w.fin32, sizeof(r32), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
-        return fail(MC_E_DEVICE, "finisher: readback failed");
+    if (!fill_i32(w.sc->fin, 0, 4, s) || !finish_graphs(fa, 1, S.c->cus, s) || !S.readback())
+        return fail(MC_E_DEVICE, "finisher: launch or readback failed");
+    const int64_t lam_out = S.c->hsc->fin_lam;
+    const int32_t* r32 = S.c->hsc->fin;
     if (r32[2] != 0) return fail(MC_E_DEVICE, "finisher: a graph could not finish (code " + std::to_string(r32[2]) + ")");
     if (r32[0] && lam_out < S.lam) {
         if (!side_from_flag(w.side, w.map0, S.n0, w.flag8, s)) return MC_E_DEVICE;
         if (!S.set_lam(lam_out)) return MC_E_DEVICE;
     }
-    S.stats.rounds += r32[1];
-    S.stats.finish_rounds += r32[1];
+    S.stats.rounds += S.c->hsc->fin[1];
+    S.stats.finish_rounds += S.c->hsc->fin[1];
     return MC_OK;
 }
 
@@ -941,9 +961,8 @@ static mc_status threshold_bound(Solver& S, int32_t round) {
     mc_status err = MC_OK;
     while (cur->n > 2 && (cur == &w.g[0] || cur->n > finish_max_n(S.c))) {
         const int32_t n = cur->n;
-        k_reset_round<<<1, 1, 0, s>>>(w.sc);
-        k_set_lam<<<1, 1, 0, s>>>(w.sc, target);
-        if (!uf_init(w.parent, n, s) ||
+        k_round_start<<<grid_for(n, 256), 256, 0, s>>>(w.sc, target, w.parent, n);
+        if (!mc_hip_ok(hipGetLastError(), "k_round_start") ||
             (!S.tests12_idle(*cur, target) &&
              !pr12(*cur, &w.sc->lam, w.parent, &w.sc->marks_pr, nullptr, nullptr, w.prw, s, nullptr, max_row)) ||
             !S.certificates(*cur, w.g[nxt_idx], false) || !uf_labels(w.parent, n, w.L, w.flag, w.cw.scan_tmp, w.sc, s) ||
@@ -989,8 +1008,8 @@ static mc_status exact_rounds(Solver& S, int src) {
         DGraph* nxt = &w.g[nxt_idx];
         const int32_t n = cur->n;
         prof_round_begin(S.in_heuristic ? 2 : 0, n, S.cur_m, s);
-        k_reset_round<<<1, 1, 0, s>>>(w.sc);
-        if (!uf_init(w.parent, n, s)) return MC_E_DEVICE;
+        k_round_start<<<grid_for(n, 256), 256, 0, s>>>(w.sc, -1, w.parent, n);
+        if (!mc_hip_ok(hipGetLastError(), "k_round_start")) return MC_E_DEVICE;
         // in the automatic mode tests 3 and 4 wait until a pass of CAPFOREST
         // is to be saved
         const bool idle = S.tests12_idle(*cur, S.lam) && !S.tri();
@@ -1203,6 +1222,14 @@ static mc_status exact_rounds(Solver& S, int src) {
     return MC_OK;
 }
 
+// map, claims, first bound and first side, from the minimum degree on the
+// device (before it is read back: the side of a malformed input is not used)
+static bool solve_start(Solver& S, int32_t n) {
+    SolveWS& w = S.w;
+    k_solve_start<<<grid_for(n, 256), 256, 0, S.s>>>(w.sc, w.map0, w.claim, w.side, n);
+    return mc_hip_ok(hipGetLastError(), "k_solve_start");
+}
+
 // lambda = 0 iff the input is disconnected. g is the input or a contraction
 // of it that merged vertices of one component only (map0 takes input
 // vertices to g's vertices): such a contraction keeps every component
@@ -1380,7 +1407,7 @@ static mc_status solve(mc_ctx* c, const mc_csr* g, void* dev_ws, size_t ws_bytes
     parts.check = !host_input;
     if (!canon_check(rp, col, wt, n, (int32_t)nnz, w.g[0].len, w.g[0].deg, &w.sc->noncanon,
                      host_input ? nullptr : w.sc, run_heuristic ? w.lab2 : nullptr, w.cw, parts, s) ||
-        !min_degree(w.g[0], w.cw, w.sc, s, parts) || !S.readback())
+        !min_degree(w.g[0], w.cw, w.sc, s, parts) || !solve_start(S, n) || !S.readback())
         return MC_E_DEVICE;
     if (c->hsc->err != 0)
         return fail((mc_status)c->hsc->err, c->hsc->err == MC_E_OVERFLOW ? "total weight must be below 2^62"
@@ -1398,10 +1425,9 @@ static mc_status solve(mc_ctx* c, const mc_csr* g, void* dev_ws, size_t ws_bytes
         user.col = const_cast<int32_t*>(col);
         user.w = const_cast<int64_t*>(wt);
         if (!csr_to_padded(rp, n, user.off, user.len, s)) return MC_E_DEVICE;
-        if (!contract(user, nullptr, n, w.g[0], w.cw, w.sc, s)) return MC_E_DEVICE;
+        if (!contract(user, nullptr, n, w.g[0], w.cw, w.sc, s) || !solve_start(S, n)) return MC_E_DEVICE;
     }
     S.stats.input_normal = input_normal;
-    if (!iota_i32(w.map0, n, s) || !fill_i32(w.claim, 0, n, s)) return MC_E_DEVICE;
     // connectivity: lambda = 0 iff the positive-weight graph is disconnected.
     // When the heuristic runs, its coarse graph has the same components and
     // decides it at a fraction of the cost (a vertex of degree 0 decides it
@@ -1433,8 +1459,7 @@ static mc_status solve(mc_ctx* c, const mc_csr* g, void* dev_ws, size_t ws_bytes
         result = 0;   // check_connected set the side
     } else {
         // minimum degree is the first bound; its vertex is the first side
-        if (!side_from_vertex(w.side, w.map0, n, &w.sc->dmin_arg, s)) return MC_E_DEVICE;
-        if (!S.set_lam(h.dmin)) return MC_E_DEVICE;
+        S.lam = h.dmin;
         S.stats.lambda_min_degree = h.dmin;
         mc_status r = MC_OK;
         S.heur_pending = run_heuristic && S.automatic;
