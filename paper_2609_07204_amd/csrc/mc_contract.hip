@@ -988,10 +988,16 @@ __global__ __launch_bounds__(GR_T) void k_giant_row(const int32_t* __restrict__ 
         const bool last = h0 >= n2;
         __syncthreads();
         if (cnt > GR_BUF - (int32_t)step || (last && cnt > 0)) {
-            if (threadIdx.x == 0) at = atomicAdd(&bcur[G], cnt);
+            if (threadIdx.x == 0) {
+                // (a symmetric graph's row has room for all; of any other the
+                // row ends with its window)
+                at = atomicAdd(&bcur[G], cnt);
+                const int32_t over = at + cnt - room;
+                if (over > 0) atomicSub(&bcur[G], over < cnt ? over : cnt);
+            }
             __syncthreads();
             for (int i = threadIdx.x; i < cnt; i += GR_T) {
-                if (at + i >= room) continue;   // (not in a symmetric graph)
+                if (at + i >= room) continue;
                 dst.col[g0 + at + i] = bh[i];
                 dst.w[g0 + at + i] = bw[i];
                 sum += bw[i];
