@@ -56,8 +56,10 @@ __device__ __forceinline__ void l1_max(int64_t* lg, long long* ls, int32_t b, in
 }
 
 constexpr int LDS_PT = 1024;
-constexpr int LDS_N = 8192;
-constexpr int64_t LDS_LAM = (int64_t)1 << 49;   // keys are packed above 13 bits of vertex
+constexpr int LDS_N = 16256;                    // 10 B a vertex and the step's sums: a workgroup's 160 KB
+constexpr int LDS_VBITS = 14;
+constexpr int64_t LDS_LAM = (int64_t)1 << 48;   // keys are packed above the bits of a vertex
+static_assert(LDS_N <= 1 << LDS_VBITS && LDS_N <= INT16_MAX, "vertex in a key and in the list");
 __device__ __forceinline__ bool lds_pass(int32_t n, int64_t lam) { return n <= LDS_N && lam < LDS_LAM; }
 
 template <int PT>
@@ -497,12 +499,14 @@ __global__ __launch_bounds__(PT) void k_capforest_private(PrivateArgs a) {
 
 // The same pass on a graph of at most LDS_N vertices, with r in LDS (-1: scanned,
 // -2: in the step's batch, 0: not reached). It needs no index over the queue:
-// each step reads all keys (8 a thread at most), reduces them by DPP moves and
+// each step reads all keys (16 a thread at most), reduces them by DPP moves and
 // takes every capped vertex, or else the one of the largest key. What is left
 // of a step's chain is three barriers and the round trip to the popped rows,
 // 1 to 2 us, where a single pop of the pass above is a chain of a dozen round
 // trips to HBM and barriers (5 to 7 us): a batch of 384 graphs whose last four
-// have 1,098 to 3,074 vertices, 3.5 ms a launch, 7.6 before.
+// have 1,098 to 3,074 vertices, 3.5 ms a launch, 7.6 before. Up to 16,256
+// vertices (before, up to 8192): another such batch, whose slowest graph lies
+// between, 25 ms a launch by the pass above, 14 ms here.
 __global__ __launch_bounds__(LDS_PT) void k_capforest_lds(PrivateArgs a) {
     extern __shared__ long long dyn[];
     __shared__ uint64_t red[LDS_PT / MC_WAVE];
@@ -540,7 +544,7 @@ __global__ __launch_bounds__(LDS_PT) void k_capforest_lds(PrivateArgs a) {
         uint64_t key = 0;
         for (int32_t v = tid; v < n; v += LDS_PT) {
             const int64_t rv = r[v];
-            const uint64_t kv = rv > 0 ? ((uint64_t)(rv < lam ? rv : lam) << 13) + (uint64_t)(LDS_N - 1 - v) : 0;
+            const uint64_t kv = rv > 0 ? ((uint64_t)(rv < lam ? rv : lam) << LDS_VBITS) + (uint64_t)(LDS_N - 1 - v) : 0;
             key = kv > key ? kv : key;
         }
         key = wave_max_u64(key);
@@ -548,8 +552,8 @@ __global__ __launch_bounds__(LDS_PT) void k_capforest_lds(PrivateArgs a) {
         __syncthreads();
         key = wave_max_u64(lane < LDS_PT / MC_WAVE ? red[lane] : 0);
         if (key == 0 && steps > 0) break;                      // queue empty
-        const bool batch = steps > 0 && (int64_t)(key >> 13) >= lam;
-        const int32_t x1 = steps > 0 ? LDS_N - 1 - (int32_t)(key & (LDS_N - 1)) : first;
+        const bool batch = steps > 0 && (int64_t)(key >> LDS_VBITS) >= lam;
+        const int32_t x1 = steps > 0 ? LDS_N - 1 - (int32_t)(key & ((1 << LDS_VBITS) - 1)) : first;
         // ---- the step's vertices (of a batch as many as the budget allows:
         // any order among them is a valid one)
         if (batch) {

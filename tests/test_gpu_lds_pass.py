@@ -1,5 +1,5 @@
 """GPU tests of the CAPFOREST pass with its state in LDS (graphs of 1025 to
-8192 vertices, bounds below 2^49): whole solves with private passes asked for
+16,256 vertices, bounds below 2^48): whole solves with private passes asked for
 by name, single and batched, against the CPU oracle, at the edges of its
 sizes, its packed keys and its scan budget."""
 import numpy as np
@@ -41,6 +41,18 @@ def test_private_solve(n, degree, wmin, wmax):
     st = check(ctx, g, oracle.noi(g)[0])
     assert st["rounds"] >= 1
     ctx.close()
+
+
+# the largest graphs of the kernel: keys of 14 bits of vertex, all of the LDS
+@pytest.mark.parametrize("n", [9000, 16255, 16256, 16257])
+def test_largest_graphs(n):
+    import paper_2609_07204_amd as mc
+    for w in ((1, 1), (1 << 43, 1 << 44)):
+        g = sparse(n, 6, w[1], n, w[0])
+        ctx = mc.Context(0, capforest_mode=PRIVATE, capforest_passes=3, heuristic_min_n=0, finish_max_n=-1,
+                         pr_tri_deg_cap=0)
+        check(ctx, g, oracle.noi(g)[0])
+        ctx.close()
 
 
 # bounds of 2^49 and more, too large to be packed beside a vertex (the pass in
