@@ -42,6 +42,14 @@ mc_status mc_step_ws_size(int32_t n, int64_t cap, int32_t passes, size_t* bytes)
 mc_status mc_step_contract(mc_ctx* ctx, const mc_dgraph* src, const int32_t* labels, int32_t n2,
                            mc_dgraph* dst, void* ws, size_t ws_bytes, int64_t* dmin, int32_t* dmin_arg);
 
+/* The same contraction as the rounds of mc_mincut run it: src is symmetric
+ * (every entry v->x has its reverse x->v of the same weight) with deg set.
+ * The row of a group that holds at least half of all entries is then taken
+ * from the other rows' column, and, where no row of src has more than 8192
+ * entries, groups with dense accumulators are read row by row. */
+mc_status mc_step_contract_round(mc_ctx* ctx, const mc_dgraph* src, const int32_t* labels, int32_t n2,
+                                 mc_dgraph* dst, void* ws, size_t ws_bytes, int64_t* dmin, int32_t* dmin_arg);
+
 /* Canonical components of the pairs (a[i], b[i]) on [0,n): labels[v] is
  * the rank of the smallest vertex of v's component among all component
  * minima; *n2 (host) receives the component count. */

@@ -125,6 +125,7 @@ SIGNATURES = {
     "mc_profile_round": (ctypes.c_int, [P, I32, P, P]),
     "mc_step_ws_size": (ctypes.c_int, [I32, I64, I32, P]),
     "mc_step_contract": (ctypes.c_int, [P, P, P, I32, P, P, SZ, P, P]),
+    "mc_step_contract_round": (ctypes.c_int, [P, P, P, I32, P, P, SZ, P, P]),
     "mc_step_components": (ctypes.c_int, [P, I32, I64, P, P, P, P, P, SZ]),
     "mc_step_pr12": (ctypes.c_int, [P, P, I64, P, P, P, P, P, SZ]),
     "mc_step_lp": (ctypes.c_int, [P, P, P, P, P, SZ]),
@@ -376,14 +377,16 @@ class Context:
             d.w[:rp[-1]].copy_(torch.as_tensor(np.ascontiguousarray(g.w, np.int64)))
         return d
 
-    def step_contract(self, src, labels=None, n2=None):
+    def step_contract(self, src, labels=None, n2=None, in_round=False):
+        """Contraction by labels (None: the identity); in_round: as the rounds
+        of a solve run it (see mc_step_contract_round)."""
         n2 = src.n if labels is None else int(n2)
         dst = DeviceGraph(n2, src.cap, self.device)
         ws = self.step_workspace(src.n, src.cap)
         dmin, darg = ctypes.c_int64(), ctypes.c_int32()
-        _check(lib().mc_step_contract(self.h, ctypes.byref(src.c()), _ptr(labels), n2, ctypes.byref(dst.c()),
-                                      ctypes.c_void_p(ws.data_ptr()), ws.numel(), ctypes.byref(dmin),
-                                      ctypes.byref(darg)))
+        call = lib().mc_step_contract_round if in_round else lib().mc_step_contract
+        _check(call(self.h, ctypes.byref(src.c()), _ptr(labels), n2, ctypes.byref(dst.c()),
+                    ctypes.c_void_p(ws.data_ptr()), ws.numel(), ctypes.byref(dmin), ctypes.byref(darg)))
         return dst, dmin.value, darg.value
 
     def step_components(self, n, a, b):

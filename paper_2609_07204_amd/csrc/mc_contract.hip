@@ -987,23 +987,26 @@ __global__ __launch_bounds__(GR_T) void k_giant_row(const int32_t* __restrict__ 
     for (int64_t h0 = blockIdx.x * step;; h0 += gridDim.x * step) {
         const bool last = h0 >= n2;
         __syncthreads();
-        if (cnt > GR_BUF - (int32_t)step || (last && cnt > 0)) {
+        // every wavefront reads the count of the steps before, and none adds a
+        // find of this step until all have: they flush together or not at all
+        const int32_t held = cnt;
+        __syncthreads();
+        if (held > GR_BUF - (int32_t)step || (last && held > 0)) {
             if (threadIdx.x == 0) {
                 // (a symmetric graph's row has room for all; of any other the
                 // row ends with its window)
-                at = atomicAdd(&bcur[G], cnt);
-                const int32_t over = at + cnt - room;
-                if (over > 0) atomicSub(&bcur[G], over < cnt ? over : cnt);
+                at = atomicAdd(&bcur[G], held);
+                const int32_t over = at + held - room;
+                if (over > 0) atomicSub(&bcur[G], over < held ? over : held);
+                cnt = 0;
             }
             __syncthreads();
-            for (int i = threadIdx.x; i < cnt; i += GR_T) {
+            for (int i = threadIdx.x; i < held; i += GR_T) {
                 if (at + i >= room) continue;
                 dst.col[g0 + at + i] = bh[i];
                 dst.w[g0 + at + i] = bw[i];
                 sum += bw[i];
             }
-            __syncthreads();
-            if (threadIdx.x == 0) cnt = 0;
             __syncthreads();
         }
         if (last) break;

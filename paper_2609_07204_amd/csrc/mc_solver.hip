@@ -1619,18 +1619,35 @@ extern "C" mc_status mc_step_ws_size(int32_t n, int64_t cap, int32_t passes, siz
     return MC_OK;
 }
 
-extern "C" mc_status mc_step_contract(mc_ctx* c, const mc_dgraph* src, const int32_t* labels, int32_t n2,
-                                      mc_dgraph* dst, void* ws, size_t bytes, int64_t* dmin, int32_t* dmin_arg) {
+// round: as the rounds of a solve call it (symmetric, and with the longest row known)
+static mc_status step_contract(mc_ctx* c, const mc_dgraph* src, const int32_t* labels, int32_t n2, mc_dgraph* dst,
+                               void* ws, size_t bytes, int64_t* dmin, int32_t* dmin_arg, bool round) {
     if (!src || !dst) return fail(MC_E_INVALID_ARG, "mc_step_contract: NULL graph");
     StepWS w;
     mc_status r = step_begin(c, src->n, src->cap, 1, ws, bytes, w);
     if (r != MC_OK) return r;
     DGraph s = to_dgraph(src), d = to_dgraph(dst);
-    if (!contract(s, labels, labels ? n2 : src->n, d, w.cw, w.sc, c->stream)) return MC_E_DEVICE;
+    int32_t max_row = INT32_MAX;
+    if (round) {
+        if (!min_degree(s, w.cw, w.sc, c->stream)) return MC_E_DEVICE;
+        if ((r = sync_read(c, w)) != MC_OK) return r;
+        max_row = c->hsc->max_row;
+    }
+    if (!contract(s, labels, labels ? n2 : src->n, d, w.cw, w.sc, c->stream, max_row, round)) return MC_E_DEVICE;
     if ((r = sync_read(c, w)) != MC_OK) return r;
     if (dmin) *dmin = c->hsc->dmin;
     if (dmin_arg) *dmin_arg = c->hsc->dmin_arg;
     return MC_OK;
+}
+
+extern "C" mc_status mc_step_contract(mc_ctx* c, const mc_dgraph* src, const int32_t* labels, int32_t n2,
+                                      mc_dgraph* dst, void* ws, size_t bytes, int64_t* dmin, int32_t* dmin_arg) {
+    return step_contract(c, src, labels, n2, dst, ws, bytes, dmin, dmin_arg, false);
+}
+
+extern "C" mc_status mc_step_contract_round(mc_ctx* c, const mc_dgraph* src, const int32_t* labels, int32_t n2,
+                                            mc_dgraph* dst, void* ws, size_t bytes, int64_t* dmin, int32_t* dmin_arg) {
+    return step_contract(c, src, labels, n2, dst, ws, bytes, dmin, dmin_arg, true);
 }
 
 extern "C" mc_status mc_step_components(mc_ctx* c, int32_t n, int64_t np, const int32_t* a, const int32_t* b,
