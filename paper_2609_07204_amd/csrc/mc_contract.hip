@@ -1104,6 +1104,59 @@ __device__ __forceinline__ void min_deg_store(const MinDeg& a, DevScalars* sc) {
     sc->max_row = a.row;
 }
 
+// The trees that the first CONN_FIRST entries of every row leave of a graph of at
+// most CONN_SMALL vertices, by one workgroup in LDS: one tree of most connected
+// graphs, which decides them in one launch beside others whose results are read
+// back anyway, a workgroup of its own beside the minimum degree's (8 us at 1,100 vertices, 33 us at 9,000, bound by the chains of
+// its unions; the general form is eleven launches and a readback, about 55 us;
+// all eight entries unioned at once 38 us at 8,000 vertices, two and then the
+// others 29 us, a thread's rows in flight together 31 us, lowering sweeps as in
+// k_uf_root_min 57 us, eight lanes a row 89 us). Several trees decide nothing. A
+// device input is not checked yet, so targets out of range are passed over.
+constexpr int CONN_T = 1024;
+constexpr int CONN_FIRST = 8;
+__device__ __forceinline__ void connect_trees(const DGraph& g, DevScalars* sc) {
+    __shared__ int32_t root[CONN_SMALL];
+    __shared__ int32_t part[CONN_T / MC_WAVE];
+    const int tid = threadIdx.x;
+    const int32_t n = g.n;
+    for (int32_t v = tid; v < n; v += CONN_T) root[v] = v;
+    __syncthreads();
+    // two entries of every row; then, with every vertex at its root, the others
+    // mostly end at one comparison
+    for (int32_t v = tid; v < n; v += CONN_T) {
+        const int32_t o = g.off[v], l = g.len[v];
+        const int32_t x = l > 0 ? g.col[o] : -1, y = l > 1 ? g.col[o + 1] : -1;
+        if ((uint32_t)x < (uint32_t)n) uf_union_lds(root, v, x);
+        if ((uint32_t)y < (uint32_t)n) uf_union_lds(root, v, y);
+    }
+    __syncthreads();
+    for (int32_t v = tid; v < n; v += CONN_T) root[v] = uf_find_lds(root, v);
+    __syncthreads();
+    for (int32_t v = tid; v < n; v += CONN_T) {
+        const int32_t o = g.off[v], l = g.len[v] < CONN_FIRST ? g.len[v] : CONN_FIRST;
+        int32_t x[CONN_FIRST - 2];
+#pragma unroll
+        for (int j = 2; j < CONN_FIRST; j++) x[j - 2] = j < l ? g.col[o + j] : -1;
+#pragma unroll
+        for (int j = 2; j < CONN_FIRST; j++)
+            if ((uint32_t)x[j - 2] < (uint32_t)n && root[x[j - 2]] != root[v]) uf_union_lds(root, v, x[j - 2]);
+    }
+    __syncthreads();
+    int32_t trees = 0;
+    for (int32_t v = tid; v < n; v += CONN_T) trees += root[v] == v;
+    trees = wave_sum_i32(trees);
+    if (lane_id() == 0) part[tid / MC_WAVE] = trees;
+    __syncthreads();
+    if (tid != 0) return;
+    for (int q = 1; q < CONN_T / MC_WAVE; q++) trees += part[q];
+    sc->n2 = trees;
+}
+
+__global__ __launch_bounds__(CONN_T) void k_connect_first(DGraph g, DevScalars* sc) { connect_trees(g, sc); }
+
+// CONNECT: one block folds, a second one looks whether the graph is connected
+template <bool CONNECT>
 __global__ __launch_bounds__(MIN_DEG_T) void k_min_deg_blocks(const int64_t* __restrict__ deg, int32_t* __restrict__ len,
                                                              int32_t n, const int32_t* __restrict__ bebase,
                                                              const int32_t* __restrict__ dslot,
@@ -1111,19 +1164,24 @@ __global__ __launch_bounds__(MIN_DEG_T) void k_min_deg_blocks(const int64_t* __r
                                                              const int32_t* __restrict__ bcur,
                                                              int64_t* __restrict__ rv, int32_t* __restrict__ ri,
                                                              int64_t* __restrict__ rm, int64_t* __restrict__ rd,
-                                                             CanonParts parts, DevScalars* sc) {
+                                                             CanonParts parts, DevScalars* sc, DGraph whole) {
+    if (CONNECT && blockIdx.x == 1) {
+        connect_trees(whole, sc);
+        return;
+    }
+    const int blocks = CONNECT ? 1 : gridDim.x;
     MinDeg a{0, 0, 0, -1, 0};
-    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
+    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)blocks * blockDim.x) {
         const int64_t d = deg[v];
         int32_t l;
         if (bebase && (bebase[v + 1] > bebase[v] || dslot[v] >= 0 || v == *giant)) len[v] = l = bcur[v];
         else l = len[v];
         min_deg_take(a, d, (int32_t)v, l, d, l);
     }
-    if (gridDim.x == 1 && parts.count > 0) fold_parts(parts, sc);
+    if (blocks == 1 && parts.count > 0) fold_parts(parts, sc);
     min_deg_fold(a);
     if (threadIdx.x != 0) return;
-    if (gridDim.x == 1) {
+    if (blocks == 1) {
         min_deg_store(a, sc);
     } else {
         rv[blockIdx.x] = a.d;
@@ -1195,10 +1253,16 @@ void contract_ws_carve(Arena& a, int32_t n, int64_t cap, ContractWS& ws, bool so
 
 static bool min_degree(const DGraph& g, const int32_t* bebase, const int32_t* dslot, const int32_t* giant,
                        const int32_t* bcur, const CanonParts& parts, ContractWS& ws,
-                       DevScalars* sc, hipStream_t s) {
+                       DevScalars* sc, hipStream_t s, const DGraph* connect) {
     const int nb = g.n <= MIN_DEG_ONE ? 1 : grid_for(g.n, 4 * 256, 1024);
-    k_min_deg_blocks<<<nb, nb == 1 ? MIN_DEG_T : 256, 0, s>>>(g.deg, g.len, g.n, bebase, dslot, giant, bcur, ws.red_val, ws.red_id,
-                                                             ws.red_m, ws.red_d, parts, sc);
+    static_assert(CONN_SMALL <= MIN_DEG_ONE && CONN_T == MIN_DEG_T, "one launch for both");
+    if (connect)
+        k_min_deg_blocks<true><<<2, MIN_DEG_T, 0, s>>>(g.deg, g.len, g.n, bebase, dslot, giant, bcur, ws.red_val, ws.red_id,
+                                                       ws.red_m, ws.red_d, parts, sc, *connect);
+    else
+        k_min_deg_blocks<false><<<nb, nb == 1 ? MIN_DEG_T : 256, 0, s>>>(g.deg, g.len, g.n, bebase, dslot, giant, bcur,
+                                                                         ws.red_val, ws.red_id, ws.red_m, ws.red_d, parts,
+                                                                         sc, g);
     MC_LAUNCHED("k_min_deg_blocks");
     if (nb == 1) return true;
     k_min_deg_final<<<1, MIN_DEG_T, 0, s>>>(ws.red_val, ws.red_id, ws.red_m, ws.red_d, nb, parts, sc);
@@ -1206,8 +1270,15 @@ static bool min_degree(const DGraph& g, const int32_t* bebase, const int32_t* ds
     return true;
 }
 
-bool min_degree(const DGraph& g, ContractWS& ws, DevScalars* sc, hipStream_t s, const CanonParts& parts) {
-    return min_degree(g, nullptr, nullptr, nullptr, nullptr, parts, ws, sc, s);
+bool min_degree(const DGraph& g, ContractWS& ws, DevScalars* sc, hipStream_t s, const CanonParts& parts,
+                const DGraph* connect) {
+    return min_degree(g, nullptr, nullptr, nullptr, nullptr, parts, ws, sc, s, connect);
+}
+
+bool connect_first(const DGraph& g, DevScalars* sc, hipStream_t s) {
+    k_connect_first<<<1, CONN_T, 0, s>>>(g, sc);
+    MC_LAUNCHED("k_connect_first");
+    return true;
 }
 
 bool contract(const DGraph& src, const int32_t* L, int32_t n2, DGraph& dst, ContractWS& ws, DevScalars* sc,
@@ -1289,5 +1360,5 @@ bool contract(const DGraph& src, const int32_t* L, int32_t n2, DGraph& dst, Cont
                                                            ws.dense, n2, ws.bcur, dst);
         MC_LAUNCHED("k_giant_row");
     }
-    return min_degree(dst, ws.bigm, ws.dslot, ws.mcnt + 2, ws.bcur, CanonParts(), ws, sc, s);
+    return min_degree(dst, ws.bigm, ws.dslot, ws.mcnt + 2, ws.bcur, CanonParts(), ws, sc, s, nullptr);
 }

@@ -188,6 +188,31 @@ __device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) {
     return read_lane_u64(v, 63);
 }
 
+// the same in LDS, by one workgroup
+__device__ __forceinline__ int32_t uf_find_lds(int32_t* par, int32_t x) {
+    int32_t p = __hip_atomic_load(&par[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    while (p != x) {
+        const int32_t gp = __hip_atomic_load(&par[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (gp == p) return p;
+        __hip_atomic_store(&par[x], gp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        x = p;
+        p = gp;
+    }
+    return x;
+}
+// smaller root wins, so roots are the smallest vertex of their component
+__device__ __forceinline__ bool uf_union_lds(int32_t* par, int32_t a, int32_t b) {
+    int32_t ra = uf_find_lds(par, a), rb = uf_find_lds(par, b);
+    while (ra != rb) {
+        if (ra > rb) { const int32_t t = ra; ra = rb; rb = t; }
+        const int32_t old = atomicCAS(&par[rb], rb, ra);
+        if (old == rb) return true;
+        rb = uf_find_lds(par, old);
+        ra = uf_find_lds(par, ra);
+    }
+    return false;
+}
+
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (MC_WAVE - 1); }
 
 // order and visibility of LDS accesses between the lanes of one wavefront

@@ -75,31 +75,6 @@ struct FinLds {
     int32_t bcnt[3];
 };
 
-// ------------------------------------------------------------ union-find
-__device__ __forceinline__ int32_t lf_find(int32_t* par, int32_t x) {
-    int32_t p = __hip_atomic_load(&par[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    while (p != x) {
-        const int32_t gp = __hip_atomic_load(&par[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        if (gp == p) return p;
-        __hip_atomic_store(&par[x], gp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        x = p;
-        p = gp;
-    }
-    return x;
-}
-// smaller root wins, so roots are the smallest vertex of their component
-__device__ __forceinline__ bool lf_union(int32_t* par, int32_t a, int32_t b) {
-    int32_t ra = lf_find(par, a), rb = lf_find(par, b);
-    while (ra != rb) {
-        if (ra > rb) { const int32_t t = ra; ra = rb; rb = t; }
-        const int32_t old = atomicCAS(&par[rb], rb, ra);
-        if (old == rb) return true;
-        rb = lf_find(par, old);
-        ra = lf_find(par, ra);
-    }
-    return false;
-}
-
 // ------------------------------------------------------------ heap queue
 // max-heap on (min(r, lam), smallest id); single-threaded (lane 0)
 __device__ __forceinline__ bool h_before(const FinLds& S, int32_t a, int32_t b, int64_t lam) {
@@ -262,7 +237,7 @@ __device__ PassOut fin_pass(FinLds& S, int32_t n, const int32_t* __restrict__ co
                 } else {
                     const int64_t old = S.r[y];
                     nw = old + c;
-                    if (old < lam && lam <= nw && lf_union(S.parent, x, y)) marks++;
+                    if (old < lam && lam <= nw && uf_union_lds(S.parent, x, y)) marks++;
                     const int64_t kold = old < lam ? old : lam, knew = nw < lam ? nw : lam;
                     fresh = sy == F_NEW;
                     raise = !fresh && knew > kold;
@@ -403,7 +378,7 @@ __device__ PassOut fin_pass_batch(FinLds& S, int32_t n, const int32_t* __restric
             if (sy == F_SCANNED) return;
             const int64_t old = (int64_t)atomicAdd((unsigned long long*)&S.r[y], (unsigned long long)c);
             if (sy == F_NEW) S.st[y] = F_QUEUED;
-            if (old < lam && lam <= old + c) lf_union(S.parent, x, y);
+            if (old < lam && lam <= old + c) uf_union_lds(S.parent, x, y);
         };
         if (b == 1) {
             const int32_t x = S.order[o.nscan];
@@ -442,7 +417,7 @@ __device__ void fin_tests(FinLds& S, int32_t n, const int32_t* __restrict__ col,
         for (int32_t j = sl; j < l; j += FSUB) {
             const int32_t y = col[o + j] - cbase;
             const int64_t c = w[o + j];
-            if (c >= lam && y > v) lf_union(S.parent, v, y);
+            if (c >= lam && y > v) uf_union_lds(S.parent, v, y);
             if (c > bw || (c == bw && y < by)) { bw = c; by = y; }
         }
         for (int d = FSUB / 2; d > 0; d >>= 1) {
@@ -450,7 +425,7 @@ __device__ void fin_tests(FinLds& S, int32_t n, const int32_t* __restrict__ col,
             const int32_t y2 = __shfl_xor(by, d, FSUB);
             if (y2 >= 0 && (by < 0 || w2 > bw || (w2 == bw && y2 < by))) { bw = w2; by = y2; }
         }
-        if (sl == 0 && by >= 0 && 2 * bw >= S.deg[v]) lf_union(S.parent, v, by);
+        if (sl == 0 && by >= 0 && 2 * bw >= S.deg[v]) uf_union_lds(S.parent, v, by);
     }
 }
 
@@ -509,6 +484,31 @@ __device__ int32_t fin_roots(FinLds& S, int32_t n) {
     return S.vstart[n];
 }
 
+// whether the first entries of every row join the entry graph
+__device__ bool fin_joined(FinLds& S, int32_t n, const int32_t* __restrict__ col, int32_t cbase) {
+    constexpr int FIRST = 8;
+    for (int32_t v = threadIdx.x; v < n; v += FT) S.parent[v] = v;
+    __syncthreads();
+    static_assert(FT >= FIN_N, "a thread a vertex");
+    int32_t x[FIRST];
+    for (int32_t v = threadIdx.x; v < n; v += FT) {
+        const int32_t o = S.off[v], l = S.len[v] < FIRST ? S.len[v] : FIRST;
+#pragma unroll
+        for (int j = 0; j < FIRST; j++) x[j] = j < l ? col[o + j] - cbase : v;
+#pragma unroll
+        for (int j = 0; j < 2; j++) uf_union_lds(S.parent, v, x[j]);
+    }
+    __syncthreads();
+    for (int32_t v = threadIdx.x; v < n; v += FT) {
+        const int32_t r = uf_find_lds(S.parent, v);
+#pragma unroll
+        for (int j = 2; j < FIRST; j++)
+            if (uf_find_lds(S.parent, x[j]) != r) uf_union_lds(S.parent, v, x[j]);
+    }
+    __syncthreads();
+    return fin_roots(S, n) == 1;
+}
+
 }  // namespace
 
 // All remaining rounds of graph k by one workgroup (see the file comment).
@@ -540,6 +540,14 @@ static __device__ __forceinline__ void finish_one(const FinishArgs& a, int32_t k
     int32_t rounds = 0, err = 0;
     // every round marks an edge or lowers the bound
     const int32_t max_rounds = 4 * n0 + 16;
+    if (a.connect && !fin_joined(S, n, col, cbase)) {
+        if (tid == 0) {
+            a.lam_out[k] = lam;
+            a.dropped[k] = 2;
+            if (a.rounds) a.rounds[k] = 0;
+        }
+        return;
+    }
     while (n > 2 && lam > 0) {
         if (rounds >= max_rounds) { err = 2; break; }
         for (int32_t v = tid; v < n; v += FT) S.parent[v] = v;

@@ -167,7 +167,10 @@ struct CanonParts {
     int count = 0;
     bool check = false;
 };
-bool min_degree(const DGraph& g, ContractWS& ws, DevScalars* sc, hipStream_t s, const CanonParts& parts = CanonParts());
+// With connect (g with its rows, at most CONN_SMALL vertices) connect_first's
+// answer comes from the same launch.
+bool min_degree(const DGraph& g, ContractWS& ws, DevScalars* sc, hipStream_t s, const CanonParts& parts = CanonParts(),
+                const DGraph* connect = nullptr);
 
 // --------------------------------------------------------- union-find
 bool uf_init(int32_t* parent, int32_t n, hipStream_t s);
@@ -180,6 +183,11 @@ bool uf_all_edges(const DGraph& g, int32_t* parent, hipStream_t s);
 // lambda = 0 test: parent[] ends as a union-find of all edges of g. tmp: 4
 // ints; inbig: n bytes; snap: n ints (scratch).
 bool uf_connectivity(const DGraph& g, int32_t* parent, int32_t* tmp, uint8_t* inbig, int32_t* snap, hipStream_t s);
+// Trees of a graph of at most CONN_SMALL vertices after the first entries of
+// every row, in one launch, into sc->n2: 1 if the graph (all of whose entries
+// have positive weight) is connected, more than 1 decides nothing.
+constexpr int32_t CONN_SMALL = 1 << 14;
+bool connect_first(const DGraph& g, DevScalars* sc, hipStream_t s);
 // Compress parent[] and write canonical labels (components numbered by
 // their smallest vertex) to L; the count goes to sc->n2.
 bool uf_labels(int32_t* parent, int32_t n, int32_t* L, int32_t* flag_tmp, int32_t* scan_tmp,
@@ -462,7 +470,7 @@ struct FinishArgs {
     const int32_t* glist;     // [count] ranges to finish (nullptr: 0..count-1)
     const int64_t* lam_in;    // [K] bound of each range at entry
     int64_t* lam_out;         // [K] bound at the end: lambda of the graph (may alias lam_in)
-    int32_t* dropped;         // [K] 1 when the finisher lowered the bound
+    int32_t* dropped;         // [K] 1 when the finisher lowered the bound (2: see connect)
     uint8_t* fside;           // [g.n] side over the current vertices of dropped graphs
     int32_t* xcol[2];         // two scratch buffers for the contracted graphs
     int64_t* xw[2];
@@ -475,6 +483,8 @@ struct FinishArgs {
     int32_t* err;             // [1] 0, or why a graph could not finish
     int32_t qmode;            // 0 buckets while lam < 2048 else heap, 1 buckets, 2 heap
     int32_t* qnext;           // [1] work-queue ticket, 0 at the launch
+    bool connect;             // a graph may be disconnected: it is left alone, dropped = 2, unless the first
+                              // entries of its rows join it
 };
 // count graphs of a.glist, by at most `cus` persistent workgroups that draw
 // the graphs from a work queue (a.qnext must be 0)

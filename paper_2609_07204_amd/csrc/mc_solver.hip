@@ -594,7 +594,7 @@ struct Solver {
     bool heur_pending = false;    // the label-propagation bound runs once the input resists the tests
     bool bound_tried = false;     // threshold_bound has run
     bool in_heuristic = false;    // exact rounds on the heuristic's coarse graph
-    bool conn_pending = false;    // connectivity not decided yet (the heuristic's coarse graph decides it)
+    bool conn_pending = false;    // connectivity not decided yet (a contraction of the input decides it, or the finisher)
     bool lp1_ready = false;       // the input pass left the first LP round of the input in lab2
     bool disconnected = false;    // lambda = 0; the side is set
     bool pv_clean = false;        // private pass state cleared (once per solve, before the first private pass)
@@ -875,6 +875,8 @@ static int32_t finish_max_n(const mc_ctx* c) {
     return c->opt.finish_max_n > 0 ? std::min(c->opt.finish_max_n, FIN_N) : FIN_N;
 }
 
+static bool check_connected(Solver& S, const DGraph& g, bool first = true);
+
 // All remaining rounds of a small current graph in one launch (one
 // workgroup): the bound and, if it dropped, the side come back at once.
 static mc_status finish(Solver& S, DGraph* cur, int32_t round) {
@@ -898,15 +900,23 @@ static mc_status finish(Solver& S, DGraph* cur, int32_t round) {
     fa.xwindow = 0;
     fa.seed = S.c->opt.seed ^ ((uint64_t)(uint32_t)round << 20);
     fa.qmode = S.c->opt.deterministic ? 2 : S.c->opt.queue;
+    fa.connect = S.conn_pending;
     if (!fill_i32(w.sc->fin, 0, 4, s) || !finish_graphs(fa, 1, S.c->cus, s) || !S.readback())
         return fail(MC_E_DEVICE, "finisher: launch or readback failed");
     const int64_t lam_out = S.c->hsc->fin_lam;
     const int32_t* r32 = S.c->hsc->fin;
+    if (fa.connect && r32[0] == 2) {
+        // not joined by the first entries: all of them tell, and then the
+        // finisher runs (or the side is set)
+        if (!check_connected(S, *cur, false)) return MC_E_DEVICE;
+        return S.disconnected ? MC_OK : finish(S, cur, round);
+    }
     if (r32[2] != 0) return fail(MC_E_DEVICE, "finisher: a graph could not finish (code " + std::to_string(r32[2]) + ")");
     if (r32[0] && lam_out < S.lam) {
         if (!side_from_flag(w.side, w.map0, S.n0, w.flag8, s)) return MC_E_DEVICE;
         if (!S.set_lam(lam_out)) return MC_E_DEVICE;
     }
+    S.conn_pending = false;
     S.stats.rounds += S.c->hsc->fin[1];
     S.stats.finish_rounds += S.c->hsc->fin[1];
     return MC_OK;
@@ -949,17 +959,25 @@ static DGraph* contract_and_bound(Solver& S, DGraph* cur, int32_t n2, int* nxt_i
 // and the angular sectors of hyperbolic graphs. Runs on the input, whose two
 // spare graph buffers it takes, once per solve.
 constexpr int64_t kBoundShare = 4;
+// Inputs of at most this many vertices are looked at for components directly:
+// without the heuristic at once, with it when they resist the tests (two tori
+// of 22,500 vertices: 1,080 us when only the rounds told, 365 us; the look
+// itself takes 60 to 80 us of connected solves of 400 us and more). Larger ones
+// are looked at on a contraction: a hyperbolic core of 480,000 vertices pays
+// 0.75 ms of 4.0 for a look at the input, and what the other way costs a
+// disconnected input without the heuristic is less (two components of 150,000
+// vertices: 600 us, 400 us with the look; before the tests came first, 435 us).
+constexpr int32_t kConnectDirect = 1 << 17;
 static mc_status threshold_bound(Solver& S, int32_t round) {
     SolveWS& w = S.w;
     hipStream_t s = S.s;
     const int64_t m0 = S.cur_m;
     const int64_t target = S.lam / kBoundShare;
     int32_t max_row = S.in_max_row;
-    if (target < 1) return MC_OK;
     DGraph* cur = &w.g[0];
     int nxt_idx = 1;
     mc_status err = MC_OK;
-    while (cur->n > 2 && (cur == &w.g[0] || cur->n > finish_max_n(S.c))) {
+    while (target >= 1 && cur->n > 2 && (cur == &w.g[0] || cur->n > finish_max_n(S.c))) {
         const int32_t n = cur->n;
         k_round_start<<<grid_for(n, 256), 256, 0, s>>>(w.sc, target, w.parent, n);
         if (!mc_hip_ok(hipGetLastError(), "k_round_start") ||
@@ -976,8 +994,10 @@ static mc_status threshold_bound(Solver& S, int32_t round) {
         if (!cur) return err;
         max_row = S.c->hsc->max_row;
     }
+    if (cur != &w.g[0] && cur->n > 2 && cur->n <= finish_max_n(S.c) && (err = finish(S, cur, round)) != MC_OK) return err;
+    // the parts are connected as the input is
+    if ((S.conn_pending || S.lam == 0) && !check_connected(S, *cur)) return MC_E_DEVICE;
     if (cur != &w.g[0]) {
-        if (cur->n > 2 && cur->n <= finish_max_n(S.c) && (err = finish(S, cur, round)) != MC_OK) return err;
         if (S.debug) fprintf(stderr, "[mc] threshold bound: lam=%lld\n", (long long)S.lam);
         if (!iota_i32(w.map0, S.n0, s)) return MC_E_DEVICE;
     }
@@ -998,12 +1018,16 @@ static mc_status exact_rounds(Solver& S, int src) {
     const int64_t m_first = S.cur_m;
     int32_t max_row = src == 0 ? S.in_max_row : S.c->hsc->max_row;   // longest row of cur
     bool note_bound = false;      // the tests' contraction of the input takes the heuristic's place
-    while (cur->n > 2 && S.lam > 0) {
+    while (cur->n > 2 && S.lam > 0 && !S.disconnected) {
         if (cur->n <= finish_max_n(S.c)) {
             // a small graph finishes every remaining round in one launch
             mc_status r = finish(S, cur, round);
             if (r != MC_OK) return r;
             break;
+        }
+        if (S.conn_pending && cur != &w.g[0]) {
+            if (!check_connected(S, *cur)) return MC_E_DEVICE;
+            if (S.disconnected) break;
         }
         DGraph* nxt = &w.g[nxt_idx];
         const int32_t n = cur->n;
@@ -1048,13 +1072,19 @@ static mc_status exact_rounds(Solver& S, int src) {
             // they do not: 5.6 and 6.2 ms.
             const int64_t before = S.lam;
             mc_status r = MC_OK;
+            // (a disconnected input of ordinary size is not taken through the
+            // heuristic; a large one is looked at on its coarse graph)
+            if (!skip_cf && S.heur_pending && S.conn_pending && n <= kConnectDirect) {
+                if (!check_connected(S, *cur)) return MC_E_DEVICE;
+                if (S.disconnected) break;
+            }
             if (!skip_cf && S.heur_pending) {
                 prof_round_cancel();
                 S.heur_pending = false;
                 S.cert_max_n = INT32_MAX;
                 if ((r = heuristic(S)) != MC_OK || !iota_i32(w.map0, S.n0, s)) return r != MC_OK ? r : MC_E_DEVICE;
                 S.cur_m = m_first;
-                if (S.lam < before) continue;
+                if (S.lam < before || S.disconnected) continue;
             }
             if (!skip_cf && !S.bound_tried) {
                 prof_round_cancel();
@@ -1217,6 +1247,8 @@ static mc_status exact_rounds(Solver& S, int src) {
         round++;
     }
     if (note_bound) S.stats.lambda_heuristic = S.lam;
+    // a cut of 0: its side is the complement of vertex 0's component
+    if (S.lam == 0 && !S.disconnected && !check_connected(S, *cur)) return MC_E_DEVICE;
     if (cur->n > 1) prof_round_end(cur->n, S.cur_m, s);   // a round that ended without contraction
     S.stats.rounds += round;
     return MC_OK;
@@ -1236,13 +1268,17 @@ static bool solve_start(Solver& S, int32_t n) {
 // connected and joins no two, so g has exactly the input's components. On a
 // disconnected input the side becomes the complement of vertex 0's
 // component.
-static bool check_connected(Solver& S, const DGraph& g) {
+static bool check_connected(Solver& S, const DGraph& g, bool first) {
     SolveWS& w = S.w;
     hipStream_t s = S.s;
+    S.conn_pending = false;
+    if (first && S.lam > 0 && g.n <= CONN_SMALL) {
+        if (!connect_first(g, w.sc, s) || !S.readback()) return false;
+        if (S.c->hsc->n2 == 1) return true;
+    }
     if (!uf_init(w.parent, g.n, s) || !uf_connectivity(g, w.parent, w.vpart_i32(), w.flag8, w.L, s) ||
         !uf_labels(w.parent, g.n, w.L, w.flag, w.cw.scan_tmp, w.sc, s) || !S.readback())
         return false;
-    S.conn_pending = false;
     if (S.c->hsc->n2 > 1) {
         S.disconnected = true;
         if (!side_from_components(w.side, w.parent, &g == &w.g[0] ? nullptr : w.map0, S.n0, s)) return false;
@@ -1403,11 +1439,26 @@ static mc_status solve(mc_ctx* c, const mc_csr* g, void* dev_ws, size_t ws_bytes
     // a solve that runs the heuristic takes its first label-propagation
     // round from this pass when the input is normal
     const bool run_heuristic = c->opt.heuristic_min_n > 0 && n >= c->opt.heuristic_min_n;
+    S.automatic = c->opt.capforest_mode == MC_CF_AUTO && c->opt.deterministic == 0;
+    // Connectivity (lambda = 0 iff the positive-weight graph is disconnected).
+    // Without the heuristic it is looked up with the minimum degree, or on its
+    // own from CONN_SMALL vertices on. With it, and on large graphs in the
+    // automatic mode, a contraction of the input has the same components and
+    // decides it at a fraction of the cost (in the finisher, where that is
+    // small), before anything is spent on CAPFOREST. Where only the rounds told
+    // (they end at a cut of 0), two components of 1,000 and of 4,000 vertices
+    // took 445 and 515 us, 125 and 152 us so; two of 20,000 780 and 590 us.
+    // conn_first: whether the first entries of the rows join the graph, which
+    // decides most that are connected.
+    const bool conn_first = !run_heuristic && n <= CONN_SMALL;
     CanonParts parts;
     parts.check = !host_input;
+    DGraph raw = w.g[0];   // (it counts for a normal input; rows out of range have no entries)
+    raw.off = const_cast<int32_t*>(rp);
+    raw.col = const_cast<int32_t*>(col);
     if (!canon_check(rp, col, wt, n, (int32_t)nnz, w.g[0].len, w.g[0].deg, &w.sc->noncanon,
                      host_input ? nullptr : w.sc, run_heuristic ? w.lab2 : nullptr, w.cw, parts, s) ||
-        !min_degree(w.g[0], w.cw, w.sc, s, parts) || !solve_start(S, n) || !S.readback())
+        !min_degree(w.g[0], w.cw, w.sc, s, parts, conn_first ? &raw : nullptr) || !solve_start(S, n) || !S.readback())
         return MC_E_DEVICE;
     if (c->hsc->err != 0)
         return fail((mc_status)c->hsc->err, c->hsc->err == MC_E_OVERFLOW ? "total weight must be below 2^62"
@@ -1425,13 +1476,11 @@ static mc_status solve(mc_ctx* c, const mc_csr* g, void* dev_ws, size_t ws_bytes
         user.col = const_cast<int32_t*>(col);
         user.w = const_cast<int64_t*>(wt);
         if (!csr_to_padded(rp, n, user.off, user.len, s)) return MC_E_DEVICE;
-        if (!contract(user, nullptr, n, w.g[0], w.cw, w.sc, s) || !solve_start(S, n)) return MC_E_DEVICE;
+        if (!contract(user, nullptr, n, w.g[0], w.cw, w.sc, s) || !solve_start(S, n) ||
+            (conn_first && !connect_first(w.g[0], w.sc, s)))
+            return MC_E_DEVICE;
     }
     S.stats.input_normal = input_normal;
-    // connectivity: lambda = 0 iff the positive-weight graph is disconnected.
-    // When the heuristic runs, its coarse graph has the same components and
-    // decides it at a fraction of the cost (a vertex of degree 0 decides it
-    // here).
     S.lp1_ready = run_heuristic && input_normal;
     // Tests 3 and 4 run only in solves without the heuristic. With it they
     // cost more than they save, on the clusters and in the exact rounds
@@ -1439,14 +1488,10 @@ static mc_status solve(mc_ctx* c, const mc_csr* g, void* dev_ws, size_t ws_bytes
     // Chung-Lu 2^22: 14.54 and 14.42 ms).
     if (run_heuristic) S.tri_on = false;
     if (!input_normal && !S.readback()) return MC_E_DEVICE;   // the normalisation's minimum degree
-    S.automatic = c->opt.capforest_mode == MC_CF_AUTO && c->opt.deterministic == 0;
-    if (c->hsc->dmin > 0 && (S.automatic || run_heuristic)) {
-        // in the automatic mode not even that: unions only ever join
-        // connected vertices, so the rounds of a disconnected graph end at a
-        // cut of 0, and only then its components are looked up
-        S.conn_pending = !S.automatic;
-    } else if (!check_connected(S, w.g[0])) {
-        return MC_E_DEVICE;
+    if (c->hsc->dmin > 0 && (run_heuristic || (S.automatic && n > kConnectDirect))) {
+        S.conn_pending = true;
+    } else if (!(conn_first && c->hsc->n2 == 1) && !check_connected(S, w.g[0], false)) {
+        return MC_E_DEVICE;   // (a vertex of degree 0 decides it here)
     }
     DevScalars h = *c->hsc;
     S.stats.n_input = n;
@@ -1473,8 +1518,7 @@ static mc_status solve(mc_ctx* c, const mc_csr* g, void* dev_ws, size_t ws_bytes
             result = 0;
         } else {
             if ((r = exact_rounds(S, 0)) != MC_OK) return r;
-            result = S.lam;
-            if (result == 0 && !check_connected(S, w.g[0])) return MC_E_DEVICE;
+            result = S.disconnected ? 0 : S.lam;
         }
     }
     if (side_out) {
