@@ -875,7 +875,7 @@ static int32_t finish_max_n(const mc_ctx* c) {
     return c->opt.finish_max_n > 0 ? std::min(c->opt.finish_max_n, FIN_N) : FIN_N;
 }
 
-static bool check_connected(Solver& S, const DGraph& g, bool first = true);
+static bool check_connected(Solver& S, const DGraph& g, bool first = true, int32_t* forest = nullptr);
 
 // All remaining rounds of a small current graph in one launch (one
 // workgroup): the bound and, if it dropped, the side come back at once.
@@ -1025,10 +1025,6 @@ static mc_status exact_rounds(Solver& S, int src) {
             if (r != MC_OK) return r;
             break;
         }
-        if (S.conn_pending && cur != &w.g[0]) {
-            if (!check_connected(S, *cur)) return MC_E_DEVICE;
-            if (S.disconnected) break;
-        }
         DGraph* nxt = &w.g[nxt_idx];
         const int32_t n = cur->n;
         prof_round_begin(S.in_heuristic ? 2 : 0, n, S.cur_m, s);
@@ -1098,6 +1094,13 @@ static mc_status exact_rounds(Solver& S, int src) {
                 S.stats.heuristic_levels = 1;
                 note_bound = true;
             }
+        }
+        // rounds that the tests halve are cheap and few; before more is spent, or
+        // in the finisher, it is looked up whether the graph is connected (the
+        // round's unions stay)
+        if (!skip_cf && S.conn_pending) {
+            if (!check_connected(S, *cur, true, w.lab2)) return MC_E_DEVICE;
+            if (S.disconnected) break;
         }
         if (!skip_cf && S.automatic && S.tri()) {
             if (!S.tests34(*cur) || !S.readback()) return MC_E_DEVICE;
@@ -1268,20 +1271,21 @@ static bool solve_start(Solver& S, int32_t n) {
 // connected and joins no two, so g has exactly the input's components. On a
 // disconnected input the side becomes the complement of vertex 0's
 // component.
-static bool check_connected(Solver& S, const DGraph& g, bool first) {
+static bool check_connected(Solver& S, const DGraph& g, bool first, int32_t* forest) {
     SolveWS& w = S.w;
     hipStream_t s = S.s;
+    int32_t* const par = forest ? forest : w.parent;
     S.conn_pending = false;
     if (first && S.lam > 0 && g.n <= CONN_SMALL) {
         if (!connect_first(g, w.sc, s) || !S.readback()) return false;
         if (S.c->hsc->n2 == 1) return true;
     }
-    if (!uf_init(w.parent, g.n, s) || !uf_connectivity(g, w.parent, w.vpart_i32(), w.flag8, w.L, s) ||
-        !uf_labels(w.parent, g.n, w.L, w.flag, w.cw.scan_tmp, w.sc, s) || !S.readback())
+    if (!uf_init(par, g.n, s) || !uf_connectivity(g, par, w.vpart_i32(), w.flag8, w.L, s) ||
+        !uf_labels(par, g.n, w.L, w.flag, w.cw.scan_tmp, w.sc, s) || !S.readback())
         return false;
     if (S.c->hsc->n2 > 1) {
         S.disconnected = true;
-        if (!side_from_components(w.side, w.parent, &g == &w.g[0] ? nullptr : w.map0, S.n0, s)) return false;
+        if (!side_from_components(w.side, par, &g == &w.g[0] ? nullptr : w.map0, S.n0, s)) return false;
     }
     return true;
 }
