@@ -79,6 +79,16 @@ mc_status mc_step_pr12(mc_ctx* ctx, const mc_dgraph* g, int64_t lam, uint8_t* fl
 mc_status mc_step_pr34(mc_ctx* ctx, const mc_dgraph* g, int64_t lam, int32_t D, const int32_t* ptr2,
                        uint8_t* flag4, int32_t* acc3, int32_t* labels, int32_t* n2, void* ws, size_t ws_bytes);
 
+/* The reduction test by edge-disjoint subgraphs on a simple graph g with deg
+ * set: vertices that the test finds at least lam-connected are unioned, on
+ * top of the forest `start` ([n] device array of parents, start[v] <= v;
+ * NULL: every vertex its own). Canonical labels of the result (labels[n],
+ * *n2), and the trees joined (*marks: those of `start` less n2). The
+ * subgraphs lie in the workspace, so g->cap must be about 4 n entries or
+ * more (MC_E_INVALID_ARG). */
+mc_status mc_step_certify(mc_ctx* ctx, const mc_dgraph* g, int64_t lam, const int32_t* start, int32_t* labels,
+                          int32_t* n2, int64_t* marks, void* ws, size_t ws_bytes);
+
 /* One synchronous label-propagation round, the clustering step of the
  * bound heuristic (Section 2.1, "Lowering the upper bound"): lab_out[v] is
  * the label (among lab_in of v's neighbours, loops ignored) with the

@@ -128,6 +128,7 @@ SIGNATURES = {
     "mc_step_contract_round": (ctypes.c_int, [P, P, P, I32, P, P, SZ, P, P]),
     "mc_step_components": (ctypes.c_int, [P, I32, I64, P, P, P, P, P, SZ]),
     "mc_step_pr12": (ctypes.c_int, [P, P, I64, P, P, P, P, P, SZ]),
+    "mc_step_certify": (ctypes.c_int, [P, P, I64, P, P, P, P, P, SZ]),
     "mc_step_lp": (ctypes.c_int, [P, P, P, P, P, SZ]),
     "mc_step_pr34": (ctypes.c_int, [P, P, I64, I32, P, P, P, P, P, P, SZ]),
     "mc_step_capforest": (ctypes.c_int, [P, P, I64, I32, I32, I32, I32, I32, P, P, P, P, P, P, P, P, SZ]),
@@ -424,6 +425,18 @@ class Context:
         _check(lib().mc_step_pr34(self.h, ctypes.byref(g.c()), lam, D, _ptr(p), _ptr(flag), _ptr(acc), _ptr(lab),
                                   ctypes.byref(n2), ctypes.c_void_p(ws.data_ptr()), ws.numel()))
         return flag, acc[:g.n].cpu().numpy(), lab[:g.n].cpu().numpy(), n2.value
+
+    def step_certify(self, g, lam, start=None):
+        """The edge-disjoint subgraphs' test on device graph g (see
+        mc_step_certify): (labels, their number, trees joined)."""
+        torch = _torch()
+        p = None if start is None else torch.as_tensor(np.ascontiguousarray(start, np.int32)).to(self.device)
+        lab = torch.empty(g.n, dtype=torch.int32, device=self.device)
+        n2, marks = ctypes.c_int32(), ctypes.c_int64()
+        ws = self.step_workspace(g.n, g.cap)
+        _check(lib().mc_step_certify(self.h, ctypes.byref(g.c()), lam, None if p is None else _ptr(p), _ptr(lab),
+                                     ctypes.byref(n2), ctypes.byref(marks), ctypes.c_void_p(ws.data_ptr()), ws.numel()))
+        return lab.cpu().numpy(), n2.value, marks.value
 
     def step_lp(self, g, lab_in):
         """One label-propagation round on device graph g (see mc_step_lp);

@@ -382,12 +382,13 @@ __device__ void add_marks(int32_t joined, unsigned long long* marks) {
     }
 }
 
-// Members join the class's smallest vertex. A member that is a root is hung
-// under it by a plain store: its only other writers are unions of its own
-// descendants with that same vertex, which hang it under that vertex's root,
-// an ancestor of what the store writes, and never hang that root under it
-// (roots are the smallest of their trees, so that root is smaller). 1.6
-// million members: 22 us, by compare-and-swap about 100 us.
+// Members that are roots join the class's smallest vertex by a plain store, and
+// nothing else is written by this launch: each store hangs one tree under
+// another (the vertex is smaller, and roots are the smallest of their trees),
+// so the count is that of the trees joined. Members below other roots follow in
+// k_cert_near; unioned here, they hung roots that their own threads hung again
+// and counted twice (1402 counted of 1142 trees). 1.6 million members: 22 us, by
+// compare-and-swap about 100 us.
 __global__ __launch_bounds__(256) void k_cert_join(CertArgs a) {
     const int32_t n = a.g.n;
     if (unused(a, 0)) return;
@@ -397,25 +398,28 @@ __global__ __launch_bounds__(256) void k_cert_join(CertArgs a) {
         if ((a.active && !a.active[inst]) || !a.member[v]) continue;
         const int32_t rep = a.rep[inst];
         if (v == rep) continue;
-        if (ld_acq(&a.parent[v]) == (int32_t)v) {
+        if (ld_old(&a.parent[v]) == (int32_t)v) {
             st_rel(&a.parent[v], rep);
-            joined++;
-        } else if (uf_union(a.parent, (int32_t)v, rep)) {
             joined++;
         }
     }
     add_marks(joined, a.marks);
 }
 
-// the others look for their class among their first entries (a launch of its
-// own: their unions may move any root)
+// Members below other roots join the class; the others look for their class
+// among their first entries (a launch of its own: these unions may move any root)
 __global__ __launch_bounds__(256) void k_cert_near(CertArgs a) {
     const int32_t n = a.g.n;
     if (unused(a, 0)) return;
     int32_t joined = 0;
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
         const int32_t inst = a.vinst ? a.vinst[v] : 0;
-        if ((a.active && !a.active[inst]) || a.member[v]) continue;
+        if (a.active && !a.active[inst]) continue;
+        if (a.member[v]) {
+            const int32_t rep = a.rep[inst];
+            if (v != rep && ld_old(&a.parent[v]) != rep && uf_union(a.parent, (int32_t)v, rep)) joined++;
+            continue;
+        }
         const int32_t k = a.count[inst];
         if (k == 0 || !a.near[inst]) continue;
         // targets, memberships and first components of all of them in flight

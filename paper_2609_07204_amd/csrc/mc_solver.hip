@@ -1750,6 +1750,35 @@ extern "C" mc_status mc_step_pr34(mc_ctx* c, const mc_dgraph* g, int64_t lam, in
     return MC_OK;
 }
 
+extern "C" mc_status mc_step_certify(mc_ctx* c, const mc_dgraph* g, int64_t lam, const int32_t* start, int32_t* labels,
+                                     int32_t* n2, int64_t* marks, void* ws, size_t bytes) {
+    if (!g || !labels) return fail(MC_E_INVALID_ARG, "mc_step_certify: NULL argument");
+    StepWS w;
+    mc_status r = step_begin(c, g->n, g->cap, 1, ws, bytes, w);
+    if (r != MC_OK) return r;
+    hipStream_t s = c->stream;
+    k_set_lam<<<1, 1, 0, s>>>(w.sc, lam);
+    k_reset_round<<<1, 1, 0, s>>>(w.sc);
+    if (start ? hipMemcpyAsync(w.parent, start, sizeof(int32_t) * (size_t)g->n, hipMemcpyDeviceToDevice, s) != hipSuccess
+              : !uf_init(w.parent, g->n, s))
+        return fail(MC_E_DEVICE, "mc_step_certify: start forest");
+    CertArgs a{};
+    a.g = to_dgraph(g);
+    a.lam = &w.sc->lam;
+    a.ngraphs = 1;
+    a.parent = w.parent;
+    a.marks = &w.sc->marks_cert;
+    // in the contraction's tables, which lie side by side
+    char *const base = (char*)w.cw.tkey, *const end = (char*)w.cw.dslot;
+    if (!cert_carve(a, base, (size_t)(end - base)))
+        return fail(MC_E_INVALID_ARG, "mc_step_certify: the graph's capacity leaves too little room for the subgraphs");
+    if (!certify(a, s) || !uf_labels(w.parent, g->n, labels, w.flag, w.cw.scan_tmp, w.sc, s)) return MC_E_DEVICE;
+    if ((r = sync_read(c, w)) != MC_OK) return r;
+    if (n2) *n2 = c->hsc->n2;
+    if (marks) *marks = (int64_t)c->hsc->marks_cert;
+    return MC_OK;
+}
+
 extern "C" mc_status mc_step_lp(mc_ctx* c, const mc_dgraph* g, const int32_t* lab_in, int32_t* lab_out, void* ws,
                                 size_t bytes) {
     if (!g || !lab_out) return fail(MC_E_INVALID_ARG, "mc_step_lp: NULL argument");
