@@ -268,7 +268,7 @@ __global__ __launch_bounds__(256) void k_cert_compress(CertArgs a, int sweep) {
 __global__ __launch_bounds__(256) void k_cert_sweep(CertArgs a, int sweep) {
     const int32_t n = a.g.n;
     const int i = blockIdx.y;
-    if ((sweep > 1 && a.more[i] != sweep - 1) || unused(a, i)) return;
+    if ((sweep > 1 && a.more[i] < sweep - 1) || unused(a, i)) return;   // (this sweep's stamp may be there already)
     int32_t* par = a.own + (int64_t)i * n;
     const int32_t* next = a.own + (int64_t)(a.kc + i) * n;
     bool apart = false;
