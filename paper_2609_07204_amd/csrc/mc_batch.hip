@@ -273,18 +273,27 @@ __global__ void k_bg_fallback(const int32_t* voff, const int32_t* voff2, const u
     if (lane_id() == 0 && c) atomicAdd(cnt, c);
 }
 
+// the graphs in prun and their vertices, added to cnt[0] and cnt[1]
+__device__ __forceinline__ void count_running(int32_t graphs, int32_t vertices, int32_t* cnt) {
+    graphs = wave_sum_i32(graphs);
+    vertices = wave_sum_i32(vertices);
+    if (lane_id() == 0 && graphs) {
+        atomicAdd(&cnt[0], graphs);
+        atomicAdd(&cnt[1], vertices);
+    }
+}
+
 // graphs whose unions so far leave more than half of their vertices
-// (voff2: prefix counts of the component roots) go on to the next test;
-// *cnt counts them
+// (voff2: prefix counts of the component roots) go on to the next test
 __global__ void k_bg_unhalved(const int32_t* voff, const int32_t* voff2, int32_t k, uint8_t* prun,
                               int32_t* cnt) {
-    int32_t c = 0;
+    int32_t c = 0, v = 0;
     for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < k; i += gridDim.x * blockDim.x) {
-        if (2 * (int64_t)(voff2[i + 1] - voff2[i]) <= voff[i + 1] - voff[i]) prun[i] = 0;
-        c += prun[i];
+        const int32_t n = voff[i + 1] - voff[i];
+        if (2 * (int64_t)(voff2[i + 1] - voff2[i]) <= n) prun[i] = 0;
+        if (prun[i]) { c++; v += n; }
     }
-    c = wave_sum_i32(c);
-    if (lane_id() == 0 && c) atomicAdd(cnt, c);
+    count_running(c, v, cnt);
 }
 
 // threshold of the loosely connected parts of the graphs in prun; out: the
@@ -308,9 +317,13 @@ __global__ void k_bg_threshold(const int32_t* voff2, const int64_t* dmin, int32_
     }
 }
 
-__global__ void k_bg_drop(const uint8_t* lowered, int32_t k, uint8_t* prun) {
-    for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < k; i += gridDim.x * blockDim.x)
+__global__ void k_bg_drop(const uint8_t* lowered, const int32_t* voff, int32_t k, uint8_t* prun, int32_t* cnt) {
+    int32_t c = 0, v = 0;
+    for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < k; i += gridDim.x * blockDim.x) {
         if (lowered[i]) prun[i] = 0;
+        if (prun[i]) { c++; v += voff[i + 1] - voff[i]; }
+    }
+    count_running(c, v, cnt);
 }
 
 __global__ void k_bg_part_side(const int32_t* vinst, const uint8_t* hit, const int32_t* part, const int32_t* darg,
@@ -895,6 +908,11 @@ struct Engine {
         return a;
     }
 
+    // graphs that stay in prun, and their vertices
+    struct Running {
+        int32_t graphs, vertices;
+    };
+
     // One round for every graph in the engine. Graphs whose result became
     // final are appended to `finished` (their sides are then read with
     // side_of); graphs finished in the previous round leave the union graph.
@@ -971,6 +989,7 @@ struct Engine {
         // only on the graphs left for CAPFOREST (all of 384 graphs: 2.1 ms)
         const bool automatic = c->opt.capforest_mode == MC_CF_AUTO && !c->opt.deterministic;
         bool ran34 = false;
+        Running left{k, n};   // the graphs that they look at
         auto tests34 = [&](const uint8_t* active) {
             ran34 = tri_on;
             return !tri_on || pr34(G, w.lam, c->opt.pr_tri_deg_cap, w.parent, &w.sc->marks_tri, w.tw.ptr2, w.tw, nullptr,
@@ -996,17 +1015,16 @@ struct Engine {
             ca.marks = &w.sc->marks_cert;
             char* const base = (char*)Nx.col;
             const bool room = cert_carve(ca, base, (size_t)((char*)(Nx.w + Nx.cap) - base));
-            int32_t running = 0;
-            EG_OK(unhalved(k, &running));
-            if (room && running > 0) {
+            EG_OK(unhalved(k, &left));
+            if (room && left.graphs > 0) {
                 EG_OK(certify(ca, s));
-                EG_OK(unhalved(k, &running));
-                if (running > 0) {
-                    const mc_status r = threshold_bounds(G, ca, k);
+                EG_OK(unhalved(k, &left));
+                if (left.graphs > 0) {
+                    const mc_status r = threshold_bounds(G, ca, k, &left);
                     if (r != MC_OK) return r;
                 }
             }
-            if (running > 0) EG_OK(tests34(w.prun));
+            if (left.graphs > 0) EG_OK(tests34(w.prun));
         }
         PrivateArgs pa = w.pv;
         pa.g = G;
@@ -1035,7 +1053,9 @@ struct Engine {
         int32_t hcnt[4];
         EG_HIP(hipMemcpyAsync(hcnt, w.cnt, sizeof(hcnt), hipMemcpyDeviceToHost, s));
         if (!readback()) return mc_fail(MC_E_DEVICE, "readback failed");
-        if (ran34 && c->hsc->marks_tri * 100 < (unsigned long long)std::max(n, 1)) tri_on = false;
+        // tests 3 and 4 stop once they gain less than one contraction per 100
+        // vertices of the graphs that they looked at
+        if (ran34 && c->hsc->marks_tri * 100 < (unsigned long long)std::max(left.vertices, 1)) tri_on = false;
         if (hcnt[0] > 0) {
             // Algorithm 2: graphs without a contractible edge get one complete
             // pass; first take the sides of the truncated passes' prefixes
@@ -1114,16 +1134,19 @@ struct Engine {
         return MC_OK;
     }
 
-    // drops the graphs that this round's unions have halved from prun;
-    // *running: those that stay
-    bool unhalved(int32_t k, int32_t* running) {
-        if (!uf_labels(w.parent, n, w.L, w.flag, w.cw.scan_tmp, w.sc, s) || !fill_i32(w.cnt + 1, 0, 1, s)) return false;
+    bool read_running(Running* left) {
+        MC_HIP(hipMemcpyAsync(left, w.cnt + 1, sizeof(*left), hipMemcpyDeviceToHost, s));
+        MC_HIP(hipStreamSynchronize(s));
+        return true;
+    }
+
+    // drops the graphs that this round's unions have halved from prun
+    bool unhalved(int32_t k, Running* left) {
+        if (!uf_labels(w.parent, n, w.L, w.flag, w.cw.scan_tmp, w.sc, s) || !fill_i32(w.cnt + 1, 0, 2, s)) return false;
         k_bg_offsets<<<grid_for(k + 1, 256), 256, 0, s>>>(w.flag, w.voff, k, w.voff2);
         k_bg_unhalved<<<grid_for(k, 256), 256, 0, s>>>(w.voff, w.voff2, k, w.prun, w.cnt + 1);
         MC_LAUNCHED("k_bg_unhalved");
-        MC_HIP(hipMemcpyAsync(running, w.cnt + 1, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-        MC_HIP(hipStreamSynchronize(s));
-        return true;
+        return read_running(left);
     }
 
     // Lower bounds of the graphs that no test halved (prun), from their more
@@ -1136,7 +1159,7 @@ struct Engine {
     // arguments at the graphs' bounds. The coarse graphs take the two
     // union-graph buffers that are not current, the vertex maps the lists of
     // CAPFOREST's passes, and the targets and flags admission's arrays.
-    mc_status threshold_bounds(const DGraph& G, CertArgs ca, int32_t k) {
+    mc_status threshold_bounds(const DGraph& G, CertArgs ca, int32_t k, Running* left) {
         int64_t* const target = w.h_dmin;
         uint8_t* const left_out = w.dead2;
         int32_t *const par = w.pv.order, *const inst = w.pv.fifo, *const map = w.pv.touched;
@@ -1182,8 +1205,10 @@ struct Engine {
         k_bg_side<<<grid_for(n0_used, 256), 256, 0, s>>>(w.side, w.map0, w.inst0, n0_used, w.snap, w.darg, w.inpref,
                                                           w.fside);
         k_bg_clear_snap<<<grid_for(k, 256), 256, 0, s>>>(w.snap, k);
-        k_bg_drop<<<grid_for(k, 256), 256, 0, s>>>(w.lowered, k, w.prun);
+        EG_OK(fill_i32(w.cnt + 1, 0, 2, s));
+        k_bg_drop<<<grid_for(k, 256), 256, 0, s>>>(w.lowered, w.voff, k, w.prun, w.cnt + 1);
         EG_OK(mc_hip_ok(hipGetLastError(), "threshold sides"));
+        EG_OK(read_running(left));
         return MC_OK;
     }
 
