@@ -1077,9 +1077,9 @@ static mc_status exact_rounds(Solver& S, int src) {
             if (!skip_cf && S.heur_pending) {
                 prof_round_cancel();
                 S.heur_pending = false;
-                S.cert_max_n = INT32_MAX;
                 if ((r = heuristic(S)) != MC_OK || !iota_i32(w.map0, S.n0, s)) return r != MC_OK ? r : MC_E_DEVICE;
                 S.cur_m = m_first;
+                S.cert_max_n = INT32_MAX;   // (the rounds on its coarse graph lower it)
                 if (S.lam < before || S.disconnected) continue;
             }
             if (!skip_cf && !S.bound_tried) {
