@@ -535,7 +535,7 @@ __global__ __launch_bounds__(LDS_PT) void k_capforest_lds(PrivateArgs a) {
     }
     __syncthreads();
     int64_t alpha = 0, best_alpha = INT64_MAX;
-    int32_t best_len = 0, nscan = 0, steps = 0;
+    int32_t best_len = 0, nscan = 0, steps = 0, singles = 0, maxbatch = 0;
     int64_t marks = 0;
     for (int s = 0;; s = s == 2 ? 0 : s + 1, steps++) {
         const int32_t budget = a.len_cap > 0 ? a.len_cap - nscan : n;
@@ -585,6 +585,8 @@ __global__ __launch_bounds__(LDS_PT) void k_capforest_lds(PrivateArgs a) {
         if (tid == 0) { const int z = s == 2 ? 0 : s + 1; sum[z] = 0; cnt[z] = 0; }
         __syncthreads();
         const int32_t b = cnt[s] < budget ? cnt[s] : budget;
+        singles += !batch;
+        maxbatch = b > maxbatch ? b : maxbatch;
         // ---- their rows: one by all threads, or a row a wavefront
         int64_t inside = 0;
         auto entry = [&](int32_t x, int32_t j) {
@@ -633,6 +635,10 @@ __global__ __launch_bounds__(LDS_PT) void k_capforest_lds(PrivateArgs a) {
         a.alpha_len[p] = best_len;
         a.lam_out[p] = lam;
         if (a.steps) a.steps[p] = steps;
+        if (a.diag) {   // (vertices touched, entries and times are not counted here)
+            const int64_t d[8] = {steps, singles, 0, 0, 0, 0, nscan, maxbatch};
+            for (int k = 0; k < 8; k++) a.diag[p * 8 + k] = d[k];
+        }
     }
 }
 

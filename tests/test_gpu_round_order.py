@@ -51,3 +51,29 @@ def test_subgraphs_are_tried_again_at_the_heuristics_bound():
     # at the smallest degree, then at the heuristic's bound, before a lower one is looked for
     assert len(tried) >= 2 and "lam=59" in lines[tried[0]] and "lam=20" in lines[tried[1]], lines
     assert not any("threshold" in l for l in lines[:tried[1]]), lines
+
+
+# passes with their state in LDS report their own steps, not those of an earlier launch
+PRIVATE = """
+import numpy as np
+import gen
+import paper_2609_07204_amd as mc
+r = np.random.default_rng(1)
+for n in (20000, 1500, 1500):
+    p = r.permutation(n)
+    u, v = np.concatenate([p, r.integers(0, n, 2 * n)]), np.concatenate([np.roll(p, 1), r.integers(0, n, 2 * n)])
+    g = gen.from_edges(n, u, v, r.integers(50, 100, u.size))
+    mc.Context(0, capforest_mode=0, capforest_passes=2, heuristic_min_n=0, pr_tri_deg_cap=0).mincut(g)
+"""
+
+
+def test_lds_passes_report_their_steps():
+    import re
+    lines = [l for l in debug_lines(PRIVATE) if "passes=2" in l]
+    seen = 0
+    for l in lines:
+        n, steps, singles, scans, batch = (int(re.search(p, l).group(1)) for p in (
+            r" n=(\d+) ", r"steps max (\d+) ", r"singles max (\d+) ", r"scans max (\d+) ", r"maxbatch (\d+)"))
+        assert 1 <= scans <= n and 1 <= batch <= scans and 1 <= singles <= steps <= scans, l
+        seen += n <= 16256
+    assert seen, lines
