@@ -319,7 +319,9 @@ mc_status mc_server_destroy(mc_server* srv);
 /* Check and queue a copy of host graph g; *ticket identifies it. The
  * checks' error (MC_E_INVALID_ARG, MC_E_BAD_GRAPH, MC_E_OVERFLOW) is
  * returned at once and nothing is queued; MC_E_OOM when the graph alone
- * exceeds what the server can ever admit. */
+ * exceeds what the server can ever admit (it is not copied then). The host
+ * memory of the copies is kept for later requests when theirs are polled,
+ * up to 512 MB until the server is destroyed. */
 mc_status mc_server_submit(mc_server* srv, const mc_csr* g, uint64_t* ticket);
 /* Collect, admit, run one round, collect. *in_flight / *queued (may be
  * NULL): requests running (engine and solo slots) and waiting after the

@@ -1809,22 +1809,20 @@ extern "C" mc_status mc_server_destroy(mc_server* S) {
 extern "C" mc_status mc_server_submit(mc_server* S, const mc_csr* g, uint64_t* ticket) {
     if (!S || !g || !ticket) return mc_fail(MC_E_INVALID_ARG, "mc_server_submit: NULL argument");
     if (g->location != MC_HOST) return mc_fail(MC_E_INVALID_ARG, "mc_server_submit: host graphs only");
-    // the request's contents are checked here, so admission never fails on
-    // data
     if (g->n < 2 || g->nnz < 0) return check_host_csr(g, false);
-    mc_server::Req r;
-    if (!r.data.make(&S->pool, g->n, g->nnz)) return mc_fail(MC_E_OOM, "mc_server_submit: out of host memory");
-    mc_status v = check_host_csr(g, S->c->opt.validate != 0, r.data.col(), r.data.w());
-    if (v != MC_OK) return v;
     const Caps& cp = S->E.cap;
-    if (g->n >= S->solo_min_n) {
-        size_t need = 0;
-        need = workspace_min_bytes(S->c, g->n, g->nnz);
-        if (S->slots.empty() || need > S->solo_bytes)
-            return mc_fail(MC_E_OOM, "mc_server_submit: graph larger than the server admits");
-    } else if (g->n > cp.nmax || g->n > cp.Ns || g->nnz > cp.Cs || g->n > cp.N || g->nnz > cp.C) {
-        return mc_fail(MC_E_OOM, "mc_server_submit: graph larger than the server admits");
-    }
+    const bool admits = g->n >= S->solo_min_n
+                            ? !S->slots.empty() && workspace_min_bytes(S->c, g->n, g->nnz) <= S->solo_bytes
+                            : g->n <= cp.nmax && g->n <= cp.Ns && g->nnz <= cp.Cs && g->n <= cp.N && g->nnz <= cp.C;
+    // the request's contents are checked here, so admission never fails on
+    // data, and copied in the same pass; one too large is checked only (what is
+    // wrong with it comes first)
+    mc_server::Req r;
+    if (admits && !r.data.make(&S->pool, g->n, g->nnz)) return mc_fail(MC_E_OOM, "mc_server_submit: out of host memory");
+    const mc_status v = admits ? check_host_csr(g, S->c->opt.validate != 0, r.data.col(), r.data.w())
+                               : check_host_csr(g, S->c->opt.validate != 0);
+    if (v != MC_OK) return v;
+    if (!admits) return mc_fail(MC_E_OOM, "mc_server_submit: graph larger than the server admits");
     r.n = g->n;
     r.nnz = g->nnz;
     std::copy(g->row_ptr, g->row_ptr + g->n + 1, r.data.rp());
