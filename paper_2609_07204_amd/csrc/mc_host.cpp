@@ -6,7 +6,7 @@
 
 #include <algorithm>
 #include <cstring>
-#include <system_error>
+#include <exception>
 #include <thread>
 #include <utility>
 #include <vector>
@@ -115,8 +115,8 @@ bool all_entries_ok(const mc_csr* g, int32_t* ccol, int64_t* cw) {
     for (int q = 1; q < parts; q++) {
         try {
             th[q] = std::thread(part, q);
-        } catch (const std::system_error&) {
-            part(q);   // no thread to be had: here
+        } catch (const std::exception&) {
+            part(q);   // no thread, or no memory for one: here (others are running and are joined below)
         }
     }
     part(0);
