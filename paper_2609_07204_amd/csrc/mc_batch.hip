@@ -1501,6 +1501,7 @@ extern "C" mc_status mc_batch_autotune(mc_ctx* c, int32_t k, const mc_csr* gs, v
 #include <atomic>
 #include <deque>
 #include <memory>
+#include <new>
 #include <thread>
 #include <unordered_map>
 
@@ -1530,10 +1531,17 @@ public:
         *cap = bytes;
         return std::malloc(bytes);
     }
-    void give(void* p, size_t cap) {
-        if (held_ + cap > kPoolBytes) { std::free(p); return; }
-        free_.push_back({p, cap});
-        held_ += cap;
+    // (called by destructors: nothing may leave it)
+    void give(void* p, size_t cap) noexcept {
+        try {
+            if (held_ + cap <= kPoolBytes) {
+                free_.push_back({p, cap});
+                held_ += cap;
+                return;
+            }
+        } catch (const std::bad_alloc&) {
+        }
+        std::free(p);
     }
 
 private:
