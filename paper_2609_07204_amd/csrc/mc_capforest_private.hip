@@ -56,9 +56,7 @@ __device__ __forceinline__ void l1_max(int64_t* lg, long long* ls, int32_t b, in
 }
 
 constexpr int LDS_PT = 1024;
-constexpr int LDS_N = 16256;                    // 10 B a vertex and the step's sums: a workgroup's 160 KB
 constexpr int LDS_VBITS = 14;
-constexpr int64_t LDS_LAM = (int64_t)1 << 48;   // keys are packed above the bits of a vertex
 static_assert(LDS_N <= 1 << LDS_VBITS && LDS_N <= INT16_MAX, "vertex in a key and in the list");
 __device__ __forceinline__ bool lds_pass(int32_t n, int64_t lam) { return n <= LDS_N && lam < LDS_LAM; }
 

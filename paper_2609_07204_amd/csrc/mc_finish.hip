@@ -730,7 +730,8 @@ __global__ __launch_bounds__(FT) void k_finish(FinishArgs a, int32_t count) {
 
 // One pass of the finisher's CAPFOREST on its own (parity and measurement):
 // graph g (n <= FIN_N, rows at off/len, local targets), from `start` at
-// bound lam, with the queue of qmode (1 buckets, 2 heap). Writes the marks
+// bound lam, with the queue of qmode (0 the workgroup's batch pass, 1 buckets,
+// 2 heap). Writes the marks
 // as a union-find forest to parent[n] (roots smallest), the scan order and
 // its length, the bound after the pass (lam_io), the smallest proper-prefix
 // alpha (INT64_MAX if none) and its prefix length.
@@ -748,7 +749,17 @@ __global__ __launch_bounds__(FT) void k_fin_pass(DGraph g, int32_t start, int32_
         S.parent[v] = v;
     }
     __syncthreads();
-    if (tid < MC_WAVE) {
+    if (qmode == 0 && lam_io[0] < FKEY) {
+        const PassOut po = fin_pass_batch(S, n, g.col, g.w, 0, start, lam_io[0]);
+        __syncthreads();   // (every thread has read the bound)
+        if (tid == 0) {
+            lam_io[0] = po.lam;
+            best_alpha[0] = po.best_alpha < 0 ? INT64_MAX : po.best_alpha;
+            nscan_out[0] = po.nscan;
+            best_len[0] = po.best_len;
+            scal[6] = po.nscan;
+        }
+    } else if (tid < MC_WAVE) {
         const PassOut po = fin_pass(S, n, g.col, g.w, 0, start, lam_io[0], qmode == 2 || lam_io[0] >= FQB, scal);
         if (tid == 0) {
             lam_io[0] = po.lam;

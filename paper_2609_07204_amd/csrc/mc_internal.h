@@ -355,6 +355,9 @@ struct CompleteArgs {
 };
 bool capforest_complete(const CompleteArgs& a, hipStream_t s);
 
+constexpr int LDS_N = 16256;                    // vertices of a pass in LDS: 10 B each and the step's sums, a workgroup's 160 KB
+constexpr int64_t LDS_LAM = (int64_t)1 << 48;   // its bounds: keys are packed above the bits of a vertex
+
 // Private passes with capped batches: `passes` workgroups, each one pass
 // with its own dense state over the vertices (no shared visited array), so
 // passes never fragment each other's traversal. All queued vertices whose

@@ -1799,8 +1799,10 @@ extern "C" mc_status mc_step_capforest(mc_ctx* c, const mc_dgraph* g, int64_t la
                                        int32_t* order, int32_t* nscan, int64_t* best_alpha, int32_t* best_len,
                                        int64_t* lam_out, void* ws, size_t bytes) {
     if (!g || !labels || !order) return fail(MC_E_INVALID_ARG, "mc_step_capforest: NULL argument");
-    if (mode < MC_STEP_CF_SHARED || mode > MC_STEP_CF_HEAP) return fail(MC_E_INVALID_ARG, "mc_step_capforest: bad mode");
-    if (mode == MC_STEP_CF_BUCKET || mode == MC_STEP_CF_HEAP) {
+    if (mode < MC_STEP_CF_SHARED || mode > MC_STEP_CF_LDS) return fail(MC_E_INVALID_ARG, "mc_step_capforest: bad mode");
+    if (mode == MC_STEP_CF_LDS && (g->n > LDS_N || lam >= LDS_LAM))
+        return fail(MC_E_INVALID_ARG, "mc_step_capforest: the pass in LDS takes n <= 16256 and lam < 2^48");
+    if (mode == MC_STEP_CF_BUCKET || mode == MC_STEP_CF_HEAP || mode == MC_STEP_CF_BATCH) {
         // one pass of the finisher's CAPFOREST, queue in LDS
         if (g->n > FIN_N) return fail(MC_E_INVALID_ARG, "mc_step_capforest: the LDS-queue pass takes n <= 1024");
         if (start < 0 || start >= g->n) return fail(MC_E_INVALID_ARG, "mc_step_capforest: bad start");
@@ -1809,7 +1811,7 @@ extern "C" mc_status mc_step_capforest(mc_ctx* c, const mc_dgraph* g, int64_t la
         if (r != MC_OK) return r;
         hipStream_t s = c->stream;
         if (!fill_i64(w.lamout, lam, 1, s)) return MC_E_DEVICE;
-        if (!finish_pass(to_dgraph(g), start, mode == MC_STEP_CF_HEAP ? 2 : 1, w.lamout, w.alpha, w.parent, order,
+        if (!finish_pass(to_dgraph(g), start, mode == MC_STEP_CF_HEAP ? 2 : mode == MC_STEP_CF_BUCKET ? 1 : 0, w.lamout, w.alpha, w.parent, order,
                          w.nscan, w.alen, s))
             return fail(MC_E_DEVICE, "mc_step_capforest: finisher pass launch failed");
         if (!uf_labels(w.parent, g->n, labels, w.flag, w.cw.scan_tmp, w.sc, s)) return MC_E_DEVICE;
@@ -1898,6 +1900,7 @@ extern "C" mc_status mc_step_capforest(mc_ctx* c, const mc_dgraph* g, int64_t la
         pa.start = start;
         pa.marks = &w.sc->marks_cf;
         pa.steps = w.psteps;
+        pa.lds = mode == MC_STEP_CF_LDS;
         if (!capforest_private_reset(pa, s)) return MC_E_DEVICE;
         if (mode == MC_STEP_CF_LEVELS) {
             StepArgs sa = w.sa;
