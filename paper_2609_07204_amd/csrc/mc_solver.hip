@@ -737,12 +737,15 @@ static void debug_round(Solver& S, const DGraph& g, int32_t round, int32_t passe
 constexpr int32_t kProbeScans = 32;
 constexpr int32_t kProbePasses = 4;
 constexpr int32_t kProbePrivate = 4096;   // scans per private pass in a probe round
-// A private run of that many scans takes 1.4 ms or more with one workgroup a
-// pass (3,600 vertices) and 20 to 25 ms in whole-GPU steps (hyperbolic cores
-// of 95,000 to 600,000 vertices, where it joined 3,500 vertices and the
-// shared probe 14,000 in 0.2 ms; solves at 95,000 vertices 33 ms with it, 10 ms
-// without).
-constexpr double kPrivateMs = 1.4, kPrivateStepsMs = 4.0;
+// The least time that a private run of so many scans was seen to take: at most n
+// vertices can be joined in it, so where n per that time is below the shared
+// probe's rate the run cannot win and is left out. Geometric graphs of 20,000
+// to 60,000 vertices, one workgroup a pass: 1.02 to 30 ms; of 70,000 to 600,000,
+// whole-GPU steps: 2.2 to 47 ms (a hyperbolic core of 95,000 vertices: 20 ms for
+// 3,500 vertices where the shared probe joined 14,000 in 0.2 ms; solves 33 ms
+// with it, 10 ms without). Passes in LDS took 5.1 ms and more, on graphs whose
+// probes joined too little for the rule to hold.
+constexpr double kPrivateMs = 1.0, kPrivateStepsMs = 2.0;
 static bool shared_passes(Solver& S, const DGraph& g, bool probe) {
     SolveWS& w = S.w;
     CapforestArgs ca{};
@@ -1141,8 +1144,7 @@ static mc_status exact_rounds(Solver& S, int src) {
                 double ms_p = 0;
                 unsigned long long marks_p = 0;
                 if (marks_s * 1024 >= (unsigned long long)n && (double)n * ms_s < (reg == 0 ? kPrivateStepsMs : kPrivateMs) * (double)marks_s) {
-                    // private passes would have to join every vertex in
-                    // less than the least time they take to be the faster form
+                    // (kPrivateMs: private passes cannot be the faster form)
                     form = CF_RUN_SHARED;
                     if (!shared_passes(S, *cur, false)) return MC_E_DEVICE;
                 } else if (marks_s * 1024 >= (unsigned long long)n) {
