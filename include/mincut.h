@@ -169,7 +169,7 @@ typedef struct {
 typedef struct mc_ctx mc_ctx;
 
 /* Default options (seed 1, heuristic at n >= 10000, 2 LP rounds, automatic
- * pass count and length, private passes, no validation). */
+ * pass count, length and visited-array policy, no validation). */
 void mc_default_options(mc_options* opt);
 
 /* Create a context on HIP device `device` issuing all work on `hip_stream`

@@ -29,10 +29,11 @@
 // coalesced comparison of k words a vertex. Others look for a neighbour of
 // their own class among their first CERT_NEAR entries.
 //
-// Solves on MI355X, with CAPFOREST alone and with this test before it (the
-// label-propagation bound first in both): Erdos-Renyi, 300,000 vertices, mean
-// degree 24, weights to 1000: 174 and 7.6 ms; Chung-Lu 2^20 and 2^22, 10-cores,
-// unit weights: 6.9 and 4.7 ms, 14.0 and 11.1 ms.
+// Solves on MI355X with CAPFOREST alone, with this test's first form before it
+// (the label-propagation bound first in both), and now, with the tests before
+// that bound: Erdos-Renyi, 300,000 vertices, mean degree 24, weights to 1000:
+// 174, 7.6 and 0.97 ms; Chung-Lu 2^20 and 2^22, 10-cores, unit weights: 6.9, 4.7
+// and 1.11 ms, 14.0, 11.1 and 2.55 ms.
 //
 // The kernels are bound by the k n random reads of the two compressions and
 // of the linking, not by the rows: one pass over the entries (12 B each, and
@@ -491,8 +492,13 @@ bool certify(const CertArgs& a, hipStream_t s) {
     k_cert_plan<<<grid_for(a.ngraphs, 256), 256, 0, s>>>(a);
     k_cert_rows<<<grid_for(n, ROWS), 256, 0, s>>>(a);
     MC_LAUNCHED("k_cert_rows");
-    // small graphs are bound by the launches: the probe's seven would cost
-    // more than they can save
+    // The probe's 2 CERT_SWEEPS + 3 launches cost a graph that it lets through
+    // about 40 us (Erdos-Renyi, 20,000 vertices: 377 and 416 us a solve), and
+    // small ones are bound by their launches. From 32,768 vertices on it is
+    // mixed: hyperbolic cores of 79,000 to 116,000 vertices 1.71 to 2.71 ms with
+    // it, 1.95 to 2.94 ms without; Erdos-Renyi graphs of 60,000 519 and 483 us;
+    // some geometric graphs that it leaves out would be joined (45,000 vertices:
+    // 2.5 ms, 0.45 ms without).
     if (n >= CERT_PROBE_N) {
         if (!components(a, 1, s)) return false;
         k_cert_probe<<<gg, 64, 0, s>>>(a);
